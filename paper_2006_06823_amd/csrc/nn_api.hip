@@ -90,7 +90,10 @@ class Net {
     if (gbuf_) (void)hipFree(gbuf_);
     if (dbuf_[0]) (void)hipFree(dbuf_[0]);
     if (dbuf_[1]) (void)hipFree(dbuf_[1]);
+    if (packed_) (void)hipFree(packed_);
+    if (part_) (void)hipFree(part_);
     if (P_) (void)hipFree(P_);
+    if (stage_) (void)hipFree(stage_);
     if (diff_) (void)hipFree(diff_);
     if (Lw_) (void)hipFree(Lw_);
     if (work_) (void)hipFree(work_);
@@ -149,11 +152,12 @@ class Net {
 
   void forward(const float* in, int B, float* out) {
     ensure(B);
+    pack_weights(layers_.data(), packed_at_.data(), (int)layers_.size(), false, st_);
     const float* x = in;
     in_ = in;
     for (size_t l = 0; l < layers_.size(); ++l) {
       float* y = (l + 1 == layers_.size()) ? out : acts_[l];
-      conv_forward(layers_[l], x, y, B, sizes_[l], st_);
+      conv_forward(layers_[l], x, y, B, sizes_[l], packed_at_[l], st_);
       x = y;
     }
     out_ = out;
@@ -164,12 +168,14 @@ class Net {
   // accumulates parameter gradients for the last forward pass
   void backward(const float* dout, int B) {
     if (B != lastB_ || !out_) throw StateError("backward needs a forward pass with the same batch");
+    // (the first layer has no data gradient)
+    pack_weights(layers_.data() + 1, packed_at_.data() + 1, (int)layers_.size() - 1, true, st_);
     const float* dy = dout;
     for (int l = static_cast<int>(layers_.size()) - 1; l >= 0; --l) {
       const float* x = l == 0 ? in_ : acts_[l - 1];
       const float* y = (l + 1 == (int)layers_.size()) ? out_ : acts_[l];
       float* dx = l == 0 ? nullptr : dbuf_[l & 1];
-      conv_backward(layers_[l], x, y, dy, gbuf_, dx, B, sizes_[l], st_);
+      conv_backward(layers_[l], x, y, dy, gbuf_, dx, B, sizes_[l], packed_at_[l], part_, st_);
       dy = dx;
     }
     LDDMM_HIP(hipStreamSynchronize(st_));
@@ -205,7 +211,7 @@ class Net {
   // network output [B][3(1+r)][s^3] -> coefficients [B][1+r][3][k0][k1][k2] (velocity, then directions)
   void velocity(const float* out, int B, const int k[3], float* v) {
     check_velocity_args(B, k);
-    samples_to_bl(out, proj(), B * (1 + rank_), 1, out_size_, k, v, st_);
+    samples_to_bl(out, proj(), B * (1 + rank_), 1, out_size_, k, v, stages(B * (1 + rank_)), st_);
     LDDMM_HIP(hipStreamSynchronize(st_));
   }
 
@@ -223,7 +229,7 @@ class Net {
     }
     weights(k, alpha, s_exp);
     const int gs = 1 + rank_;  // the velocity channels are the first 3 of each sample's 3 (1 + r)
-    samples_to_bl(out, proj(), B, gs, out_size_, k, diff_, st_);
+    samples_to_bl(out, proj(), B, gs, out_size_, k, diff_, stages(B), st_);
     bl_axpby<float>(diff_, 1.f, diff_, -1.f, vt, n, st_);
     if (!work_) {
       if (hipMalloc(&work_, sizeof(double) * reduce_work_size()) != hipSuccess) throw std::bad_alloc();
@@ -234,7 +240,7 @@ class Net {
     if (dout) {
       // the loss does not depend on the direction channels
       if (rank_ > 0) fill(dout, (int64_t)B * out_channels() * out_size_ * out_size_ * out_size_, 0.f, st_);
-      block_grad(diff_, Lw_, proj(), B, gs, out_size_, k, 2.f / B, dout, st_);
+      block_grad(diff_, Lw_, proj(), B, gs, out_size_, k, 2.f / B, dout, stages(B), st_);
     }
     LDDMM_HIP(hipStreamSynchronize(st_));
     return l;
@@ -245,6 +251,16 @@ class Net {
     if (B < 1) throw ArgError("batch must be >= 1");
     for (int j = 0; j < 3; ++j)
       if (k[j] < out_size_ - 1 || k[j] < 2 || k[j] % 2) throw ArgError("band too small for the network output");
+  }
+  float* stages(int B) {
+    const int64_t n = stage_elems(B, out_size_);
+    if (n > stage_cap_) {
+      if (stage_) (void)hipFree(stage_);
+      stage_ = nullptr, stage_cap_ = 0;
+      if (hipMalloc(&stage_, sizeof(float) * n) != hipSuccess) throw std::bad_alloc();
+      stage_cap_ = n;
+    }
+    return stage_;
   }
   // projection onto the out_size-point band: P[a][x] = b_a(x / s) / s in the real basis
   // (slot 0 the constant, 2m-1 / 2m sqrt2 cos / sqrt2 sin of frequency m, last slot zero)
@@ -293,12 +309,15 @@ class Net {
   }
   void ensure(int B) {
     if (B <= capB_) return;
+    capB_ = 0;  // until every buffer below is there
     for (auto* a : acts_) (void)hipFree(a);
     acts_.clear();
-    int64_t maxe = 0;
+    int64_t maxe = 0, maxp = 0, sumw = 0;
     for (size_t l = 0; l < layers_.size(); ++l) {
       const int64_t e = act_elems(static_cast<int>(l), B);
       maxe = std::max(maxe, e);
+      maxp = std::max(maxp, wgrad_part_elems(layers_[l], B, sizes_[l]));
+      sumw += packed_elems(layers_[l]);
       float* a = nullptr;
       if (l + 1 < layers_.size()) {
         if (hipMalloc(&a, sizeof(float) * e) != hipSuccess) throw std::bad_alloc();
@@ -310,9 +329,17 @@ class Net {
     if (gbuf_) (void)hipFree(gbuf_);
     if (dbuf_[0]) (void)hipFree(dbuf_[0]);
     if (dbuf_[1]) (void)hipFree(dbuf_[1]);
-    if (hipMalloc(&gbuf_, sizeof(float) * maxe) != hipSuccess || hipMalloc(&dbuf_[0], sizeof(float) * maxe) != hipSuccess ||
-        hipMalloc(&dbuf_[1], sizeof(float) * maxe) != hipSuccess)
+    if (part_) (void)hipFree(part_);
+    if (packed_) (void)hipFree(packed_);
+    gbuf_ = packed_ = nullptr;
+    dbuf_[0] = dbuf_[1] = part_ = nullptr;
+    if (hipMalloc(&gbuf_, sizeof(unsigned short) * maxe) != hipSuccess || hipMalloc(&dbuf_[0], sizeof(float) * maxe) != hipSuccess ||
+        hipMalloc(&dbuf_[1], sizeof(float) * maxe) != hipSuccess ||
+        hipMalloc(&part_, sizeof(float) * maxp) != hipSuccess ||
+        hipMalloc(&packed_, sizeof(unsigned short) * sumw) != hipSuccess)
       throw std::bad_alloc();
+    packed_at_.clear();
+    for (int64_t l = 0, o = 0; l < (int64_t)layers_.size(); o += packed_elems(layers_[l++])) packed_at_.push_back(packed_ + o);
     capB_ = B;
   }
 
@@ -325,11 +352,16 @@ class Net {
   int64_t nparam_ = 0;
   float* arena_ = nullptr;
   std::vector<float*> acts_;
-  float* gbuf_ = nullptr;
+  unsigned short* gbuf_ = nullptr;    // bf16 gradient after the activation derivative
+  unsigned short* packed_ = nullptr;  // the layers' weights in the kernels' operand order
+  std::vector<unsigned short*> packed_at_;
+  float* part_ = nullptr;             // partial weight gradients
   float* dbuf_[2] = {nullptr, nullptr};
   const float* in_ = nullptr;
   const float* out_ = nullptr;
   float* P_ = nullptr;
+  float* stage_ = nullptr;  // scratch of the separable coefficient maps
+  int64_t stage_cap_ = 0;
   float* diff_ = nullptr;
   int64_t diff_cap_ = 0;
   double* Lw_ = nullptr;
