@@ -1,17 +1,29 @@
 // Tricubic B-spline interpolation at SL departure points through LDS bricks
 // (float, 3D grids).
 //
-// A workgroup owns a 4 x 8 x 32 tile of output nodes.  Per coefficient field
-// it stages the tile plus a 2-node halo on every side (8 x 12 x 36 floats,
-// 13.8 KB) into LDS with coalesced, periodically wrapped loads (the wrapped row
-// offsets and columns are tabulated once per workgroup), then evaluates
-// the 64-tap tensor B-spline for each of its nodes from LDS.  A departure
-// point whose 4 x 4 x 4 stencil leaves the brick (displacement of a voxel or
-// more) falls back to a gather from global memory, so any displacement is
-// handled; at the SL step sizes of the configurations (about 0.8 voxel) every
-// stencil lies in the brick.  The epilogue functor consumes the interpolated
-// values of a node together with its other pointwise operands, fusing the
-// SL-RK2 step update of each equation into the same pass.
+// A workgroup owns a tile of output nodes and stages, per coefficient field, the tile plus two nodes on
+// every side into LDS (16-byte loads, periodically wrapped).  A thread owns four neighbours of a row.  At
+// the SL step sizes of the configurations (about 0.8 voxel) a departure point lies less than a voxel from
+// its node, so its 4 x 4 x 4 stencil lies in the node's own 5 x 5 x 5 neighbourhood: the kernel sums that
+// whole window with five weights per axis, one of them zero.  The addresses then depend on the node alone,
+// and a row of the windows of four neighbours is eight consecutive floats, two 16-byte LDS reads per field.
+//
+// Why the window and not the 64 taps themselves: the taps start where the displacement puts them, so every
+// tap of every node is its own LDS read (64 x 4 bytes per field, at the 128 bytes per clock and CU of reads
+// below 16 bytes, plus a quarter more for bank conflicts), and those reads bounded the kernels: with the
+// arithmetic taken out, the pair kernel at 128^3 kept 26 of its 28 us.  The window's reads
+// are a sixth of that and run at the 256 bytes per clock of aligned 16-byte reads; its 125 products per field
+// instead of 64 cost less than they free (a wave's FMA issues every two clocks).  At 128^3 (Infinity-Cache-resident
+// fields), launches back to back: one field 19.6 -> 15.7 us, the adjoint pair 33.1 -> 23.5 us, three fields
+// 48.0 -> 33.6 us; in a matvec, between other kernels: 21.2 -> 17.8, 31.8 -> 26.1; at 160x192x160 three fields
+// 125 -> 75 us, the three components' pairs 198 -> 149 us.  What
+// bounds it now is the window's arithmetic after a staging phase that a CU's two workgroups reach together
+// (staging alone 11 us of the pair's 23.5, at 6.2 TB/s).
+//
+// A node displaced by a voxel or more is interpolated apart: from the brick where its stencil lies in it,
+// else by a gather from global memory, with the same products in the same order, so a node's value depends on
+// neither the tile nor its neighbours.  The epilogue combines a node's interpolated values with its other
+// pointwise operands, fusing the SL-RK2 step update of each equation into the same pass.
 #include "kernels.h"
 
 #include <climits>
@@ -23,32 +35,34 @@ namespace lddmm {
 
 namespace {
 
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef const __attribute__((address_space(3))) f32x4 lds_f32x4;
+typedef const __attribute__((address_space(3))) float lds_float;
+typedef __amdgpu_buffer_rsrc_t Rsrc;
+
 constexpr int HALO = 2;
 
-// Output tile of one workgroup; the autotuner picks one of these per grid shape.
-// LD2 >= B2 is the LDS row stride of the brick (B2 plus PAD2 unused columns)
-template <int X0, int X1, int X2, int NT, int PAD2 = 0>
+// Output tile of one workgroup; the autotuner picks one of these per grid shape and staging width.
+// A row of the brick holds TX2 + 4 floats (a multiple of 16 bytes), fetched as QB aligned quads from two
+// floats before it to two floats after it
+template <int X0, int X1, int X2, int NT>
 struct Tile {
   static constexpr int TX0 = X0, TX1 = X1, TX2 = X2, NTHR = NT;
-  static constexpr int B0 = TX0 + 2 * HALO, B1 = TX1 + 2 * HALO, B2 = TX2 + 2 * HALO;
-  static constexpr int LD2 = B2 + PAD2;
-  static constexpr int NPT = B0 * B1 * B2;   // staged points
-  static constexpr int VOL = B0 * B1 * LD2;  // LDS floats per field
-  static constexpr int PPT = TX0 * TX1 * TX2 / NTHR;  // nodes per thread
+  static constexpr int B0 = TX0 + 2 * HALO, B1 = TX1 + 2 * HALO, LD = TX2 + 2 * HALO;
+  static constexpr int ROWS = B0 * B1, QB = TX2 / 4 + 2, NQ = ROWS * QB;
+  static constexpr int VOL = ROWS * LD;               // LDS floats per field
+  static constexpr int QPT = TX0 * TX1 * TX2 / 4 / NT;  // quads of nodes per thread
+  static_assert(X2 % 4 == 0 && QPT * NT * 4 == TX0 * TX1 * TX2, "whole quads per thread");
 };
 using TileA = Tile<4, 8, 32, 256>;
 using TileB = Tile<8, 8, 32, 512>;
-using TileC = Tile<2, 16, 32, 256>;
+using TileC = Tile<4, 4, 32, 128>;  // small grids: more workgroups
 using TileD = Tile<4, 4, 64, 256>;
-// 1024-thread tiles for the 160 KB LDS of a gfx950 workgroup: a 16 x 8 x 32 tile re-reads 2.1x its
-// coefficient volume through the halo instead of 2.5x (8 x 8 x 32), and two workgroups fill a CU
-using TileE = Tile<16, 8, 32, 1024>;
-using TileF = Tile<8, 16, 32, 1024>;
-// row strides a multiple of 32 floats: a departure point's bank depends only on its column, so
-// neighbouring lanes in different brick rows no longer collide (3-5x fewer LDS bank conflicts
-// than the unpadded stride 36 at sub-voxel displacements)
-using TileG = Tile<8, 8, 32, 512, 28>;  // row stride 64
-using TileH = Tile<4, 4, 64, 256, 28>;  // row stride 96
+using TileE = Tile<8, 4, 32, 256>;
+using TileF = Tile<4, 16, 32, 512>;
+using TileG = Tile<8, 8, 16, 256>;  // a last tile of 16 on the contiguous axis
+using TileH = Tile<4, 8, 64, 512>;
 constexpr int kTiles = 8;
 
 struct Grid3 {
@@ -60,9 +74,15 @@ __device__ __forceinline__ int wrapi(int i, int n) {
   i %= n;
   return i < 0 ? i + n : i;
 }
+// the same for indices that one period mostly brings back
+__device__ __forceinline__ int wrap_near(int i, int n) {
+  i = i < 0 ? i + n : i >= n ? i - n : i;
+  if ((unsigned)i >= (unsigned)n) i = wrapi(i, n);
+  return i;
+}
 
-// Cubic B-spline weights of a tap offset t in [0, 1): w3 = t^3/6, w0 = (1-t)^3/6, w1 = 2/3 - t^2 (1 - t/2),
-// and w2 from the partition of unity (12 operations instead of the polynomial forms' 15).
+// Cubic B-spline weights of the taps at -1, 0, 1, 2 for an offset t in [0, 1): (1-t)^3/6, 2/3 - t^2 (1 - t/2),
+// the third from the partition of unity, t^3/6.
 __device__ __forceinline__ void brick_weights(float t, float w[4]) {
   const float t2 = t * t, u = 1.f - t;
   w[3] = t2 * (t * (1.f / 6.f));
@@ -70,471 +90,413 @@ __device__ __forceinline__ void brick_weights(float t, float w[4]) {
   w[1] = fmaf(t2, fmaf(t, 0.5f, -1.f), 2.f / 3.f);
   w[2] = 1.f - w[0] - w[1] - w[3];
 }
-
-// LDS views of the brick: with the address space explicit, tap addresses stay 32-bit and the rows of a
-// stencil are reached by immediate offsets from one base per node
-typedef const __attribute__((address_space(3))) float lds_float;
-typedef const __attribute__((address_space(3))) unsigned long long lds_pair;  // two interleaved floats
-
-// p + off as a base the compiler cannot see through: the taps of one slab (row offsets b B2 + c <= 3 B2 + 3)
-// are then reached by the LDS reads' immediate offsets from this one register, instead of an address
-// add per pair of taps (the slab offset itself exceeds the 8-bit offsets of the paired reads)
-template <typename P>
-__device__ __forceinline__ P* opaque_base(P* p, int off) {
-  unsigned u = static_cast<unsigned>(reinterpret_cast<uintptr_t>(p + off));
-  asm volatile("" : "+v"(u));
-  return reinterpret_cast<P*>(static_cast<uintptr_t>(u));
+// Weights of the five nodes at -2 .. 2 for a displacement d, |d| < 1 (those of |d|, mirrored for d < 0)
+__device__ __forceinline__ void window_weights(float d, float w[5]) {
+  float v[4];
+  brick_weights(fabsf(d), v);
+  const bool neg = d < 0.f;
+  w[0] = neg ? v[3] : 0.f;
+  w[1] = neg ? v[2] : v[0];
+  w[2] = v[1];
+  w[3] = neg ? v[0] : v[2];
+  w[4] = neg ? 0.f : v[3];
 }
 
-// 64-tap evaluation from the LDS brick at the brick-relative first tap (s0, s1, s2).  The stencil is read
-// in four slabs of 4 x 4 taps (first index a), the next slab's reads issued before the current one is
-// summed; empty asm statements (no instruction) keep the compiler from moving a slab's sums below the
-// next slab's reads.
-template <int B1, int B2>
-__device__ __forceinline__ float eval_brick(const float* br, int s0, int s1, int s2, const float w0[4],
-                                            const float w1[4], const float w2[4]) {
-  lds_float* p = (lds_float*)br + ((s0 * B1 + s1) * B2 + s2);
-  float v[2][4][4];
-  auto load = [&](int a, float (&d)[4][4]) {
-    lds_float* q = opaque_base(p, a * B1 * B2);
-#pragma unroll
-    for (int b = 0; b < 4; ++b)
-#pragma unroll
-      for (int c = 0; c < 4; ++c) d[b][c] = q[b * B2 + c];
-  };
-  load(0, v[0]);
-  float acc = 0.f;
-#pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    if (a < 3) load(a + 1, v[(a + 1) & 1]);
-    const float(&d)[4][4] = v[a & 1];
-    float sa = 0.f;
-#pragma unroll
-    for (int b = 0; b < 4; ++b) sa += w1[b] * (w2[0] * d[b][0] + w2[1] * d[b][1] + w2[2] * d[b][2] + w2[3] * d[b][3]);
-    acc += w0[a] * sa;
-    asm volatile("" : "+v"(acc)::"memory");
-  }
-  return acc;
+// Raw buffer accesses: 32-bit byte offsets from a uniform base, 0 for reads at or past the end
+constexpr unsigned kOut = 0xFFFFFFF0u;
+__device__ __forceinline__ Rsrc rsrc(const float* p, int64_t n) {
+  const int64_t bytes = n * 4 < 0x7FFFFFF0 ? n * 4 : 0x7FFFFFF0;
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), (short)0, (int)bytes, 0x00020000);
+}
+__device__ __forceinline__ float bload(Rsrc r, unsigned off) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
+}
+__device__ __forceinline__ f32x4 bload4(Rsrc r, unsigned off) {
+  return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
 }
 
-// two fields stored interleaved (float2): one LDS read per tap serves both, and the products
-// w1[b] w2[c] are formed once for the two
-template <int B1, int B2>
-__device__ __forceinline__ float2 eval_brick2(const float2* br, int s0, int s1, int s2, const float w0[4],
-                                              const float w1[4], const float w2[4]) {
-  lds_pair* p = (lds_pair*)br + ((s0 * B1 + s1) * B2 + s2);
-  float w12[4][4];
-#pragma unroll
-  for (int b = 0; b < 4; ++b)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) w12[b][c] = w1[b] * w2[c];
-  float2 v[2][4][4];
-  auto load = [&](int a, float2 (&d)[4][4]) {
-    lds_pair* q = opaque_base(p, a * B1 * B2);
-#pragma unroll
-    for (int b = 0; b < 4; ++b)
-#pragma unroll
-      for (int c = 0; c < 4; ++c) d[b][c] = __builtin_bit_cast(float2, q[b * B2 + c]);
-  };
-  load(0, v[0]);
-  float ax = 0.f, ay = 0.f;
-#pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    if (a < 3) load(a + 1, v[(a + 1) & 1]);
-    const float2(&d)[4][4] = v[a & 1];
-    float sx = 0.f, sy = 0.f;
-#pragma unroll
-    for (int b = 0; b < 4; ++b)
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        sx = fmaf(w12[b][c], d[b][c].x, sx);
-        sy = fmaf(w12[b][c], d[b][c].y, sy);
-      }
-    ax = fmaf(w0[a], sx, ax);
-    ay = fmaf(w0[a], sy, ay);
-    asm volatile("" : "+v"(ax), "+v"(ay)::"memory");
-  }
-  return make_float2(ax, ay);
+// row sum of four taps, in the order of the window's (whose zero tap adds nothing)
+__device__ __forceinline__ float row4(float a, float b, float c, float d, const float w[4]) {
+  return fmaf(w[3], d, fmaf(w[2], c, fmaf(w[1], b, w[0] * a)));
 }
 
-// GS fields stored one after the other (stride VOL): each slab's reads of every field are issued
-// together, and the products w1[b] w2[c] are shared by the fields
-template <int GS, int B1, int B2, int VOL>
-__device__ __forceinline__ void eval_brick_n(const float* br, int s0, int s1, int s2, const float w0[4],
-                                             const float w1[4], const float w2[4], float out[GS]) {
-  lds_float* p = (lds_float*)br + ((s0 * B1 + s1) * B2 + s2);
-  float w12[4][4];
+// periodic indices of the four taps around the node b
+__device__ __forceinline__ void tap_nodes(int b, int n, int idx[4]) {
+  b = wrapi(b, n);
+  idx[0] = b == 0 ? n - 1 : b - 1;
 #pragma unroll
-  for (int b = 0; b < 4; ++b)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) w12[b][c] = w1[b] * w2[c];
-#pragma unroll
-  for (int k = 0; k < GS; ++k) out[k] = 0.f;
-#pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    float d[GS][4][4];
-#pragma unroll
-    for (int k = 0; k < GS; ++k) {
-      lds_float* q = opaque_base(p, k * VOL + a * B1 * B2);
-#pragma unroll
-      for (int b = 0; b < 4; ++b)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) d[k][b][c] = q[b * B2 + c];
-    }
-#pragma unroll
-    for (int k = 0; k < GS; ++k) {
-      float sk = 0.f;
-#pragma unroll
-      for (int b = 0; b < 4; ++b)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) sk = fmaf(w12[b][c], d[k][b][c], sk);
-      out[k] = fmaf(w0[a], sk, out[k]);
-      asm volatile("" : "+v"(out[k])::"memory");
-    }
-  }
+  for (int o = 1; o < 4; ++o) idx[o] = idx[o - 1] + 1 == n ? 0 : idx[o - 1] + 1;
 }
 
+// 64-tap gather from global memory at the nodes (b0, b1, b2) plus the offsets t in [0, 1)
 // (the grid sizes go by value: a reference would put the caller's Grid3 on the stack, a 24-byte
 // scratch store per lane on every launch whether or not the gather runs)
-__device__ __noinline__ float eval_global(const float* __restrict__ c, float x0, float x1, float x2, int n0, int n1,
-                                          int n2) {
-  const Grid3 g{n0, n1, n2, 0};
+__device__ __noinline__ float eval_global(const float* __restrict__ c, int b0, int b1, int b2, float t0, float t1,
+                                          float t2, int n0, int n1, int n2) {
   int i0[4], i1[4], i2[4];
   float w0[4], w1[4], w2[4];
-  bspline_weights(tap_indices(x0, g.n0, i0), w0);
-  bspline_weights(tap_indices(x1, g.n1, i1), w1);
-  bspline_weights(tap_indices(x2, g.n2, i2), w2);
+  tap_nodes(b0, n0, i0);
+  tap_nodes(b1, n1, i1);
+  tap_nodes(b2, n2, i2);
+  brick_weights(t0, w0);
+  brick_weights(t1, w1);
+  brick_weights(t2, w2);
   float acc = 0.f;
 #pragma unroll
   for (int a = 0; a < 4; ++a) {
     float sa = 0.f;
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
-      const float* row = c + (static_cast<int64_t>(i0[a]) * g.n1 + i1[b]) * g.n2;
-      sa += w1[b] * (w2[0] * row[i2[0]] + w2[1] * row[i2[1]] + w2[2] * row[i2[2]] + w2[3] * row[i2[3]]);
+      const float* row = c + (static_cast<int64_t>(i0[a]) * n1 + i1[b]) * n2;
+      sa = fmaf(w1[b], row4(row[i2[0]], row[i2[1]], row[i2[2]], row[i2[3]], w2), sa);
     }
-    acc += w0[a] * sa;
+    acc = fmaf(w0[a], sa, acc);
   }
   return acc;
 }
 
-// Epilogues that also take the interpolant at the node itself (NODE = true, accum_node).
+// Epilogues that also take the interpolant at the node itself
 template <class E, class = void>
 struct HasNode : std::false_type {};
 template <class E>
 struct HasNode<E, std::void_t<decltype(E::NODE)>> : std::bool_constant<E::NODE> {};
 
 // Generic brick kernel.  Epi provides:
-//   NF, GROUPS, GSIZE and field(g, k): the NF coefficient fields (stacked with
-//       stride P in `coef`) are staged GSIZE at a time, GROUPS times;
-//   struct State                 per-node accumulator;
-//   pos(p, i0, i1, i2, x[3])     departure point of node p (grid units);
-//   init(p, State&)              loads the node's pointwise operands;
-//   accum(State&, f, value)      folds the interpolated value of field f in;
-//   emit(p, const State&)        writes the node's results.
-// The B-spline weights of a node are computed once per group and shared by the
-// group's fields.
+//   NF, FS       fields interpolated together and the stride between them (in fields) in `coef`;
+//   NC           components launched together (component c's fields start at field c of `coef`);
+//   NO           output fields (component c's results at field c of `out` when NC > 1);
+//   struct In    a quad's operands; load(In&, rsrc of field k -> quad) reads them;
+//   disp(In, k)  displacement of the four departure points along axis k (grid units);
+//   finish(In, v, node, o)  results o[NO] from the interpolated values v[NF] (and the interpolants at the
+//                nodes, node[NF], if NODE).
 template <class Epi, class TL>
-__global__ __launch_bounds__(TL::NTHR) void k_brick(Epi epi, const float* __restrict__ coef, Grid3 g) {
-  constexpr int TX0 = TL::TX0, TX1 = TL::TX1, TX2 = TL::TX2, NTHR = TL::NTHR, PPT = TL::PPT;
-  constexpr int B0 = TL::B0, B1 = TL::B1, B2 = TL::B2, LD2 = TL::LD2, VOL = TL::VOL, NPT = TL::NPT;
-  constexpr int GS = Epi::GSIZE;
-  __shared__ __align__(16) float br[GS * VOL];
-  __shared__ int rowoff[B0 * B1];  // wrapped (i0, i1) row offsets of the brick
-  __shared__ int colidx[B2];       // wrapped i2 of the brick columns
+__global__ __launch_bounds__(TL::NTHR, Epi::NF >= 3 ? 2 : 4) void k_brick(Epi epi, const float* __restrict__ coef,
+                                                                          Grid3 g) {
+  constexpr int TX0 = TL::TX0, TX1 = TL::TX1, TX2 = TL::TX2, NTHR = TL::NTHR, QPT = TL::QPT;
+  constexpr int B0 = TL::B0, B1 = TL::B1, LD = TL::LD, QB = TL::QB, NQ = TL::NQ, VOL = TL::VOL;
+  constexpr int NF = Epi::NF, NE = (NQ + NTHR - 1) / NTHR, Q2 = TX2 / 4;
+  constexpr bool NODE = HasNode<Epi>::value;
+  __shared__ __align__(16) float br[NF * VOL];
   // Workgroups are dealt to the 8 XCDs round-robin in launch order, so grid neighbours would sit in
   // different L2s and every halo would be fetched again from the fabric.  When the block count is a
   // multiple of 8 the launch index is remapped so that each XCD owns one contiguous run of tiles
-  // (whole rows and slabs of the volume), whose shared halos then hit in its own L2.
+  // (whole rows and slabs of the volume), whose shared halos then hit in its own L2.  The components of a
+  // tile follow each other: they read the same displacements.
   const int gx = gridDim.x, gy = gridDim.y, nb = gx * gy * gridDim.z;
   int bid = blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z);
   if ((nb & 7) == 0) bid = (bid & 7) * (nb >> 3) + (bid >> 3);
-  const int bx = bid % gx, byz = bid / gx, by = byz % gy, bz = byz / gy;
+  const int comp = bid % Epi::NC;
+  bid /= Epi::NC;
+  const int tx = gx / Epi::NC, bx = bid % tx, byz = bid / tx, by = byz % gy, bz = byz / gy;
   const int t0 = bz * TX0, t1 = by * TX1, t2 = bx * TX2;
-  const int o0 = t0 - HALO, o1 = t1 - HALO, o2 = t2 - HALO;
   const int tid = threadIdx.x;
-  for (int e = tid; e < B0 * B1; e += NTHR) {
-    const int b0 = e / B1, b1 = e - b0 * B1;
-    rowoff[e] = (wrapi(o0 + b0, g.n0) * g.n1 + wrapi(o1 + b1, g.n1)) * g.n2;
-  }
-  for (int e = tid; e < B2; e += NTHR) colidx[e] = wrapi(o2 + e, g.n2);
-  float x[PPT][3];
-  int pidx[PPT];  // node index (grids stay below 2^31 nodes)
-  bool live[PPT];
-  typename Epi::State st[PPT];
+  const int64_t P = g.P, plane = (int64_t)g.n1 * g.n2;
+  coef += comp * P;
+  // staging: every load of the thread is requested before its first LDS store
+  f32x4 v[NF][NE];
+  const bool rawbuf = P < (int64_t(1) << 29);  // 32-bit byte offsets within a field
+  Rsrc rs[NF];
 #pragma unroll
-  for (int j = 0; j < PPT; ++j) {
-    const int q = tid + NTHR * j;
-    const int l2 = q % TX2, l1 = (q / TX2) % TX1, l0 = q / (TX1 * TX2);
-    const int i0 = t0 + l0, i1 = t1 + l1, i2 = t2 + l2;
-    live[j] = (i0 < g.n0) && (i1 < g.n1) && (i2 < g.n2);
-    pidx[j] = (i0 * g.n1 + i1) * g.n2 + i2;
-    if (live[j]) {
-      epi.pos(pidx[j], i0, i1, i2, x[j]);
-      epi.init(pidx[j], st[j]);
-    } else {
-      x[j][0] = x[j][1] = x[j][2] = 0.f;
-    }
-  }
-  // every load of the thread is issued before its first LDS store (one memory latency per brick);
-  // with several field groups the next group's loads are issued before the current group's
-  // evaluation, so their latency hides behind it
-  constexpr int NIT = (NPT + NTHR - 1) / NTHR;
-  float v[NIT][GS];
-  __syncthreads();  // row offsets and columns tabulated
-  // fields below 2^29 nodes are read through raw buffer loads (one resource per field, 32-bit byte
-  // offsets: no 64-bit address arithmetic per staged point)
-  const bool rawbuf = g.P < (int64_t(1) << 29);
-  auto load_group = [&](int grp) {
-    if (rawbuf) {
-      __amdgpu_buffer_rsrc_t rs[GS];
+  for (int f = 0; f < NF; ++f) rs[f] = rsrc(coef + f * Epi::FS * P, P);
 #pragma unroll
-      for (int k = 0; k < GS; ++k)
-        rs[k] = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(coef + Epi::field(grp, k) * g.P), (short)0,
-                                                  (int)(g.P * 4), 0x00020000);
+  for (int k = 0; k < NE; ++k) {
+    const int e = tid + k * NTHR;
+    if (e < NQ) {
+      const int row = e / QB, q = e - row * QB, b0 = row / B1, b1 = row - b0 * B1;
+      const int r0 = wrap_near(t0 - HALO + b0, g.n0), r1 = wrap_near(t1 - HALO + b1, g.n1);
+      const int c = wrap_near(t2 - 4 + 4 * q, g.n2);
+      if (rawbuf) {
+        const unsigned off = ((unsigned)(r0 * g.n1 + r1) * (unsigned)g.n2 + (unsigned)c) * 4u;
 #pragma unroll
-      for (int it = 0; it < NIT; ++it) {
-        const int e = tid + it * NTHR;
-        if (e < NPT) {
-          const int row = e / B2, b2 = e - row * B2;
-          const unsigned off = (unsigned)(rowoff[row] + colidx[b2]) * 4u;
+        for (int f = 0; f < NF; ++f) v[f][k] = bload4(rs[f], off);
+        if (c + 3 >= g.n2) {  // the quad runs past the row's end (rows that are no multiple of four)
 #pragma unroll
-          for (int k = 0; k < GS; ++k)
-            v[it][k] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs[k], (int)off, 0, 0));
+          for (int j = 1; j < 4; ++j) {
+            const unsigned oj = off + 4u * (unsigned)(wrapi(c + j, g.n2) - c);
+#pragma unroll
+            for (int f = 0; f < NF; ++f) v[f][k][j] = bload(rs[f], oj);
+          }
         }
-      }
-      return;
-    }
+      } else {
+        const int64_t ro = ((int64_t)r0 * g.n1 + r1) * g.n2;
 #pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-      const int e = tid + it * NTHR;
-      if (e < NPT) {
-        const int row = e / B2, b2 = e - row * B2;
-        const int off = rowoff[row] + colidx[b2];
+        for (int f = 0; f < NF; ++f)
 #pragma unroll
-        for (int k = 0; k < GS; ++k) v[it][k] = coef[Epi::field(grp, k) * g.P + off];
+          for (int j = 0; j < 4; ++j) v[f][k][j] = coef[f * Epi::FS * P + ro + wrapi(c + j, g.n2)];
       }
     }
-  };
-  load_group(0);
-#pragma unroll 1
-  for (int grp = 0; grp < Epi::GROUPS; ++grp) {
-    __syncthreads();  // the previous group's evaluation is done with the brick
+  }
+  // pointwise operands of the thread's quads; offsets count from the tile's first plane
+  typename Epi::In in[QPT];
+  unsigned off[QPT];
+  const int64_t base = t0 * plane, left = P - base;
+#pragma unroll
+  for (int j = 0; j < QPT; ++j) {
+    const int q = tid + NTHR * j, l2 = (q % Q2) * 4, l1 = (q / Q2) % TX1, l0 = q / (Q2 * TX1);
+    const int i0 = t0 + l0, i1 = t1 + l1, i2 = t2 + l2;
+    const bool live = i0 < g.n0 && i1 < g.n1 && i2 < g.n2;
+    off[j] = live ? ((unsigned)(l0 * g.n1 + i1) * (unsigned)g.n2 + (unsigned)i2) * 4u : kOut;
+    epi.load(in[j], [&](const float* p) { return bload4(rsrc(p + base, left), off[j]); });
+  }
+#pragma unroll
+  for (int k = 0; k < NE; ++k) {
+    const int e = tid + k * NTHR;
+    if (e < NQ) {
+      const int row = e / QB, q = e - row * QB;
+#pragma unroll
+      for (int f = 0; f < NF; ++f) {  // a quad straddles the rows' two-float shift
+        float* w = br + f * VOL + row * LD + 4 * q - 2;
+        if (q > 0) *reinterpret_cast<f32x2*>(w) = f32x2{v[f][k].x, v[f][k].y};
+        if (q < QB - 1) *reinterpret_cast<f32x2*>(w + 2) = f32x2{v[f][k].z, v[f][k].w};
+      }
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < QPT; ++j) {
+    const int q = tid + NTHR * j, l2 = (q % Q2) * 4, l1 = (q / Q2) % TX1, l0 = q / (Q2 * TX1);
+    float w0[4][5], w1[4][5], w2[4][5];
+    unsigned far = 0;  // nodes displaced by a voxel or more
     {
+      const f32x4 d0 = epi.disp(in[j], 0), d1 = epi.disp(in[j], 1), d2 = epi.disp(in[j], 2);
 #pragma unroll
-      for (int it = 0; it < NIT; ++it) {
-        const int e = tid + it * NTHR;
-        if (e < NPT) {
-          const int row = e / B2, b2 = e - row * B2;
-          const int q = row * LD2 + b2;
-          if constexpr (GS == 2) {  // interleaved pair
-            reinterpret_cast<float2*>(br)[q] = make_float2(v[it][0], v[it][1]);
-          } else {
+      for (int n = 0; n < 4; ++n) {
+        if (!(fabsf(d0[n]) < 1.f && fabsf(d1[n]) < 1.f && fabsf(d2[n]) < 1.f)) far |= 1u << n;
+        window_weights(d0[n], w0[n]);
+        window_weights(d1[n], w1[n]);
+        window_weights(d2[n], w2[n]);
+      }
+    }
+    f32x4 acc[NF], node[NF];
 #pragma unroll
-            for (int k = 0; k < GS; ++k) br[k * VOL + q] = v[it][k];
+    for (int f = 0; f < NF; ++f) acc[f] = node[f] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const float* win = br + (l0 * B1 + l1) * LD + l2;
+#pragma unroll 1
+    for (int a = 0; a < 5; ++a) {
+      f32x4 s[NF], sn[NF];
+#pragma unroll
+      for (int f = 0; f < NF; ++f) s[f] = sn[f] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int b = 0; b < 5; ++b) {
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+          lds_f32x4* p = (lds_f32x4*)((lds_float*)win + f * VOL + (a * B1 + b) * LD);
+          const f32x4 lo = p[0], hi = p[1];
+          const float r[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+          float t[4];
+#pragma unroll
+          for (int n = 0; n < 4; ++n) t[n] = w2[n][0] * r[n];
+#pragma unroll
+          for (int c = 1; c < 5; ++c)
+#pragma unroll
+            for (int n = 0; n < 4; ++n) t[n] = fmaf(w2[n][c], r[n + c], t[n]);
+#pragma unroll
+          for (int n = 0; n < 4; ++n) s[f][n] = fmaf(w1[n][b], t[n], s[f][n]);
+          if constexpr (NODE) {  // taps (1/6, 2/3, 1/6) around the node
+            if (b >= 1 && b <= 3) {
+              const float wb = b == 2 ? 2.f / 3.f : 1.f / 6.f;
+#pragma unroll
+              for (int n = 0; n < 4; ++n)
+                sn[f][n] = fmaf(wb, fmaf(1.f / 6.f, r[n + 3], fmaf(2.f / 3.f, r[n + 2], (1.f / 6.f) * r[n + 1])), sn[f][n]);
+            }
           }
         }
       }
-    }
-    __syncthreads();
-    if (grp + 1 < Epi::GROUPS) load_group(grp + 1);
+      const float wa = a == 2 ? 2.f / 3.f : (a == 1 || a == 3) ? 1.f / 6.f : 0.f;
 #pragma unroll
-    for (int j = 0; j < PPT; ++j) {
-      if (!live[j]) continue;
-      if constexpr (HasNode<Epi>::value) {
-        // the interpolant at the node itself: taps node-1 .. node+2, always inside the brick
-        const int q = tid + NTHR * j;
-        const int l2 = q % TX2, l1 = (q / TX2) % TX1, l0 = q / (TX1 * TX2);
-        float wn[4];
-        bspline_weights(0.f, wn);
+      for (int n = 0; n < 4; ++n) {
+        const float w = w0[n][0];
 #pragma unroll
-        for (int k = 0; k < GS; ++k)
-          epi.accum_node(st[j], Epi::field(grp, k),
-                         eval_brick<B1, LD2>(br + k * VOL, l0 + HALO - 1, l1 + HALO - 1, l2 + HALO - 1, wn, wn, wn));
-      }
-      const float f0 = floorf(x[j][0]), f1 = floorf(x[j][1]), f2 = floorf(x[j][2]);
-      const int s0 = static_cast<int>(f0) - 1 - o0, s1 = static_cast<int>(f1) - 1 - o1,
-                s2 = static_cast<int>(f2) - 1 - o2;
-      const bool inb = s0 >= 0 && s0 + 3 < B0 && s1 >= 0 && s1 + 3 < B1 && s2 >= 0 && s2 + 3 < B2;
-      if (inb) {
-        float w0[4], w1[4], w2[4];
-        brick_weights(x[j][0] - f0, w0);
-        brick_weights(x[j][1] - f1, w1);
-        brick_weights(x[j][2] - f2, w2);
-        if constexpr (GS == 2) {
-          const float2 v = eval_brick2<B1, LD2>(reinterpret_cast<const float2*>(br), s0, s1, s2, w0, w1, w2);
-          epi.accum(st[j], Epi::field(grp, 0), v.x);
-          epi.accum(st[j], Epi::field(grp, 1), v.y);
-        } else if constexpr (GS >= 3) {
-          float o[GS];
-          eval_brick_n<GS, B1, LD2, VOL>(br, s0, s1, s2, w0, w1, w2, o);
-#pragma unroll
-          for (int k = 0; k < GS; ++k) epi.accum(st[j], Epi::field(grp, k), o[k]);
-        } else {
-#pragma unroll
-          for (int k = 0; k < GS; ++k)
-            epi.accum(st[j], Epi::field(grp, k), eval_brick<B1, LD2>(br + k * VOL, s0, s1, s2, w0, w1, w2));
+        for (int f = 0; f < NF; ++f) {
+          acc[f][n] = fmaf(w, s[f][n], acc[f][n]);
+          if constexpr (NODE) node[f][n] = fmaf(wa, sn[f][n], node[f][n]);
         }
+        w0[n][0] = w0[n][1], w0[n][1] = w0[n][2], w0[n][2] = w0[n][3], w0[n][3] = w0[n][4];
+      }
+    }
+    if (off[j] == kOut) continue;
+    if (far) {
+      const f32x4 d0 = epi.disp(in[j], 0), d1 = epi.disp(in[j], 1), d2 = epi.disp(in[j], 2);
+#pragma unroll 1
+      for (int n = 0; n < 4; ++n) {
+        if (!((far >> n) & 1)) continue;
+        auto pick = [&](const f32x4& d) { return n == 0 ? d.x : n == 1 ? d.y : n == 2 ? d.z : d.w; };
+        const float e0 = pick(d0), e1 = pick(d1), e2 = pick(d2);
+        const float f0 = floorf(e0), f1 = floorf(e1), f2 = floorf(e2);
+        // first tap in the brick
+        const int s0 = l0 + HALO - 1 + static_cast<int>(f0), s1 = l1 + HALO - 1 + static_cast<int>(f1),
+                  s2 = l2 + n + HALO - 1 + static_cast<int>(f2);
+        const bool inb = fabsf(e0) < 64.f && fabsf(e1) < 64.f && fabsf(e2) < 64.f && s0 >= 0 && s0 + 3 < B0 &&
+                         s1 >= 0 && s1 + 3 < B1 && s2 >= 0 && s2 + 3 < LD;
+        float u0[4], u1[4], u2[4];
+        brick_weights(e0 - f0, u0);
+        brick_weights(e1 - f1, u1);
+        brick_weights(e2 - f2, u2);
+#pragma unroll 1
+        for (int f = 0; f < NF; ++f) {
+          float val = 0.f;
+          if (inb) {
+            lds_float* p = (lds_float*)br + f * VOL + (s0 * B1 + s1) * LD + s2;
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+              float sa = 0.f;
+#pragma unroll
+              for (int b = 0; b < 4; ++b) {
+                lds_float* r = p + (a * B1 + b) * LD;
+                sa = fmaf(u1[b], row4(r[0], r[1], r[2], r[3], u2), sa);
+              }
+              val = fmaf(u0[a], sa, val);
+            }
+          } else {
+            // (displacements beyond every grid are as good as none: the index is periodic)
+            auto node = [](int i, float fl, int n) { return i + static_cast<int>(fabsf(fl) < 1e9f ? fl : 0.f) % n; };
+            val = eval_global(coef + f * Epi::FS * P, node(t0 + l0, f0, g.n0), node(t1 + l1, f1, g.n1),
+                              node(t2 + l2 + n, f2, g.n2), e0 - f0, e1 - f1, e2 - f2, g.n0, g.n1, g.n2);
+          }
+#pragma unroll
+          for (int m = 0; m < 4; ++m)
+#pragma unroll
+            for (int h = 0; h < NF; ++h) acc[h][m] = (m == n && h == f) ? val : acc[h][m];
+        }
+      }
+    }
+    f32x4 o[Epi::NO];
+    epi.finish(in[j], acc, node, o);
+    const int last = g.n2 - (t2 + l2);  // nodes left in the row
+#pragma unroll
+    for (int k = 0; k < Epi::NO; ++k) {
+      const Rsrc ro = rsrc(epi.out + (comp + k) * P + base, left);
+      typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+      if (last >= 4) {
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o[k]), ro, (int)off[j], 0, 0);
       } else {
 #pragma unroll
-        for (int k = 0; k < GS; ++k) {
-          const int f = Epi::field(grp, k);
-          epi.accum(st[j], f, eval_global(coef + f * g.P, x[j][0], x[j][1], x[j][2], g.n0, g.n1, g.n2));
+        for (int n = 0; n < 3; ++n) {
+          const float w = o[k][n];  // (a scalar of its own: a bit cast of a vector element takes element 0)
+          if (n < last)
+            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, w), ro, (int)(off[j] + 4u * n), 0, 0);
         }
       }
     }
   }
-#pragma unroll
-  for (int j = 0; j < PPT; ++j)
-    if (live[j]) epi.emit(pidx[j], st[j]);
 }
-
-// default field staging: all fields in one group
-template <int NFv>
-struct OneGroup {
-  static constexpr int NF = NFv, GROUPS = 1, GSIZE = NFv;
-  __device__ static int field(int, int k) { return k; }
-};
 
 // ---- epilogues ---------------------------------------------------------------------
 
+template <int NFv, int FSv = 1, int NCv = 1, int NOv = NFv>
+struct Shape {
+  static constexpr int NF = NFv, FS = FSv, NC = NCv, NO = NOv;
+};
+
 // nodes displaced by a stored departure displacement field (grid units)
-struct DispPos {
-  const float* __restrict__ disp;
+struct Displaced {
+  const float* __restrict__ dsp;
   int64_t P;
-  __device__ __forceinline__ void pos(int64_t p, int i0, int i1, int i2, float x[3]) const {
-    x[0] = i0 + disp[p];
-    x[1] = i1 + disp[P + p];
-    x[2] = i2 + disp[2 * P + p];
+  struct In {
+    f32x4 d[3];
+  };
+  template <class L>
+  __device__ __forceinline__ void load(In& in, L&& ld) const {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) in.d[k] = ld(dsp + k * P);
   }
+  __device__ __forceinline__ f32x4 disp(const In& in, int k) const { return in.d[k]; }
+};
+// the same with the velocity divergence at the node
+struct DisplacedDiv : Displaced {
+  const float* __restrict__ divv;
+  struct In : Displaced::In {
+    f32x4 v;
+  };
+  template <class L>
+  __device__ __forceinline__ void load(In& in, L&& ld) const {
+    Displaced::load(in, ld);
+    in.v = ld(divv);
+  }
+  __device__ __forceinline__ f32x4 disp(const In& in, int k) const { return in.d[k]; }
 };
 
 template <int NFv>
-struct EpiInterp : DispPos, OneGroup<NFv> {
-  static constexpr int NF = NFv;
-  struct State {
-    float o[NF];
-  };
+struct EpiInterp : Displaced, Shape<NFv> {
   float* __restrict__ out;
-  __device__ __forceinline__ void init(int64_t, State&) const {}
-  __device__ __forceinline__ void accum(State& s, int f, float v) const {
+  __device__ __forceinline__ void finish(const In&, const f32x4* v, const f32x4*, f32x4* o) const {
 #pragma unroll
-    for (int i = 0; i < NF; ++i) s.o[i] = (f == i) ? v : s.o[i];
-  }
-  __device__ __forceinline__ void emit(int64_t p, const State& s) const {
-#pragma unroll
-    for (int f = 0; f < NF; ++f) out[f * P + p] = s.o[f];
+    for (int f = 0; f < NFv; ++f) o[f] = v[f];
   }
 };
 
 // out_f = P(c_f) o X - P(c_f)(x): the interpolant's change along the characteristic (projected, it is
 // the step's increment of a band-limited field, whose own projection the caller adds back exactly)
 template <int NFv>
-struct EpiInterpDiff : DispPos, OneGroup<NFv> {
-  static constexpr int NF = NFv;
+struct EpiInterpDiff : Displaced, Shape<NFv> {
   static constexpr bool NODE = true;
-  static_assert(NFv != 2, "two fields are staged interleaved");
-  struct State {
-    float o[NF], n[NF];
-  };
   float* __restrict__ out;
-  __device__ __forceinline__ void init(int64_t, State&) const {}
-  __device__ __forceinline__ void accum(State& s, int f, float v) const {
+  __device__ __forceinline__ void finish(const In&, const f32x4* v, const f32x4* node, f32x4* o) const {
 #pragma unroll
-    for (int i = 0; i < NF; ++i) s.o[i] = (f == i) ? v : s.o[i];
-  }
-  __device__ __forceinline__ void accum_node(State& s, int f, float v) const {
-#pragma unroll
-    for (int i = 0; i < NF; ++i) s.n[i] = (f == i) ? v : s.n[i];
-  }
-  __device__ __forceinline__ void emit(int64_t p, const State& s) const {
-#pragma unroll
-    for (int f = 0; f < NF; ++f) out[f * P + p] = s.o[f] - s.n[f];
+    for (int f = 0; f < NFv; ++f) o[f] = v[f] - node[f];
   }
 };
 
-// band-limited adjoint Heun step: out_f = cA_f o X + dt/2 divv (cB_f o X)
-// FS: fields between cA_i and cB_i (NC, or 3 for one component of a three-component pair of stacks)
-template <int NC, int FS = NC>
-struct EpiBLAdjoint : DispPos {
-  // fields [cA_0..cA_{NC-1}, cB_0..cB_{NC-1}], staged as the pairs (cA_i, cB_i)
-  static constexpr int NF = 2 * NC, GROUPS = NC, GSIZE = 2;
-  __device__ static int field(int g, int k) { return g + k * FS; }
-  struct State {
-    float hd, o[NC];
-  };
+// band-limited adjoint Heun step of NCv components (one per workgroup): out_c = cA_c o X + dt/2 divv (cB_c o X),
+// fields [cA_0 .. cA_{NCv-1}, cB_0 .. cB_{NCv-1}]
+template <int NCv>
+struct EpiBLAdjoint : DisplacedDiv, Shape<2, NCv, NCv, 1> {
   float* __restrict__ out;
-  const float* __restrict__ divv;
   float dt;
-  __device__ __forceinline__ void init(int64_t p, State& s) const {
-    s.hd = 0.5f * dt * divv[p];
+  __device__ __forceinline__ void finish(const In& in, const f32x4* v, const f32x4*, f32x4* o) const {
 #pragma unroll
-    for (int i = 0; i < NC; ++i) s.o[i] = 0.f;
-  }
-  __device__ __forceinline__ void accum(State& s, int f, float v) const {
-    const float w = f < NC ? v : s.hd * v;
-    const int i0 = f < NC ? f : f - FS;
-#pragma unroll
-    for (int i = 0; i < NC; ++i) s.o[i] += (i0 == i) ? w : 0.f;
-  }
-  __device__ __forceinline__ void emit(int64_t p, const State& s) const {
-#pragma unroll
-    for (int f = 0; f < NC; ++f) out[f * P + p] = s.o[f];
+    for (int n = 0; n < 4; ++n) o[0][n] = v[0][n] + 0.5f * dt * in.v[n] * v[1][n];
   }
 };
 
 // image-transport adjoint on the grid: a = c1 o X, b = c2 o X,
 // out = a + dt/2 (b + (a + dt b) divv) = (1 + dt/2 divv) a + dt/2 (1 + dt divv) b
-struct EpiAdjointGrid : DispPos, OneGroup<2> {
-  static constexpr int NF = 2;
-  struct State {
-    float ca, cb, o;
-  };
+struct EpiAdjointGrid : DisplacedDiv, Shape<2, 1, 1, 1> {
   float* __restrict__ out;
-  const float* __restrict__ divv;
   float dt;
-  __device__ __forceinline__ void init(int64_t p, State& s) const {
-    const float dv = divv[p];
-    s.ca = 1.f + 0.5f * dt * dv;
-    s.cb = 0.5f * dt * (1.f + dt * dv);
-    s.o = 0.f;
+  __device__ __forceinline__ void finish(const In& in, const f32x4* v, const f32x4*, f32x4* o) const {
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+      const float dv = in.v[n];
+      o[0][n] = (1.f + 0.5f * dt * dv) * v[0][n] + 0.5f * dt * (1.f + dt * dv) * v[1][n];
+    }
   }
-  __device__ __forceinline__ void accum(State& s, int f, float v) const { s.o += (f == 0 ? s.ca : s.cb) * v; }
-  __device__ __forceinline__ void emit(int64_t p, const State& s) const { out[p] = s.o; }
 };
 
 // characteristics: X* = x + sdt v, X - x = sdt/2 (v + v o X*) (grid units)
-struct EpiCharacteristics : OneGroup<3> {
-  static constexpr int NF = 3;
-  struct State {
-    float o[3];
-  };
+struct EpiCharacteristics : Shape<3> {
   const float* __restrict__ v;
-  float* __restrict__ disp;
+  float* __restrict__ out;
   int64_t P;
   float sdt, s0, s1, s2;  // signed dt and per-axis grid sizes
-  __device__ __forceinline__ void pos(int64_t p, int i0, int i1, int i2, float x[3]) const {
-    x[0] = i0 + sdt * v[p] * s0;
-    x[1] = i1 + sdt * v[P + p] * s1;
-    x[2] = i2 + sdt * v[2 * P + p] * s2;
-  }
-  __device__ __forceinline__ void init(int64_t, State&) const {}
-  __device__ __forceinline__ void accum(State& s, int f, float val) const {
+  struct In {
+    f32x4 v[3];
+  };
+  template <class L>
+  __device__ __forceinline__ void load(In& in, L&& ld) const {
 #pragma unroll
-    for (int i = 0; i < 3; ++i) s.o[i] = (f == i) ? val : s.o[i];
+    for (int k = 0; k < 3; ++k) in.v[k] = ld(v + k * P);
   }
-  __device__ __forceinline__ void emit(int64_t p, const State& s) const {
+  __device__ __forceinline__ float scale(int k) const { return k == 0 ? s0 : k == 1 ? s1 : s2; }
+  __device__ __forceinline__ f32x4 disp(const In& in, int k) const {
+    f32x4 d;
+#pragma unroll
+    for (int n = 0; n < 4; ++n) d[n] = sdt * in.v[k][n] * scale(k);
+    return d;
+  }
+  __device__ __forceinline__ void finish(const In& in, const f32x4* c, const f32x4*, f32x4* o) const {
     const float h = 0.5f * sdt;
-    disp[p] = h * (v[p] * s0 + s.o[0] * s0);
-    disp[P + p] = h * (v[P + p] * s1 + s.o[1] * s1);
-    disp[2 * P + p] = h * (v[2 * P + p] * s2 + s.o[2] * s2);
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+#pragma unroll
+      for (int n = 0; n < 4; ++n) o[k][n] = h * (in.v[k][n] * scale(k) + c[k][n] * scale(k));
   }
 };
 
 template <class Epi, class TL>
 void launch_tile(const std::string& name, double bytes, const Epi& epi, const float* coef, const Grid3& g,
                  hipStream_t s) {
-  dim3 grid(ceil_div(g.n2, TL::TX2), ceil_div(g.n1, TL::TX1), ceil_div(g.n0, TL::TX0));
+  dim3 grid(ceil_div(g.n2, TL::TX2) * Epi::NC, ceil_div(g.n1, TL::TX1), ceil_div(g.n0, TL::TX0));
   prof::launch(name, bytes, 0.0, k_brick<Epi, TL>, grid, dim3(TL::NTHR), 0, s, epi, coef, g);
 }
 
@@ -546,9 +508,7 @@ template <class Epi>
 void launch(const std::string& name, double bytes, const Epi& epi, const float* coef, const Dims& d,
             hipStream_t s, int tile = -1) {
   const Grid3 g{d.n[0], d.n[1], d.n[2], d.P};
-  if (tile < 0) tile = std::max(0, tune::get(shape_key(d) + ":gs" + std::to_string(Epi::GSIZE), 0));
-  // epilogues with more than three fields would spill at 1024 threads: they keep the 512-thread tile
-  if ((tile == 4 || tile == 5) && Epi::NF > 3) tile = 1;
+  if (tile < 0) tile = std::max(0, tune::get(shape_key(d) + ":gs" + std::to_string(Epi::NF), 0));
   switch (tile) {
     case 1:
       launch_tile<Epi, TileB>(name, bytes, epi, coef, g, s);
@@ -559,11 +519,11 @@ void launch(const std::string& name, double bytes, const Epi& epi, const float* 
     case 3:
       launch_tile<Epi, TileD>(name, bytes, epi, coef, g, s);
       break;
-    case 4:  // (not instantiated for the epilogues that keep the 512-thread tile)
-      if constexpr (Epi::NF <= 3) launch_tile<Epi, TileE>(name, bytes, epi, coef, g, s);
+    case 4:
+      launch_tile<Epi, TileE>(name, bytes, epi, coef, g, s);
       break;
     case 5:
-      if constexpr (Epi::NF <= 3) launch_tile<Epi, TileF>(name, bytes, epi, coef, g, s);
+      launch_tile<Epi, TileF>(name, bytes, epi, coef, g, s);
       break;
     case 6:
       launch_tile<Epi, TileG>(name, bytes, epi, coef, g, s);
@@ -730,7 +690,9 @@ __global__ __launch_bounds__(NTHR) void k_pull_back_box(float* __restrict__ out,
       val = eval_box(br, static_cast<int>(f0) - 1 - lo0, static_cast<int>(f1) - 1 - lo1,
                      static_cast<int>(f2) - 1 - lo2, e1, e2, w0, w1, w2);
     } else {
-      val = eval_global(c, x[j][0], x[j][1], x[j][2], g.n0, g.n1, g.n2);
+      const float f0 = floorf(x[j][0]), f1 = floorf(x[j][1]), f2 = floorf(x[j][2]);
+      val = eval_global(c, static_cast<int>(f0), static_cast<int>(f1), static_cast<int>(f2), x[j][0] - f0, x[j][1] - f1,
+                        x[j][2] - f2, g.n0, g.n1, g.n2);
     }
     const int64_t o = node * P + pidx[j];
     out[o] = a * (w ? w[o] * val : val);
@@ -758,76 +720,65 @@ void brick_pull_back(float* out, const float* c, const float* u, const float* w,
 
 int brick_tile_count() { return kTiles; }
 
-// One tile per grid shape and staging width (fields staged together: 1, 2 interleaved, or 3), timed
-// on the interpolation epilogue of that width; out holds 3 fields, coef 3 fields.
+// One tile per grid shape and staging width (fields staged together: 1, 2 or 3), timed on the epilogues of
+// that width that the sweeps launch most (the pair: one component's adjoint step); out holds 3 fields, coef 3
+// fields.
 void brick_autotune(float* out, const float* coef, float* disp, const Dims& d, hipStream_t s) {
   const std::string key = shape_key(d) + ":gs";
   if (tune::get(key + "1", -1) >= 0 && tune::get(key + "2", -1) >= 0 && tune::get(key + "3", -1) >= 0) return;
   k_tune_disp<<<ceil_div(d.P, 256), 256, 0, s>>>(disp, d.n[0], d.n[1], d.n[2]);
   LDDMM_LAUNCH_CHECK();
   EpiInterp<1> e1;
-  e1.disp = disp, e1.P = d.P, e1.out = out;
-  EpiInterp<2> e2;
-  e2.disp = disp, e2.P = d.P, e2.out = out;
+  e1.dsp = disp, e1.P = d.P, e1.out = out;
+  EpiBLAdjoint<1> e2;
+  e2.dsp = disp, e2.P = d.P, e2.out = out, e2.divv = coef + 2 * d.P, e2.dt = 0.1f;
   EpiInterp<3> e3;
-  e3.disp = disp, e3.P = d.P, e3.out = out;
+  e3.dsp = disp, e3.P = d.P, e3.out = out;
   tune::set(key + "1", tune::pick(kTiles, [&](int c) { launch("tune", 0.0, e1, coef, d, s, c); }, s));
   tune::set(key + "2", tune::pick(kTiles, [&](int c) { launch("tune", 0.0, e2, coef, d, s, c); }, s));
   tune::set(key + "3", tune::pick(kTiles, [&](int c) { launch("tune", 0.0, e3, coef, d, s, c); }, s));
 }
 
-void brick_interp(float* out, const float* coef, int nf, const float* disp, const Dims& d, hipStream_t s) {
-  const std::string name_ = nm("k_interp") + std::to_string(nf);
+template <template <int> class Epi>
+static void interp_any(const char* base, float* out, const float* coef, int nf, const float* disp, const Dims& d,
+                       hipStream_t s) {
+  const std::string name_ = nm(base) + std::to_string(nf);
   const double bytes_ = (3.0 + 2.0 * nf) * d.P * 4;
   if (nf == 1) {
-    EpiInterp<1> e;
-    e.disp = disp, e.P = d.P, e.out = out;
+    Epi<1> e;
+    e.dsp = disp, e.P = d.P, e.out = out;
     launch(name_, bytes_, e, coef, d, s);
   } else if (nf == 3) {
-    EpiInterp<3> e;
-    e.disp = disp, e.P = d.P, e.out = out;
+    Epi<3> e;
+    e.dsp = disp, e.P = d.P, e.out = out;
     launch(name_, bytes_, e, coef, d, s);
   } else {
-    throw ArgError("brick_interp: nf must be 1 or 3");
+    throw ArgError(std::string(base) + ": nf must be 1 or 3");
   }
 }
 
+void brick_interp(float* out, const float* coef, int nf, const float* disp, const Dims& d, hipStream_t s) {
+  interp_any<EpiInterp>("k_interp", out, coef, nf, disp, d, s);
+}
+
 void brick_interp_diff(float* out, const float* coef, int nf, const float* disp, const Dims& d, hipStream_t s) {
-  const std::string name_ = nm("k_interp_diff") + std::to_string(nf);
-  const double bytes_ = (3.0 + 2.0 * nf) * d.P * 4;
-  if (nf == 1) {
-    EpiInterpDiff<1> e;
-    e.disp = disp, e.P = d.P, e.out = out;
-    launch(name_, bytes_, e, coef, d, s);
-  } else if (nf == 3) {
-    EpiInterpDiff<3> e;
-    e.disp = disp, e.P = d.P, e.out = out;
-    launch(name_, bytes_, e, coef, d, s);
-  } else {
-    throw ArgError("brick_interp_diff: nf must be 1 or 3");
-  }
+  interp_any<EpiInterpDiff>("k_interp_diff", out, coef, nf, disp, d, s);
 }
 
 void brick_bl_adjoint_step(float* out, const float* cAB, int nc, const float* disp, const float* divv,
                            const Dims& d, float dt, hipStream_t s) {
   const std::string name_ = nm("k_bl_adjoint_step") + std::to_string(nc);
   const double bytes_ = (4.0 + 3.0 * nc) * d.P * 4;
-  if (nc == 1) {
-    EpiBLAdjoint<1> e;
-    e.disp = disp, e.P = d.P, e.out = out, e.divv = divv, e.dt = dt;
+  auto go = [&](auto e) {
+    e.dsp = disp, e.P = d.P, e.out = out, e.divv = divv, e.dt = dt;
     launch(name_, bytes_, e, cAB, d, s);
-  } else if (nc == 3) {
-    // one launch per component on its pair (cA_i, cB_i): a single staged pair per workgroup keeps the
-    // registers (and the occupancy) of the one-component kernel
-    const double bytes_i = 7.0 * d.P * 4;
-    for (int i = 0; i < 3; ++i) {
-      EpiBLAdjoint<1, 3> e;
-      e.disp = disp, e.P = d.P, e.out = out + i * d.P, e.divv = divv, e.dt = dt;
-      launch(name_, bytes_i, e, cAB + i * d.P, d, s);
-    }
-  } else {
-    throw ArgError("brick_bl_adjoint_step: nc must be 1 or 3");
-  }
+  };
+  // three components: one workgroup per component and tile on its pair (cA_c, cB_c), which keeps the registers
+  // (and the occupancy) of the one-component kernel; in one launch, so that the components of a tile share
+  // its displacements in the caches
+  if (nc == 1) go(EpiBLAdjoint<1>{});
+  else if (nc == 3) go(EpiBLAdjoint<3>{});
+  else throw ArgError("brick_bl_adjoint_step: nc must be 1 or 3");
 }
 
 void brick_adjoint_grid_step(float* out, const float* c12, const float* disp, const float* divv, const Dims& d,
@@ -835,7 +786,7 @@ void brick_adjoint_grid_step(float* out, const float* c12, const float* disp, co
   const std::string name_ = nm("k_adjoint_grid_step");
   const double bytes_ = 7.0 * d.P * 4;
   EpiAdjointGrid e;
-  e.disp = disp, e.P = d.P, e.out = out, e.divv = divv, e.dt = dt;
+  e.dsp = disp, e.P = d.P, e.out = out, e.divv = divv, e.dt = dt;
   launch(name_, bytes_, e, c12, d, s);
 }
 
@@ -844,7 +795,7 @@ void brick_characteristics(float* disp, const float* v, const float* cv, const D
   const std::string name_ = nm("k_characteristics");
   const double bytes_ = 9.0 * d.P * 4;
   EpiCharacteristics e;
-  e.v = v, e.disp = disp, e.P = d.P;
+  e.v = v, e.out = disp, e.P = d.P;
   e.sdt = dir > 0 ? dt : -dt;
   e.s0 = float(d.n[0]), e.s1 = float(d.n[1]), e.s2 = float(d.n[2]);
   launch(name_, bytes_, e, cv, d, s);
