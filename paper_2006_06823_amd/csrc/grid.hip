@@ -446,192 +446,113 @@ __global__ void k_jacobian(double* out, const T* Du, int64_t P) {
 // first-order recursion with pole z = sqrt(3) - 2 and gain 6; the periodic start
 // values are the geometrically weighted wrap-around sums (truncated where z^h is
 // below the working precision).
+//
+// One pass per axis, out of place.  A thread filters a chunk of 16 points of a line: it requests the chunk
+// and the points around it that the two recursions still feel (W before, W after) at once, runs the causal
+// recursion from zero through the points before, and the anti-causal one from zero through those after, in
+// registers and in double.  Chunks are independent, so nothing is staged, no thread waits for another, and a
+// pass is a few microseconds of load latency: 128^3, one field 15.8 -> 7.5 us per axis (16.8 MB at 2.2 TB/s; the
+// neighbours' points come from the caches), two fields 11.2, against a staged tile of lines whose serial start
+// sums and recursions each waited for LDS.  FP64 64^2: 7.7 -> 7.4 us.
 template <typename T>
 struct Pole {
   static constexpr double z = -0.26794919243112270647255365849413;  // sqrt(3) - 2
-  static constexpr int horizon = sizeof(T) == 4 ? 16 : 32;
+  static constexpr int W = sizeof(T) == 4 ? 16 : 32;                // |z|^W below the working precision
+};
+constexpr int kChunk = 16;
+constexpr int kMaxPrefilter = 2;  // fields of one call
+
+template <typename T>
+struct PrefilterArgs {
+  const T* src[kMaxPrefilter];
+  const T* w[kMaxPrefilter];  // optional pointwise factor of the samples
+  T* dst;
+  int n;           // points of a line
+  int64_t stride;  // between points of a line
+  int64_t inner, outer_stride;  // lines: inner consecutive ones at stride 1, repeated at outer_stride (ROWS: inner rows)
+  int outer;
+  int64_t P;
 };
 
-template <typename T>
-__device__ void filter_line(T* f, int64_t stride, int n) {
+// ROWS: lines along the contiguous axis, lanes on consecutive chunks (VEC: rows of a multiple of four points,
+// read as 16-byte quads).  Otherwise lanes on consecutive lines, the points' addresses uniform.  The index
+// advances by compare and select (a wrapped index per point, inlined, made the code 23 KB and the pass
+// bound by fetching it).
+template <typename T, bool ROWS, bool VEC>
+__global__ __launch_bounds__(256) void k_prefilter(PrefilterArgs<T> a) {
+  constexpr int C = kChunk, W = Pole<T>::W, N = C + 2 * W, STEP = VEC ? 4 : 1;
+  typedef T T4 __attribute__((ext_vector_type(4)));
+  const int n = a.n;
+  int field, c0;
+  int64_t line;    // first point of the line (ROWS), or of the lines' row of points
+  unsigned q = 0;  // the lane's line among consecutive ones
+  if constexpr (ROWS) {
+    const int nch = (n + C - 1) / C;
+    const int64_t t = blockIdx.x * (int64_t)256 + threadIdx.x;
+    if (t >= a.inner * nch) return;
+    field = blockIdx.y;
+    line = (t / nch) * n;
+    c0 = (int)(t % nch) * C;
+  } else {
+    q = blockIdx.x * 64u + (threadIdx.x & 63);
+    c0 = __builtin_amdgcn_readfirstlane(blockIdx.y * 4 + (threadIdx.x >> 6)) * C;
+    if (q >= a.inner || c0 >= n) return;
+    field = blockIdx.z / a.outer;
+    line = (blockIdx.z - field * a.outer) * a.outer_stride;
+  }
+  int first = c0 - W;  // periodic index of the first point felt
+  first = (first % n + n) % n;
+  T v[N];
+  auto fetch = [&](const T* __restrict__ f, auto&& use) {
+    int i = first;
+#pragma unroll
+    for (int k = 0; k < N; k += STEP) {
+      if constexpr (VEC) {
+        const T4 x = *reinterpret_cast<const T4*>(f + line + i);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) use(v[k + j], x[j]);
+      } else if constexpr (ROWS) {
+        use(v[k], f[line + i]);
+      } else {
+        const T* p = f + line + i * a.stride;
+        use(v[k], p[q]);
+      }
+      i = i + STEP >= n ? 0 : i + STEP;
+    }
+  };
+  fetch(a.src[field], [](T& d, T x) { d = x; });
+  if (a.w[field]) fetch(a.w[field], [](T& d, T x) { d *= x; });
+  // causal: y[i] = f[i] + z y[i-1]; anti-causal: u[i] = y[i] + z u[i+1]; c = -6 z u
   const double z = Pole<T>::z;
-  const int h = n < Pole<T>::horizon ? n : Pole<T>::horizon;
-  double zn = 1.0;
-  for (int i = 0; i < n; ++i) zn *= z;
-  const double inv = 1.0 / (1.0 - zn);
-  // causal start: sum_i z^i x[-i], x = 6 f
-  double acc = 0.0, zi = 1.0;
-  for (int i = 0; i < h; ++i) {
-    const int j = (n - i) % n;
-    acc += zi * 6.0 * static_cast<double>(f[j * stride]);
-    zi *= z;
-  }
-  double prev = acc * inv;
-  f[0] = static_cast<T>(prev);
-  for (int k = 1; k < n; ++k) {
-    prev = 6.0 * static_cast<double>(f[k * stride]) + z * prev;
-    f[k * stride] = static_cast<T>(prev);
-  }
-  // anti-causal start: -z/(1-z^n) sum_i z^i y+[n-1+i]
-  acc = 0.0;
-  zi = 1.0;
-  for (int i = 0; i < h; ++i) {
-    const int j = (n - 1 + i) % n;
-    acc += zi * static_cast<double>(f[j * stride]);
-    zi *= z;
-  }
-  prev = -z * inv * acc;
-  f[(n - 1) * stride] = static_cast<T>(prev);
-  for (int k = n - 2; k >= 0; --k) {
-    prev = z * (prev - static_cast<double>(f[k * stride]));
-    f[k * stride] = static_cast<T>(prev);
-  }
-}
-
-// lines along axis 0 or 1: one thread per line, lanes on consecutive n2 indices (coalesced)
-template <typename T>
-__global__ void k_prefilter_outer(T* f, int n0, int n1, int n2, int axis, int64_t lines_per_field,
-                                  int64_t P, int nf) {
-  const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (t >= lines_per_field * nf) return;
-  const int fld = static_cast<int>(t / lines_per_field);
-  const int64_t l = t - fld * lines_per_field;
-  T* base = f + fld * P;
-  if (axis == 0) {  // lines indexed by (i1, i2)
-    filter_line(base + l, (int64_t)n1 * n2, n0);
-  } else {  // lines indexed by (i0, i2)
-    const int64_t i0 = l / n2, i2 = l % n2;
-    filter_line(base + i0 * n1 * n2 + i2, (int64_t)n2, n1);
-  }
-}
-
-// lines along the contiguous axis: stage up to 64 rows through LDS so global accesses stay coalesced
-template <typename T>
-__global__ void k_prefilter_inner(T* f, int n2, int64_t rows, int rpb) {
-  extern __shared__ unsigned char smem_raw[];
-  T* sm = reinterpret_cast<T*>(smem_raw);
-  const int ld = n2 + 1;
-  const int64_t r0 = (int64_t)blockIdx.x * rpb;
-  const int nr = static_cast<int>(rows - r0 < rpb ? rows - r0 : rpb);
-  for (int e = threadIdx.x; e < nr * n2; e += blockDim.x) {
-    const int r = e / n2, c = e - r * n2;
-    sm[r * ld + c] = f[(r0 + r) * n2 + c];
-  }
-  __syncthreads();
-  if (threadIdx.x < nr) filter_line(sm + threadIdx.x * ld, 1, n2);
-  __syncthreads();
-  for (int e = threadIdx.x; e < nr * n2; e += blockDim.x) {
-    const int r = e / n2, c = e - r * n2;
-    f[(r0 + r) * n2 + c] = sm[r * ld + c];
-  }
-}
-
-// chunk-parallel form for lines of at most kChunkMaxN points: a block stages 32 lines in LDS,
-// 8 threads per line each own one chunk; a chunk starts its causal (anti-causal) recursion from
-// the truncated geometric sum over the horizon points before (after) it, the same truncation
-// as the serial start values, so every chunk runs independently.
-constexpr int kChunkLines = 32, kChunkGroups = 8, kChunkMaxC = 24, kChunkMaxN = kChunkGroups * kChunkMaxC;
-
-template <typename T>
-__global__ __launch_bounds__(256) void k_prefilter_chunked(T* f, int n, int64_t gl, int64_t gi, int nlines_max,
-                                                           int64_t tile_stride_a, int tiles_a, int64_t tile_stride_b,
-                                                           int64_t P, double inv) {
-  extern __shared__ unsigned char smem_raw[];
-  T* sm = reinterpret_cast<T*>(smem_raw);  // [n][33]: element (line l, point i) at i * 33 + l
-  constexpr int ld = kChunkLines + 1;
-  // block -> (field, outer index b, tile of 32 lines a)
-  const int ta = blockIdx.x % tiles_a;
-  const int64_t tb = blockIdx.x / tiles_a;
-  T* base = f + blockIdx.y * P + tb * tile_stride_b + (int64_t)ta * kChunkLines * tile_stride_a;
-  const int nl = min(kChunkLines, nlines_max - ta * kChunkLines);
-  const int tid = threadIdx.x;
-  const bool line_major = gi == 1;  // points of a line contiguous in memory
-  // the tile is walked line by line (points contiguous) or point by point (lines contiguous), its
-  // loads batched ahead of the LDS stores and its indices advanced without integer division; the
-  // element offsets stay below 2^31 (a tile spans at most 32 lines of 192 points of one field)
-  const int rows = line_major ? kChunkLines : n, cols = line_major ? n : kChunkLines;
-  const int gstride = static_cast<int>(line_major ? gl : gi);
-  {
-    constexpr int U = 8;
-    TileWalk w(256, tid, cols, gstride, 0);
-    while (w.r < rows) {
-      const TileWalk w0 = w;
-      T v[U];
+  double y[C + W], prev = 0.0;
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int l = line_major ? w.r : w.c;
-        const bool ok = w.r < rows && l < nl;
-        const T t = base[ok ? w.o1 : 0];
-        v[u] = ok ? t : T(0);
-        w.next();
+  for (int k = 0; k < W; ++k) prev = fma(z, prev, static_cast<double>(v[k]));
+#pragma unroll
+  for (int k = 0; k < C + W; ++k) y[k] = prev = fma(z, prev, static_cast<double>(v[W + k]));
+  prev = 0.0;
+#pragma unroll
+  for (int k = C + W - 1; k >= C; --k) prev = fma(z, prev, y[k]);
+#pragma unroll
+  for (int k = C - 1; k >= 0; --k) {
+    prev = fma(z, prev, y[k]);
+    y[k] = -6.0 * z * prev;
+  }
+  T* __restrict__ dst = a.dst + field * a.P + line;
+  if constexpr (VEC) {
+#pragma unroll
+    for (int k = 0; k < C; k += 4) {
+      T4 x;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) x[j] = static_cast<T>(y[k + j]);
+      if (c0 + k < n) *reinterpret_cast<T4*>(dst + c0 + k) = x;
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < C; ++k)
+      if (c0 + k < n) {
+        T* p = dst + (ROWS ? (int64_t)(c0 + k) : (c0 + k) * a.stride);
+        p[q] = static_cast<T>(y[k]);
       }
-      w = w0;
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int l = line_major ? w.r : w.c, i = line_major ? w.c : w.r;
-        if (w.r < rows) sm[i * ld + l] = v[u];
-        w.next();
-      }
-    }
-  }
-  __syncthreads();
-  const double z = Pole<T>::z;  // inv = 1 / (1 - z^n), from the host
-  const int h = n < Pole<T>::horizon ? n : Pole<T>::horizon;
-  const int l = tid % kChunkLines, g = tid / kChunkLines;
-  const int Lc = (n + kChunkGroups - 1) / kChunkGroups;
-  const int c0 = g * Lc, c1 = min(n, c0 + Lc);
-  double cp[kChunkMaxC];
-  // causal: c+[i] = 6 f[i] + z c+[i-1]
-  {
-    double acc = 0.0, zi = 1.0;
-    for (int k = 0; k < h; ++k) {
-      int j = c0 - k;  // periodic: k < h <= n, one wrap at most
-      if (j < 0) j += n;
-      acc += zi * 6.0 * static_cast<double>(sm[j * ld + l]);
-      zi *= z;
-    }
-    double prev = acc * inv;
-#pragma unroll
-    for (int q = 0; q < kChunkMaxC; ++q) {
-      const int i = c0 + q;
-      if (i < c1) {
-        if (q > 0) prev = 6.0 * static_cast<double>(sm[i * ld + l]) + z * prev;
-        cp[q] = prev;
-      }
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int q = 0; q < kChunkMaxC; ++q)
-    if (c0 + q < c1) sm[(c0 + q) * ld + l] = static_cast<T>(cp[q]);
-  __syncthreads();
-  // anti-causal: c[i] = z (c[i+1] - c+[i]), started at the chunk's last point
-  {
-    const int e = c1 - 1;
-    double acc = 0.0, zi = 1.0;
-    for (int k = 0; k < h; ++k) {
-      const int j = e + k < n ? e + k : e + k - n;
-      acc += zi * static_cast<double>(sm[j * ld + l]);
-      zi *= z;
-    }
-    double prev = -z * inv * acc;
-#pragma unroll
-    for (int q = kChunkMaxC - 1; q >= 0; --q) {
-      const int i = c0 + q;
-      if (i < c1) {
-        if (i < e) prev = z * (prev - static_cast<double>(sm[i * ld + l]));
-        cp[q] = prev;
-      }
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int q = 0; q < kChunkMaxC; ++q)
-    if (c0 + q < c1) sm[(c0 + q) * ld + l] = static_cast<T>(cp[q]);
-  __syncthreads();
-  for (TileWalk w(256, tid, cols, gstride, 0); w.r < rows; w.next()) {
-    const int ll = line_major ? w.r : w.c, i = line_major ? w.c : w.r;
-    if (ll < nl) base[w.o1] = sm[i * ld + ll];
   }
 }
 
@@ -690,57 +611,44 @@ void interp(T* out, const T* coef, int nf, const T* disp, const Dims& d, hipStre
 }
 
 template <typename T>
-void prefilter(T* f, int nf, const Dims& d, hipStream_t s) {
+void prefilter(T* dst, T* tmp, const T* const* src, const T* const* w, int nf, const Dims& d, hipStream_t s) {
+  if (nf < 1 || nf > kMaxPrefilter) throw ArgError("prefilter: 1 or 2 fields");
   const int n0 = d.n[0], n1 = d.n[1], n2 = d.n[2];
-  const std::string nm = std::string("k_prefilter_chunked<") + prof::tname<T>() + ">";
-  // lines of `n` points at element stride gi; 32 consecutive lines (stride gl) per tile, tiles
-  // along the line index a, outer index b
-  auto chunked = [&](int n, int64_t gl, int64_t gi, int nlines_a, int64_t stride_b, int nb) {
-    const int tiles_a = ceil_div(nlines_a, kChunkLines);
-    const uint32_t sm = (uint32_t)((size_t)n * (kChunkLines + 1) * sizeof(T));
-    double zn = 1.0;
-    for (int i = 0; i < n; ++i) zn *= Pole<T>::z;
-    prof::launch(nm, 2.0 * nf * d.P * sizeof(T), 0.0, k_prefilter_chunked<T>, dim3(tiles_a * nb, nf), dim3(256),
-                 sm, s, f, n, gl, gi, nlines_a, gl, tiles_a, stride_b, d.P, 1.0 / (1.0 - zn));
+  int left = (n0 > 1) + (n1 > 1) + (n2 > 1);
+  const std::string nm = std::string("k_prefilter<") + prof::tname<T>() + ">";
+  PrefilterArgs<T> a{};
+  for (int f = 0; f < nf; ++f) a.src[f] = src[f], a.w[f] = w ? w[f] : nullptr;
+  a.P = d.P;
+  // passes alternate between dst and tmp so that the last one writes dst
+  auto pass = [&](int axis) {
+    --left;
+    a.dst = (left & 1) ? tmp : dst;
+    a.n = d.n[axis];
+    const double bytes = 2.0 * nf * d.P * sizeof(T);
+    const int nch = ceil_div(a.n, kChunk);
+    if (axis == 2) {
+      a.stride = 1, a.inner = (int64_t)n0 * n1, a.outer = 1, a.outer_stride = 0;
+      const dim3 g(ceil_div(a.inner * nch, 256), nf);
+      if (n2 % 4 == 0) prof::launch(nm, bytes, 0.0, k_prefilter<T, true, true>, g, dim3(256), 0, s, a);
+      else prof::launch(nm, bytes, 0.0, k_prefilter<T, true, false>, g, dim3(256), 0, s, a);
+    } else {
+      a.stride = axis == 1 ? n2 : (int64_t)n1 * n2;
+      a.inner = a.stride;
+      a.outer = axis == 1 ? n0 : 1;
+      a.outer_stride = (int64_t)n1 * n2;
+      const dim3 g(ceil_div(a.inner, 64), ceil_div(nch, 4), a.outer * nf);
+      prof::launch(nm, bytes, 0.0, k_prefilter<T, false, false>, g, dim3(256), 0, s, a);
+    }
     LDDMM_LAUNCH_CHECK();
+    for (int f = 0; f < nf; ++f) a.src[f] = a.dst + f * d.P, a.w[f] = nullptr;
   };
-  if (n2 > 1) {
-    if (n2 <= kChunkMaxN) {
-      // lines along axis 2: tiles of 32 consecutive rows x1 at fixed x0
-      chunked(n2, (int64_t)n2, 1, n1, (int64_t)n1 * n2, n0);
-    } else {
-      const int64_t rows = (int64_t)nf * n0 * n1;
-      int rpb = static_cast<int>(49152 / ((size_t)(n2 + 1) * sizeof(T)));
-      rpb = rpb > 64 ? 64 : rpb;
-      if (rpb < 1) throw ArgError("prefilter: grid line too long");
-      const size_t sm = (size_t)rpb * (n2 + 1) * sizeof(T);
-      prof::launch(std::string("k_prefilter_inner<") + prof::tname<T>() + ">", 2.0 * rows * n2 * sizeof(T), 0.0,
-                   k_prefilter_inner<T>, dim3(ceil_div(rows, rpb)), dim3(64), (uint32_t)sm, s, f, n2, rows, rpb);
-      LDDMM_LAUNCH_CHECK();
+  if (left == 0)  // a single point: its own coefficient
+    for (int f = 0; f < nf; ++f) {
+      if (a.w[f]) mul<T>(dst + f * d.P, a.src[f], a.w[f], d.P, s);
+      else copy_dev<T>(dst + f * d.P, a.src[f], d.P, s);
     }
-  }
-  if (n1 > 1) {
-    if (n1 <= kChunkMaxN) {
-      // lines along axis 1: tiles of 32 consecutive x2 at fixed x0
-      chunked(n1, 1, (int64_t)n2, n2, (int64_t)n1 * n2, n0);
-    } else {
-      const int64_t lines = (int64_t)n0 * n2;
-      prof::launch(std::string("k_prefilter_outer<") + prof::tname<T>() + ">", 2.0 * nf * d.P * sizeof(T), 0.0,
-                   k_prefilter_outer<T>, grid_for(lines * nf), dim3(kBlock), 0, s, f, n0, n1, n2, 1, lines, d.P, nf);
-      LDDMM_LAUNCH_CHECK();
-    }
-  }
-  if (n0 > 1) {
-    if (n0 <= kChunkMaxN) {
-      // lines along axis 0: tiles of 32 consecutive x2 at fixed x1
-      chunked(n0, 1, (int64_t)n1 * n2, n2, (int64_t)n2, n1);
-    } else {
-      const int64_t lines = (int64_t)n1 * n2;
-      prof::launch(std::string("k_prefilter_outer<") + prof::tname<T>() + ">", 2.0 * nf * d.P * sizeof(T), 0.0,
-                   k_prefilter_outer<T>, grid_for(lines * nf), dim3(kBlock), 0, s, f, n0, n1, n2, 0, lines, d.P, nf);
-      LDDMM_LAUNCH_CHECK();
-    }
-  }
+  for (int axis = 2; axis >= 0; --axis)
+    if (d.n[axis] > 1) pass(axis);
 }
 
 template <typename T>
@@ -907,7 +815,7 @@ void zero(T* p, int64_t n, hipStream_t s) {
   template void bl_div<T>(T*, const T*, const Dims&, hipStream_t);                                      \
   template void characteristics<T>(T*, const T*, const T*, const Dims&, T, int, hipStream_t);           \
   template void interp<T>(T*, const T*, int, const T*, const Dims&, hipStream_t);                       \
-  template void prefilter<T>(T*, int, const Dims&, hipStream_t);                                        \
+  template void prefilter<T>(T*, T*, const T* const*, const T* const*, int, const Dims&, hipStream_t);   \
   template void adjoint_grid_step<T>(T*, const T*, const T*, const T*, const T*, const Dims&, T,        \
                                      hipStream_t);                                                      \
   template void bl_adjoint_step<T>(T*, const T*, const T*, int, const T*, const T*, const Dims&, T,     \

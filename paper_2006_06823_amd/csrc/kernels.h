@@ -165,9 +165,11 @@ void characteristics(T* disp, const T* v, const T* cv, const Dims& d, T dt, int 
 // out_f = P(c_f) o X, X = x + disp, for nf <= 3 coefficient fields
 template <typename T>
 void interp(T* out, const T* coef, int nf, const T* disp, const Dims& d, hipStream_t s);
-// periodic cubic B-spline prefilter of nf fields, in place
+// Periodic cubic B-spline prefilter of nf <= 2 fields, dst [nf][P] from the samples src[f] (times the pointwise
+// factor w[f] where w and w[f] are given); tmp: scratch of dst's size.  dst and tmp alias neither each other nor
+// the inputs.
 template <typename T>
-void prefilter(T* f, int nf, const Dims& d, hipStream_t s);
+void prefilter(T* dst, T* tmp, const T* const* src, const T* const* w, int nf, const Dims& d, hipStream_t s);
 // variant-1 adjoint Heun step on the grid:
 //   a = c1 o X, b = c2 o X, out = a + dt/2 (b + (a + dt b) divv)
 template <typename T>

@@ -128,8 +128,7 @@ class Solver final : public SolverBase {
   void set_images(const void* I0, const void* I1) override {
     copy(I0_.get(), static_cast<const T*>(I0), d_.P);
     copy(I1_.get(), static_cast<const T*>(I1), d_.P);
-    copy(cI0_.get(), I0_.get(), d_.P);
-    prefilter(cI0_.get(), 1, d_, st_);
+    spline_coefficients(cI0_.get(), S(0), I0_.get());
     have_images_ = true;
     state_valid_ = false;
     coarse_.reset();  // the coarse level restricts these images
@@ -491,6 +490,9 @@ class Solver final : public SolverBase {
     return m;
   }
 
+  // B-spline coefficients of a grid field (c, tmp and f distinct)
+  void spline_coefficients(T* c, T* tmp, const T* f) { prefilter<T>(c, tmp, &f, nullptr, 1, d_, st_); }
+
   // ------------------------------------ truncated products on the product grid
   // x (ncomp band fields) against the state at node n:
   //   image transport (ncomp 1): pi'([e div v, e G_0, e G_1, e G_2]), G = grad~ m~_n
@@ -675,8 +677,7 @@ class Solver final : public SolverBase {
       T* mn = m_.get() + n * P;
       full_.pi(mn, mt_.get() + n * Q, 1);  // m~_n
       if (n < nt_) {
-        copy(S(0), mn, P);
-        prefilter(S(0), 1, d_, st_);
+        spline_coefficients(S(0), S(1), mn);
         interp<T>(mn + P, S(0), 1, XbN(n), d_, st_);
       }
     }
@@ -794,16 +795,16 @@ class Solver final : public SolverBase {
   // lambda(1) = -(2/sigma^2)(m(1) - I1)
   void adjoint_v2(T* g) {
     scaled_diff<T>(S(0), T(-2.0 / sigma2_), m1_.get(), I1_.get(), d_.P, st_);
-    prefilter(S(0), 1, d_, st_);
-    pull_back_terms(S(0), T(1), lamt_.get(), acc_.get(), g, vbl_.get());
+    spline_coefficients(S(1), S(2), S(0));
+    pull_back_terms(S(1), T(1), lamt_.get(), acc_.get(), g, vbl_.get());
   }
 
   // Gauss-Newton incremental adjoint: dlambda(1) = -(2/sigma^2) dm(1), dm(1) = -g1 . iota(du~(1))
   void matvec_tail_v2(const T* du1, T* h, const T* dv) {
     full_.iota_kind(du1, S(0), 3, kPlain);
     v1_source<T>(S(3), g1_.get(), S(0), d_, st_);
-    prefilter(S(3), 1, d_, st_);
-    pull_back_terms(S(3), T(-2.0 / sigma2_), incadj_.get(), acc_.get(), h, dv);
+    spline_coefficients(S(4), S(5), S(3));
+    pull_back_terms(S(4), T(-2.0 / sigma2_), incadj_.get(), acc_.get(), h, dv);
   }
 
   // ----------------- explicit RK4 comparator (deformation-state equations in Eulerian form)
@@ -999,9 +1000,10 @@ class Solver final : public SolverBase {
         products(tmpbl_.get(), 1, n, dst, al, be);
       }
       if (n == 0) break;
-      copy(S(5), lam, P);
-      mul<T>(S(6), lam, divvN(n), P, st_);
-      prefilter(S(5), 2, d_, st_);
+      // the coefficients of lambda and of lambda div v
+      const T* src[2] = {lam, lam};
+      const T* w[2] = {nullptr, divvN(n)};
+      prefilter<T>(S(5), S(7), src, w, 2, d_, st_);
       adjoint_grid_step<T>(lam_next, S(5), S(6), XfN(n - 1), divvN(n - 1), d_, dt_, st_);
       std::swap(lam, lam_next);
     }
