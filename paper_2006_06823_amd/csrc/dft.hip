@@ -5,9 +5,8 @@
 //   left : out[b][m][c] = sum_l W[m][l] in[b][l][c]   (contract a non-last axis;
 //          rows l of the input are contiguous in c, so loads are coalesced)
 //   right: out[r][m]    = sum_l in[r][l] W[m][l]      (contract the last axis)
-// In float the products run on the matrix cores (v_mfma_f32_32x32x2f32: each
-// wave owns a 32 x 32 output block); in double the same tiling runs on the
-// vector FMA units.  Tiles of W and of the input are staged through LDS.
+// The products run on the matrix cores (v_mfma_f32_32x32x2f32: each wave owns a
+// 32 x 32 output block).  Tiles of W and of the input are staged through LDS.
 #include "kernels.h"
 #include "prof.h"
 #include "stage.h"
@@ -29,11 +28,6 @@ constexpr int LC = 32;  // contraction chunk staged in LDS
 // for the 32x32 output layout of the matrix-core instruction.
 __device__ __forceinline__ int acc_row(int r, int lane) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); }
 
-template <typename T>
-struct Acc16 {
-  T v[16];
-};
-
 // One LC-deep chunk of a 32x32 block product: acc[i][j] += sum_k A[i][k] B[k][j],
 // A read as As[(arow0 + i) * lda + k], B as Bs[k * ldb + bcol0 + j].
 __device__ __forceinline__ void chunk_mma(f32x16& acc, const float* As, int lda, const float* Bs, int ldb,
@@ -47,66 +41,35 @@ __device__ __forceinline__ void chunk_mma(f32x16& acc, const float* As, int lda,
   }
 }
 
-__device__ __forceinline__ void chunk_mma(Acc16<double>& acc, const double* As, int lda, const double* Bs,
-                                          int ldb, int lane) {
-  const int j = lane & 31;
-#pragma unroll 4
-  for (int kk = 0; kk < LC; ++kk) {
-    const double b = Bs[kk * ldb + j];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc.v[r] += As[acc_row(r, lane) * lda + kk] * b;
-  }
-}
-
-template <typename T>
-struct AccOf;
-template <>
-struct AccOf<float> {
-  using type = f32x16;
-  static __device__ __forceinline__ float get(const f32x16& a, int r) { return a[r]; }
-  static __device__ __forceinline__ void zero(f32x16& a) {
-#pragma unroll
-    for (int r = 0; r < 16; ++r) a[r] = 0.f;
-  }
-};
-template <>
-struct AccOf<double> {
-  using type = Acc16<double>;
-  static __device__ __forceinline__ double get(const Acc16<double>& a, int r) { return a.v[r]; }
-  static __device__ __forceinline__ void zero(Acc16<double>& a) {
-#pragma unroll
-    for (int r = 0; r < 16; ++r) a.v[r] = 0.0;
-  }
-};
-
 // out[b][m][c] = sum_l W[m][l] in[b][l][c]; block tile (32 WM) x (32 WC), one wave per 32x32 block.
-template <typename T, int WM, int WC>
-__global__ __launch_bounds__(64 * WM * WC) void dft_left_kernel(const T* __restrict__ in, T* __restrict__ out,
-                                                                FieldMats<T> mats, int bpf, int M, int L,
+template <int WM, int WC>
+__global__ __launch_bounds__(64 * WM * WC) void dft_left_kernel(const float* __restrict__ in, float* __restrict__ out,
+                                                                FieldMats<float> mats, int bpf, int M, int L,
                                                                 int C, int64_t sIb, int64_t sOb) {
   constexpr int TM = 32 * WM, TC = 32 * WC, NT = 64 * WM * WC;
   constexpr int LDA = LC + 1;
-  __shared__ T Ws[TM * LDA];
-  __shared__ T Xs[LC * TC];
+  __shared__ float Ws[TM * LDA];
+  __shared__ float Xs[LC * TC];
   const int b = blockIdx.z;
-  const T* __restrict__ W = mats.w[b / bpf];
+  const float* __restrict__ W = mats.w[b / bpf];
   const int m0 = blockIdx.y * TM, c0 = blockIdx.x * TC;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WC, wc = wave % WC;
   in += b * sIb;
   out += b * sOb;
-  typename AccOf<T>::type acc;
-  AccOf<T>::zero(acc);
+  f32x16 acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
   for (int l0 = 0; l0 < L; l0 += LC) {
     for (int e = tid; e < TM * LC; e += NT) {
       const int mm = e / LC, ll = e - mm * LC;
       const int m = m0 + mm, l = l0 + ll;
-      Ws[mm * LDA + ll] = (m < M && l < L) ? W[(int64_t)m * L + l] : T(0);
+      Ws[mm * LDA + ll] = (m < M && l < L) ? W[(int64_t)m * L + l] : 0.f;
     }
     for (int e = tid; e < LC * TC; e += NT) {
       const int ll = e / TC, cc = e - ll * TC;
       const int l = l0 + ll, c = c0 + cc;
-      Xs[ll * TC + cc] = (l < L && c < C) ? in[(int64_t)l * C + c] : T(0);
+      Xs[ll * TC + cc] = (l < L && c < C) ? in[(int64_t)l * C + c] : 0.f;
     }
     __syncthreads();
     chunk_mma(acc, Ws + wm * 32 * LDA, LDA, Xs + wc * 32, TC, lane);
@@ -117,39 +80,40 @@ __global__ __launch_bounds__(64 * WM * WC) void dft_left_kernel(const T* __restr
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int m = m0 + wm * 32 + acc_row(r, lane);
-      if (m < M) out[(int64_t)m * C + c] = AccOf<T>::get(acc, r);
+      if (m < M) out[(int64_t)m * C + c] = acc[r];
     }
   }
 }
 
 // out[f][r][m] = sum_l in[f][r][l] W_f[m][l]; block tile rows (32 WR) x outputs (32 WM).
-template <typename T, int WR, int WM>
-__global__ __launch_bounds__(64 * WR * WM) void dft_right_kernel(const T* __restrict__ in, T* __restrict__ out,
-                                                                 FieldMats<T> mats, int R, int L, int Mo) {
+template <int WR, int WM>
+__global__ __launch_bounds__(64 * WR * WM) void dft_right_kernel(const float* __restrict__ in, float* __restrict__ out,
+                                                                 FieldMats<float> mats, int R, int L, int Mo) {
   constexpr int TR = 32 * WR, TMo = 32 * WM, NT = 64 * WR * WM;
   constexpr int LDA = LC + 1;
-  __shared__ T Xs[TR * LDA];
-  __shared__ T Ws[LC * TMo];
+  __shared__ float Xs[TR * LDA];
+  __shared__ float Ws[LC * TMo];
   const int f = blockIdx.z;
-  const T* __restrict__ W = mats.w[f];
+  const float* __restrict__ W = mats.w[f];
   in += (int64_t)f * R * L;
   out += (int64_t)f * R * Mo;
   const int r0 = blockIdx.y * TR, m0 = blockIdx.x * TMo;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wr = wave / WM, wm = wave % WM;
-  typename AccOf<T>::type acc;
-  AccOf<T>::zero(acc);
+  f32x16 acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
   for (int l0 = 0; l0 < L; l0 += LC) {
     for (int e = tid; e < TR * LC; e += NT) {
       const int rr = e / LC, ll = e - rr * LC;
       const int r = r0 + rr, l = l0 + ll;
-      Xs[rr * LDA + ll] = (r < R && l < L) ? in[(int64_t)r * L + l] : T(0);
+      Xs[rr * LDA + ll] = (r < R && l < L) ? in[(int64_t)r * L + l] : 0.f;
     }
     // W staged transposed, [l][m], so the B operand is read contiguously
     for (int e = tid; e < TMo * LC; e += NT) {
       const int mm = e / LC, ll = e - mm * LC;
       const int m = m0 + mm, l = l0 + ll;
-      Ws[ll * TMo + mm] = (m < Mo && l < L) ? W[(int64_t)m * L + l] : T(0);
+      Ws[ll * TMo + mm] = (m < Mo && l < L) ? W[(int64_t)m * L + l] : 0.f;
     }
     __syncthreads();
     chunk_mma(acc, Xs + wr * 32 * LDA, LDA, Ws + wm * 32, TMo, lane);
@@ -160,7 +124,7 @@ __global__ __launch_bounds__(64 * WR * WM) void dft_right_kernel(const T* __rest
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
       const int r = r0 + wr * 32 + acc_row(q, lane);
-      if (r < R) out[(int64_t)r * Mo + m] = AccOf<T>::get(acc, q);
+      if (r < R) out[(int64_t)r * Mo + m] = acc[q];
     }
   }
 }
@@ -566,102 +530,90 @@ void dft_left_bf16(const float* in, float* out, const FieldMats<float>& W, int n
     };
     run(tune::choose(cap_key("expand_bf16", M, L, C), kCaps, kNumCaps, 768, run, s));
   } else {
-    return dft_left<float>(in, out, W, nb, bpf, M, L, C, sIb, sOb, s);
+    return dft_left(in, out, W, nb, bpf, M, L, C, sIb, sOb, s);
   }
   LDDMM_LAUNCH_CHECK();
 }
 
-template <typename T>
-void dft_left(const T* in, T* out, const FieldMats<T>& W, int nb, int bpf, int M, int L, int C, int64_t sIb,
-              int64_t sOb, hipStream_t s) {
+void dft_left(const float* in, float* out, const FieldMats<float>& W, int nb, int bpf, int M, int L, int C,
+              int64_t sIb, int64_t sOb, hipStream_t s) {
   if (nb <= 0 || M <= 0 || C <= 0) return;
   if (nb > 65535) throw ArgError("dft_left: batch too large");
-  const double bytes = double(sizeof(T)) * ((double)nb * L * C + (double)nb * M * C);
+  const double bytes = 4.0 * ((double)nb * L * C + (double)nb * M * C);
   const double flops = 2.0 * nb * M * (double)L * C;
-  if constexpr (std::is_same_v<T, float>) {
-    if (M <= 64 && L > 64 && L <= 192) {
-      const int MB = M > 32 ? 2 : 1;
-      const size_t wsz = (size_t)32 * MB * (L + 1), rsz = (size_t)4 * 16 * 64;
-      const int sep = (wsz + rsz) * sizeof(float) <= 65536 ? 1 : 0;
-      const uint32_t sm = (uint32_t)((sep ? wsz + rsz : std::max(wsz, rsz)) * sizeof(float));
-      const int ncb = ceil_div(C, 64);
-      // the two-tile kernel's registers leave room for 2 blocks per CU: at most 512 blocks keeps the
-      // grid resident in one round, each block walking several column tiles with its W tile
-      // (1024 ran a second round: 160x192x160 contraction 2.10 -> 1.86 ms per matvec)
-      auto run = [&](int cap) {
-        const int gx = sep ? std::max(1, std::min(ncb, cap / std::max(1, nb))) : ncb;
-        dim3 g(gx, 1, nb);
-        if (MB == 2)
-          prof::launch("dft_left_contract<2>", bytes, flops, dft_left_contract<2, 2>, g, dim3(256), sm, s, in, out,
-                       W, bpf, M, L, C, sIb, sOb, sep);
-        else
-          prof::launch("dft_left_contract<1>", bytes, flops, dft_left_contract<1, 2>, g, dim3(256), sm, s, in, out,
-                       W, bpf, M, L, C, sIb, sOb, sep);
-      };
-      const int dflt = MB == 2 ? 512 : 1024;
-      run(sep ? tune::choose(cap_key(MB == 2 ? "contract2_f32" : "contract1_f32", M, L, C), kCaps, kNumCaps, dflt,
-                             run, s)
-              : dflt);
-      LDDMM_LAUNCH_CHECK();
-      return;
-    }
-    if (L <= 64) {
-      const uint32_t sm = (uint32_t)(128 * (L + 1) + L * kExpLdb) * sizeof(float);
-      const int ncb = ceil_div(C, kExpCols), gy = ceil_div(M, 128);
-      // at most 1024 blocks (4 per CU): the whole grid is resident at once and each block walks
-      // several column tiles with its W tile staged once (2048 left a second, partial round:
-      // 160x192x160 expansion 1.45 -> 1.22 ms per matvec)
-      const int vec = (C % 4 == 0) && (sIb % 4 == 0) && (reinterpret_cast<uintptr_t>(in) % 16 == 0);
-      auto run = [&](int cap) {
-        const int gx = std::max(1, std::min(ncb, cap / std::max(1, nb * gy)));
-        dim3 g(gx, gy, nb);
-        prof::launch("dft_left_expand", bytes, flops, dft_left_expand, g, dim3(256), sm, s, in, out, W, bpf, M, L, C,
-                     sIb, sOb, vec);
-      };
-      run(tune::choose(cap_key("expand_f32", M, L, C), kCaps, kNumCaps, 1024, run, s));
-      LDDMM_LAUNCH_CHECK();
-      return;
-    }
+  if (M <= 64 && L > 64 && L <= 192) {
+    const int MB = M > 32 ? 2 : 1;
+    const size_t wsz = (size_t)32 * MB * (L + 1), rsz = (size_t)4 * 16 * 64;
+    const int sep = (wsz + rsz) * sizeof(float) <= 65536 ? 1 : 0;
+    const uint32_t sm = (uint32_t)((sep ? wsz + rsz : std::max(wsz, rsz)) * sizeof(float));
+    const int ncb = ceil_div(C, 64);
+    // the two-tile kernel's registers leave room for 2 blocks per CU: at most 512 blocks keeps the
+    // grid resident in one round, each block walking several column tiles with its W tile
+    // (1024 ran a second round: 160x192x160 contraction 2.10 -> 1.86 ms per matvec)
+    auto run = [&](int cap) {
+      const int gx = sep ? std::max(1, std::min(ncb, cap / std::max(1, nb))) : ncb;
+      dim3 g(gx, 1, nb);
+      if (MB == 2)
+        prof::launch("dft_left_contract<2>", bytes, flops, dft_left_contract<2, 2>, g, dim3(256), sm, s, in, out,
+                     W, bpf, M, L, C, sIb, sOb, sep);
+      else
+        prof::launch("dft_left_contract<1>", bytes, flops, dft_left_contract<1, 2>, g, dim3(256), sm, s, in, out,
+                     W, bpf, M, L, C, sIb, sOb, sep);
+    };
+    const int dflt = MB == 2 ? 512 : 1024;
+    run(sep ? tune::choose(cap_key(MB == 2 ? "contract2_f32" : "contract1_f32", M, L, C), kCaps, kNumCaps, dflt,
+                           run, s)
+            : dflt);
+    LDDMM_LAUNCH_CHECK();
+    return;
   }
-  const std::string nm = std::string("dft_left_kernel<") + prof::tname<T>() + ">";
+  if (L <= 64) {
+    const uint32_t sm = (uint32_t)(128 * (L + 1) + L * kExpLdb) * sizeof(float);
+    const int ncb = ceil_div(C, kExpCols), gy = ceil_div(M, 128);
+    // at most 1024 blocks (4 per CU): the whole grid is resident at once and each block walks
+    // several column tiles with its W tile staged once (2048 left a second, partial round:
+    // 160x192x160 expansion 1.45 -> 1.22 ms per matvec)
+    const int vec = (C % 4 == 0) && (sIb % 4 == 0) && (reinterpret_cast<uintptr_t>(in) % 16 == 0);
+    auto run = [&](int cap) {
+      const int gx = std::max(1, std::min(ncb, cap / std::max(1, nb * gy)));
+      dim3 g(gx, gy, nb);
+      prof::launch("dft_left_expand", bytes, flops, dft_left_expand, g, dim3(256), sm, s, in, out, W, bpf, M, L, C,
+                   sIb, sOb, vec);
+    };
+    run(tune::choose(cap_key("expand_f32", M, L, C), kCaps, kNumCaps, 1024, run, s));
+    LDDMM_LAUNCH_CHECK();
+    return;
+  }
+  const std::string nm = "dft_left_kernel";
   if (M > 64) {
     dim3 g(ceil_div(C, 32), ceil_div(M, 128), nb);
-    prof::launch(nm, bytes, flops, dft_left_kernel<T, 4, 1>, g, dim3(256), 0, s, in, out, W, bpf, M, L, C, sIb, sOb);
+    prof::launch(nm, bytes, flops, dft_left_kernel<4, 1>, g, dim3(256), 0, s, in, out, W, bpf, M, L, C, sIb, sOb);
   } else if (M > 32) {
     dim3 g(ceil_div(C, 64), ceil_div(M, 64), nb);
-    prof::launch(nm, bytes, flops, dft_left_kernel<T, 2, 2>, g, dim3(256), 0, s, in, out, W, bpf, M, L, C, sIb, sOb);
+    prof::launch(nm, bytes, flops, dft_left_kernel<2, 2>, g, dim3(256), 0, s, in, out, W, bpf, M, L, C, sIb, sOb);
   } else {
     dim3 g(ceil_div(C, 128), ceil_div(M, 32), nb);
-    prof::launch(nm, bytes, flops, dft_left_kernel<T, 1, 4>, g, dim3(256), 0, s, in, out, W, bpf, M, L, C, sIb, sOb);
+    prof::launch(nm, bytes, flops, dft_left_kernel<1, 4>, g, dim3(256), 0, s, in, out, W, bpf, M, L, C, sIb, sOb);
   }
   LDDMM_LAUNCH_CHECK();
 }
 
-template <typename T>
-void dft_right(const T* in, T* out, const FieldMats<T>& W, int nf, int R, int L, int Mo, hipStream_t s) {
+void dft_right(const float* in, float* out, const FieldMats<float>& W, int nf, int R, int L, int Mo, hipStream_t s) {
   if (nf <= 0 || R <= 0 || Mo <= 0) return;
-  const std::string nm = std::string("dft_right_kernel<") + prof::tname<T>() + ">";
-  const double bytes = double(sizeof(T)) * ((double)nf * R * L + (double)nf * R * Mo);
+  const std::string nm = "dft_right_kernel";
+  const double bytes = 4.0 * ((double)nf * R * L + (double)nf * R * Mo);
   const double flops = 2.0 * nf * R * (double)L * Mo;
   if (Mo > 64) {
     dim3 g(ceil_div(Mo, 128), ceil_div(R, 32), nf);
-    prof::launch(nm, bytes, flops, dft_right_kernel<T, 1, 4>, g, dim3(256), 0, s, in, out, W, R, L, Mo);
+    prof::launch(nm, bytes, flops, dft_right_kernel<1, 4>, g, dim3(256), 0, s, in, out, W, R, L, Mo);
   } else if (Mo > 32) {
     dim3 g(ceil_div(Mo, 64), ceil_div(R, 32), nf);
-    prof::launch(nm, bytes, flops, dft_right_kernel<T, 1, 2>, g, dim3(128), 0, s, in, out, W, R, L, Mo);
+    prof::launch(nm, bytes, flops, dft_right_kernel<1, 2>, g, dim3(128), 0, s, in, out, W, R, L, Mo);
   } else {
     dim3 g(ceil_div(Mo, 32), ceil_div(R, 32), nf);
-    prof::launch(nm, bytes, flops, dft_right_kernel<T, 1, 1>, g, dim3(64), 0, s, in, out, W, R, L, Mo);
+    prof::launch(nm, bytes, flops, dft_right_kernel<1, 1>, g, dim3(64), 0, s, in, out, W, R, L, Mo);
   }
   LDDMM_LAUNCH_CHECK();
 }
-
-template void dft_left<float>(const float*, float*, const FieldMats<float>&, int, int, int, int, int, int64_t,
-                              int64_t, hipStream_t);
-template void dft_left<double>(const double*, double*, const FieldMats<double>&, int, int, int, int, int,
-                               int64_t, int64_t, hipStream_t);
-template void dft_right<float>(const float*, float*, const FieldMats<float>&, int, int, int, int, hipStream_t);
-template void dft_right<double>(const double*, double*, const FieldMats<double>&, int, int, int, int,
-                                hipStream_t);
 
 }  // namespace lddmm

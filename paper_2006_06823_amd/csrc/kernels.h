@@ -8,11 +8,9 @@ namespace lddmm {
 // ---- separable truncated DFT contractions (dft.hip) -------------------------
 // left:  out[b][m][c] = sum_l W_f[m][l] in[b][l][c],   f = b / bpf, b < nb
 // right: out[f][r][m] = sum_l in[f][r][l] W_f[m][l],   r < R, f < nf
-template <typename T>
-void dft_left(const T* in, T* out, const FieldMats<T>& W, int nb, int bpf, int M, int L, int C,
+void dft_left(const float* in, float* out, const FieldMats<float>& W, int nb, int bpf, int M, int L, int C,
               int64_t sIb, int64_t sOb, hipStream_t s);
-template <typename T>
-void dft_right(const T* in, T* out, const FieldMats<T>& W, int nf, int R, int L, int Mo, hipStream_t s);
+void dft_right(const float* in, float* out, const FieldMats<float>& W, int nf, int R, int L, int Mo, hipStream_t s);
 
 // bf16 hi/lo split variants (float in/out, bf16 matrix-core products, float accumulation)
 void dft_left_bf16(const float* in, float* out, const FieldMats<float>& W, int nb, int bpf, int M, int L,
@@ -44,6 +42,33 @@ bool fused_dft_ok(int n1, int n2, int k1, int k2);
 int pi_ba_splits(int n1);
 void iota_ab(const IotaABArgs& a, int nf, hipStream_t s);
 void pi_ba(const PiBAArgs& a, int nf, hipStream_t s);
+
+// the same in double (dft_f64.hip): both inner axes of small planes in one kernel, else one axis each
+struct IotaABF64Args {
+  const double* x[kMaxFields];
+  const double* y[kMaxFields];
+  double alpha[kMaxFields];
+  const double* w1t[kMaxFields];
+  const double* w2t[kMaxFields];
+  bool zero[kMaxFields];  // write zeros (a derivative along a degenerate first axis)
+  double* out;            // [nf][k0][n1][n2]
+  int k0, k1, k2, n1, n2;
+};
+struct PiBAF64Args {
+  const double* in;  // [nf][k0][n1][n2]
+  const double* p1t;
+  const double* p2t;
+  double* out[kMaxFields];
+  double alpha[kMaxFields];
+  double beta[kMaxFields];
+  int k0, k1, k2, n1, n2;
+};
+constexpr int64_t kFusedF64Plane = 256 * 256;
+bool fused_f64_ok(int n1, int n2, int k1, int k2);
+void iota_ab_f64(const IotaABF64Args& a, int nf, hipStream_t s);
+void pi_ba_f64(const PiBAF64Args& a, int nf, hipStream_t s);
+void axis_f64(const double* in, double* out, const FieldMats<double>& W, int nb, int bpf, int M, int L, int C,
+              int64_t sIb, int64_t sOb, bool last, hipStream_t s);
 
 // plane-wise truncated DFT (dft_planes.hip), float.  Plane-band arrays are [x0][a1][a2] with
 // C = K1 K2 columns per grid plane.

@@ -227,16 +227,14 @@ class Plan {
   // iota of nf stacked BL fields; kinds[f][axis] picks plain / prefiltered / derivative matrices
   void iota(const T* bl, T* out, int nf, const int kinds[][3]) {
     const int n0 = d_.n[0], n1 = d_.n[1], n2 = d_.n[2], k0 = d_.k[0], k1 = d_.k[1], k2 = d_.k[2];
-    if constexpr (std::is_same_v<T, float>) {
-      if (planes_ || fused_dft_ok(n1, n2, k1, k2)) {
-        const T* xs[kMaxFields];
-        for (int f = 0; f < nf; ++f) xs[f] = bl + f * d_.Q;
-        return iota_comb(xs, nullptr, nullptr, out, nf, kinds);
-      }
+    if (fused_inner()) {
+      const T* xs[kMaxFields];
+      for (int f = 0; f < nf; ++f) xs[f] = bl + f * d_.Q;
+      return iota_comb(xs, nullptr, nullptr, out, nf, kinds);
     }
     FieldMats<T> W{};
     for (int f = 0; f < nf; ++f) W.w[f] = mat(2, kinds[f][2]);
-    dft_right(bl, t1_.get(), W, nf, k0 * k1, k2, n2, s());
+    right(bl, t1_.get(), W, nf, k0 * k1, k2, n2);
     const bool skip0 = (n0 == 1 && k0 == 1);
     T* dstB = skip0 ? out : t2_.get();
     for (int f = 0; f < nf; ++f) W.w[f] = mat(1, kinds[f][1]);
@@ -288,6 +286,25 @@ class Plan {
         }
         return;
       }
+    } else if (fused_inner()) {
+      IotaABF64Args a{};
+      for (int f = 0; f < nf; ++f) {
+        a.x[f] = xs[f];
+        a.y[f] = ys ? ys[f] : nullptr;
+        a.alpha[f] = al ? al[f] : 0.0;
+        a.w1t[f] = mat(1, kinds[f][1] + kPlainT);
+        a.w2t[f] = mat(2, kinds[f][2] + kPlainT);
+        a.zero[f] = skip0 && kinds[f][0] == kDeriv;
+      }
+      a.out = skip0 ? out : t2_.get();
+      a.k0 = k0, a.k1 = k1, a.k2 = k2, a.n1 = n1, a.n2 = n2;
+      iota_ab_f64(a, nf, s());
+      if (!skip0) {
+        FieldMats<T> W{};
+        for (int f = 0; f < nf; ++f) W.w[f] = mat(0, kinds[f][0]);
+        left(t2_.get(), out, W, nf, 1, n0, k0, n1 * n2, (int64_t)k0 * n1 * n2, d_.P);
+      }
+      return;
     }
     // generic path: stack the combinations, then the separable stages
     for (int f = 0; f < nf; ++f) {
@@ -359,6 +376,25 @@ class Plan {
         pi_ba(b, nf, s());
         return;
       }
+    } else if (fused_inner()) {
+      PiBAF64Args b{};
+      b.in = grid;
+      if (!(n0 == 1 && k0 == 1)) {
+        FieldMats<T> W{};
+        for (int f = 0; f < nf; ++f) W.w[f] = mat(0, kProj);
+        left(grid, t1_.get(), W, nf, 1, k0, n0, n1 * n2, d_.P, (int64_t)k0 * n1 * n2);
+        b.in = t1_.get();
+      }
+      b.p1t = mat(1, kProjT);
+      b.p2t = mat(2, kProjT);
+      for (int f = 0; f < nf; ++f) {
+        b.out[f] = dst[f];
+        b.alpha[f] = alpha[f];
+        b.beta[f] = beta[f];
+      }
+      b.k0 = k0, b.k1 = k1, b.k2 = k2, b.n1 = n1, b.n2 = n2;
+      pi_ba_f64(b, nf, s());
+      return;
     }
     pi_sep(grid, blC_.get(), nf);
     for (int f = 0; f < nf; ++f) {
@@ -411,8 +447,23 @@ class Plan {
             int64_t sOb) {
     if constexpr (std::is_same_v<T, float>) {
       if (bf16_) return dft_left_bf16(in, out, W, nb, bpf, M, L, C, sIb, sOb, s());
+      dft_left(in, out, W, nb, bpf, M, L, C, sIb, sOb, s());
+    } else {
+      axis_f64(in, out, W, nb, bpf, M, L, C, sIb, sOb, false, s());
     }
-    dft_left<T>(in, out, W, nb, bpf, M, L, C, sIb, sOb, s());
+  }
+  void right(const T* in, T* out, const FieldMats<T>& W, int nf, int R, int L, int Mo) {
+    if constexpr (std::is_same_v<T, float>)
+      dft_right(in, out, W, nf, R, L, Mo, s());
+    else
+      axis_f64(in, out, W, nf, 1, R, L, Mo, (int64_t)R * L, (int64_t)R * Mo, true, s());
+  }
+  // both inner axes of a transform run in one kernel (or plane by plane)
+  bool fused_inner() const {
+    if constexpr (std::is_same_v<T, float>)
+      return planes_ || fused_dft_ok(d_.n[1], d_.n[2], d_.k[1], d_.k[2]);
+    else
+      return fused_f64_ok(d_.n[1], d_.n[2], d_.k[1], d_.k[2]);
   }
   // A 2D problem skips the 1 x 1 stage of its degenerate first axis; that stage is the identity
   // except for a derivative along the axis, which vanishes: such fields are zero.
@@ -433,7 +484,7 @@ class Plan {
     for (int f = 0; f < nf; ++f) W.w[f] = mat(1, kProj);
     left(srcB, t2_.get(), W, nf * k0, k0, k1, n1, n2, (int64_t)n1 * n2, (int64_t)k1 * n2);
     for (int f = 0; f < nf; ++f) W.w[f] = mat(2, kProj);
-    dft_right(t2_.get(), bl, W, nf, k0 * k1, n2, k2, s());
+    right(t2_.get(), bl, W, nf, k0 * k1, n2, k2);
   }
 
   Dims d_{};
