@@ -66,6 +66,11 @@ __device__ __forceinline__ float bload_if(Rsrc r, unsigned idx, bool ok) {
   return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)(ok ? idx * 4u : kOut), 0, 0));
 }
 
+// byte offset in a register, element offset uniform: loads at uniform distances share the register
+__device__ __forceinline__ float bload_at(Rsrc r, unsigned voff, unsigned uidx) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)voff, (int)(uidx * 4u), 0));
+}
+
 // Values the compiler cannot see are equal across a wave (they derive from the wave index) are moved
 // to scalar registers, so pointer tables indexed by them are read with scalar loads.
 __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
@@ -182,25 +187,43 @@ struct RedIn {
     }
   }
   __device__ __forceinline__ float operator()(int f, unsigned p) const {
+    float x[kRaw];
+    fetch(f, p * 4u, 0, x);
+    return combine(x);
+  }
+  // the same in two steps, for the node at byte offset v (per lane) plus u elements (uniform): request its values,
+  // then combine them
+  static constexpr int kRaw = MODE == kRedPlain ? 1 : MODE == kRedV1Products ? 2 : MODE == kRedV3Source ? 7 : 6;
+  __device__ __forceinline__ void fetch(int f, unsigned v, unsigned u, float (&x)[kRaw]) const {
     if constexpr (MODE == kRedPlain) {
-      return bload(in, (unsigned)f * P + p);
+      x[0] = bload_at(in, v, (unsigned)f * P + u);
     } else if constexpr (MODE == kRedV1Products) {  // [e div v, e G0, e G1, e G2]
-      const float o = f == 0 ? bload(divv, p) : bload(G, (unsigned)(f - 1) * P + p);
-      return bload(e, p) * o;
+      x[0] = bload_at(e, v, u);
+      x[1] = f == 0 ? bload_at(divv, v, u) : bload_at(G, v, (unsigned)(f - 1) * P + u);
     } else if constexpr (MODE == kRedV3Products) {  // [e_i div v (3), sum_i e_i d_j u_i (3)]
-      if (f < 3) return bload(e, (unsigned)f * P + p) * bload(divv, p);
-      const unsigned j = f - 3;
-      return bload(e, p) * bload(G, j * P + p) + bload(e, P + p) * bload(G, (3 + j) * P + p) +
-             bload(e, 2 * P + p) * bload(G, (6 + j) * P + p);
-    } else if constexpr (MODE == kRedV1Source) {  // node f: -G_f . dv_f
-      const unsigned g = 3u * f * P, q = f * en + p;
-      return -(bload(G, g + p) * bload(e, q) + bload(G, g + P + p) * bload(e, P + q) +
-               bload(G, g + 2 * P + p) * bload(e, 2 * P + q));
-    } else {  // kRedV3Source, field f = 3 n + c: dv_c - sum_j d_j u_c dv_j at node n (dv of node n)
-      const unsigned n = f / 3, c = f - 3 * n, g = (9 * n + 3 * c) * P, q = n * en + p;
-      return bload(e, c * P + q) - (bload(G, g + p) * bload(e, q) + bload(G, g + P + p) * bload(e, P + q) +
-                                    bload(G, g + 2 * P + p) * bload(e, 2 * P + q));
+      if (f < 3) {
+        x[0] = bload_at(e, v, (unsigned)f * P + u), x[1] = bload_at(divv, v, u);
+#pragma unroll
+        for (int k = 2; k < 6; ++k) x[k] = 0.f;
+      } else {
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+          x[2 * k] = bload_at(e, v, k * P + u), x[2 * k + 1] = bload_at(G, v, (unsigned)(3 * k + f - 3) * P + u);
+      }
+    } else {  // node n: -G_n . dv_n, or dv_c - sum_j d_j u_c dv_j (f = 3 n + c)
+      const unsigned n = MODE == kRedV1Source ? f : f / 3, c = f - 3 * n;
+      const unsigned g = (MODE == kRedV1Source ? 3 * n : 9 * n + 3 * c) * P + u, q = n * en + u;
+#pragma unroll
+      for (int k = 0; k < 3; ++k) x[2 * k] = bload_at(G, v, g + k * P), x[2 * k + 1] = bload_at(e, v, k * P + q);
+      if constexpr (MODE == kRedV3Source) x[6] = bload_at(e, v, c * P + q);
     }
+  }
+  static __device__ __forceinline__ float combine(const float (&x)[kRaw]) {
+    if constexpr (MODE == kRedPlain) return x[0];
+    else if constexpr (MODE == kRedV1Products) return x[0] * x[1];
+    else if constexpr (MODE == kRedV3Products) return x[0] * x[1] + x[2] * x[3] + x[4] * x[5];
+    else if constexpr (MODE == kRedV1Source) return -(x[0] * x[1] + x[2] * x[3] + x[4] * x[5]);
+    else return x[6] - (x[0] * x[1] + x[2] * x[3] + x[4] * x[5]);
   }
 };
 
@@ -302,6 +325,173 @@ __global__ __launch_bounds__(64 * WAVES) void k_reduce(PlaneReduceArgs a) {
     for (int w = 0; w < NS; ++w) sum += red[(w * TILES * 16) * 64 + e];
     const int a1 = p * 32 + acc_row(r, l), a2 = q * 32 + (l & 31);
     if (a1 < k1 && a2 < k2) part[a1 * k2 + a2] = sum;
+  }
+}
+
+// ------------------------------------------------------------------ bands above 32: half planes
+// With a band above 32 on an inner axis the kernels above are bound by the matrix cores.  On an axis of even
+// length a basis function of frequency k satisfies w(x + n/2) = (-1)^k w(x), so the coefficients of even and of
+// odd frequencies contribute E and O to a node x < n/2 and E + O, E - O to x and x + n/2: half the products, and
+// tiles, loads and stores of whole rows as before.  Slots 0, 3, 4, 7, 8, .. of a band hold the even frequencies,
+// 1, 2, 5, 6, .. the odd ones (K/2 of each).
+
+// slot of entry j of the even (p = 0) or odd frequencies
+__device__ __forceinline__ int half_slot(int j, int p) { return 4 * (j >> 1) + (p ? 1 + (j & 1) : 3 * (j & 1)); }
+
+// Expansion.  One workgroup per (field f, plane x0, block b of 32 rows x1 < n1/2).  Stage 1: wave 2 p + q forms
+// V[a2][x1] over the frequencies a1 of parity p for the slots a2 of parity q; the sums and differences over p, by
+// LDS, are V at x1 and x1 + n1/2.  Stage 2: a wave per (x2 tile of the half row, half of the rows).
+// B1, B2: k-steps over a parity's K/2 slots.  256^3, 64^3 coefficients, three fields: 112 -> 57 us (201 MB at 3.5
+// TB/s; with the registers of eight waves a workgroup, two waves a SIMD, 72); 160 x 192 x 160, 40 x 48 x 40: 37 -> 22.
+template <int B1, int B2>
+__global__ __launch_bounds__(B2 == 12 ? 512 : 256, B2 == 12 ? 4 : 3) void k_expand_r2(PlaneExpandArgs a) {
+  __shared__ float red[4 * 1024];
+  const int lane = threadIdx.x & 63, i = lane & 31, kh = lane >> 5;
+  const int wave = uniform(threadIdx.x >> 6), nw = blockDim.x >> 6;
+  const int n1 = a.n1, n2 = a.n2, k1 = a.k1, k2 = a.k2, h1 = n1 >> 1, h2 = n2 >> 1;
+  const int T2 = (h2 + 31) >> 5;
+  const int b = blockIdx.x, x0 = blockIdx.y, f = blockIdx.z;
+  const Rsrc rT = rsrc(a.T[f] + x0 * (k1 * k2), (int64_t)(a.n0 - x0) * k1 * k2);
+  const Rsrc r1 = rsrc(a.w1t[f], (int64_t)k1 * n1);  // [k1][n1]
+  const Rsrc r2 = rsrc(a.w2t[f], (int64_t)k2 * n2);  // [k2][n2]
+  float* __restrict__ out = a.out + (size_t)(f * a.n0 + x0) * (size_t)(n1 * n2);
+  float wc[2][B2];
+  auto load_wc = [&](int t) {
+    const unsigned v = (unsigned)(half_slot(acc_row(0, lane), 0) * n2 + t * 32 + i) * 4u;
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int r = 0; r < B2; ++r) wc[q][r] = bload_at(r2, v, half_slot(acc_row(r, 0), q) * n2);
+  };
+  if (wave < 4) {
+    const int p = wave >> 1, q = wave & 1, row = half_slot(kh, p);
+    const unsigned vt = (unsigned)(row * k2 + half_slot(i, q)) * 4u, vw = (unsigned)(row * n1 + b * 32 + i) * 4u;
+    float ta[B1], wb[B1];
+#pragma unroll
+    for (int j = 0; j < B1; ++j) {
+      ta[j] = bload_at(rT, vt, 4 * j * k2);
+      wb[j] = bload_at(r1, vw, 4 * j * n1);
+    }
+    load_wc(wave >> 1);
+    f32x16 V;
+    zero16(V);
+#pragma unroll
+    for (int j = 0; j < B1; ++j) V = mfma(ta[j], wb[j], V);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) red[(wave * 16 + r) * 64 + lane] = V[r];
+  } else {
+    load_wc(wave >> 1);
+  }
+  __syncthreads();
+  for (int task = wave; task < 2 * T2; task += nw) {
+    const int t = task >> 1, sd = task & 1, x2 = t * 32 + i;
+    if (task != wave) load_wc(t);
+    f32x16 E, O;
+    zero16(E);
+    zero16(O);
+#pragma unroll
+    for (int r = 0; r < B2; ++r) {
+      const float e0 = red[r * 64 + lane], e1 = red[(16 + r) * 64 + lane];
+      const float o0 = red[(32 + r) * 64 + lane], o1 = red[(48 + r) * 64 + lane];
+      E = mfma(sd ? e0 - o0 : e0 + o0, wc[0][r], E);
+      O = mfma(sd ? e1 - o1 : e1 + o1, wc[1][r], O);
+    }
+    if (x2 < h2) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int row = b * 32 + acc_row(r, lane);
+        if (row < h1) {
+          const unsigned o = (unsigned)((row + sd * h1) * n2 + x2);
+          out[o] = E[r] + O[r];
+          out[o + h2] = E[r] - O[r];
+        }
+      }
+    }
+  }
+}
+
+// ------------------------------------------------------------------ bands above 32: half planes, reduction
+// The transpose of k_expand_r2: sums and differences of the rows x1, x1 + n1/2 and of the columns x2, x2 + n2/2
+// feed the even and odd frequencies.  One workgroup per (field, plane x0); a wave takes the frequencies a1 of one
+// parity and the tasks (x2 tile t of the half row, chunk of the half column) wave / 2, wave / 2 + nw / 2, ..:
+// stage A, W[x2][a1] for either parity of a2; stage B, R[a1][a2] += sum_x2 W[x2][a1] P2t[x2][a2].  Its registers
+// leave room for four waves a SIMD, which hide each other's loads (both parities in one wave, its loads a block
+// ahead: two waves, slower for plain fields).  256^3, 64^3 coefficients, three fields: 147 -> 70 us (201 MB at 2.9
+// TB/s), 160 x 192 x 160, 40 x 48 x 40: 49 -> 29, its products 31 -> 18.
+template <int MODE>
+__global__ __launch_bounds__(512, 4) void k_reduce_r2(PlaneReduceArgs a, int chunk) {
+  extern __shared__ float red[];  // [waves][2][16][64]
+  typedef RedIn<MODE> In;
+  constexpr int JC = MODE == kRedPlain ? 8 : In::kRaw == 2 ? 4 : 1;  // k-steps of a block
+  const int lane = threadIdx.x & 63, i = lane & 31, kh = lane >> 5;
+  const int wave = uniform(threadIdx.x >> 6), nw = blockDim.x >> 6, p = wave & 1;
+  const int f = blockIdx.x / a.n0, x0 = blockIdx.x - f * a.n0;
+  const int n1 = a.n1, n2 = a.n2, k1 = a.k1, k2 = a.k2, h1 = n1 >> 1, h2 = n2 >> 1;
+  const int T2 = (h2 + 31) >> 5, S1 = (h1 + chunk - 1) / chunk;
+  const In src(a);
+  const Rsrc rp1 = rsrc(a.p1t, (int64_t)n1 * k1), rp2 = rsrc(a.p2t, (int64_t)n2 * k2);
+  const unsigned up = (unsigned)(h1 * n2), plane = (unsigned)(x0 * n1 * n2);
+  const float sg = p ? -1.f : 1.f;
+  const int sl = half_slot(i, p);
+  const unsigned va = sl < k1 ? (unsigned)(kh * k1 + sl) * 4u : kOut;  // this lane's entry of a row (kh) of P1t
+  f32x16 R[2];
+  zero16(R[0]);
+  zero16(R[1]);
+  for (int task = wave >> 1; task < T2 * S1; task += nw >> 1) {
+    const int t = task % T2, c0 = (task / T2) * chunk, c1 = min(h1, c0 + chunk);
+    const unsigned vx = t * 32 + i < h2 ? (unsigned)(kh * n2 + t * 32 + i) * 4u : kOut;
+    f32x16 W[2];
+    zero16(W[0]);
+    zero16(W[1]);
+    // k-step j of a block: rows j0 + 2 j + kh
+    for (int j0 = c0; j0 < c1; j0 += 2 * JC) {
+      float v[JC][4][In::kRaw], pb[JC];
+#pragma unroll
+      for (int j = 0; j < JC; ++j) {
+        const bool row = j0 + 2 * j + kh < c1;
+        const unsigned o = row ? vx : kOut, u = plane + (unsigned)((j0 + 2 * j) * n2);
+        src.fetch(f, o, u, v[j][0]);
+        src.fetch(f, o, u + h2, v[j][1]);
+        src.fetch(f, o, u + up, v[j][2]);
+        src.fetch(f, o, u + up + h2, v[j][3]);
+        pb[j] = bload_at(rp1, row ? va : kOut, (unsigned)((j0 + 2 * j) * k1));
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < JC; ++j) {
+        const float u0 = fmaf(sg, In::combine(v[j][2]), In::combine(v[j][0]));
+        const float u1 = fmaf(sg, In::combine(v[j][3]), In::combine(v[j][1]));
+        W[0] = mfma(u0 + u1, pb[j], W[0]);
+        W[1] = mfma(u0 - u1, pb[j], W[1]);
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int sl2 = half_slot(i, q);
+      const unsigned vb = sl2 < k2 ? (unsigned)(4 * kh * k2 + sl2) * 4u : kOut;
+      float pc[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int row = t * 32 + acc_row(r, 0);
+        pc[r] = bload_at(rp2, row + 4 * kh < h2 ? vb : kOut, (unsigned)(row * k2));
+      }
+#pragma unroll
+      for (int r = 0; r < 16; ++r) R[q] = mfma(W[q][r], pc[r], R[q]);
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < 2; ++q)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) red[((wave * 2 + q) * 16 + r) * 64 + lane] = R[q][r];
+  __syncthreads();
+  // the sum over the waves of a parity, in order
+  float* __restrict__ part = a.part + (size_t)blockIdx.x * (k1 * k2);
+  for (int e = threadIdx.x; e < 4096; e += blockDim.x) {
+    const int l = e & 63, r = (e >> 6) & 15, pp = e >> 11;
+    float sum = red[e];
+    for (int w = 2; w < nw; w += 2) sum += red[(w + pp) * 2048 + (e & 2047)];
+    const int s1 = half_slot(acc_row(r, l), pp), s2 = half_slot(l & 31, (e >> 10) & 1);
+    if (s1 < k1 && s2 < k2) part[s1 * k2 + s2] = sum;
   }
 }
 
@@ -599,6 +789,11 @@ bool planes_ok(const Dims& d) {
          d.k[2] % 2 == 0 && d.P < (int64_t(1) << 31) && (int64_t)d.n[0] * d.k[1] * d.k[2] < (int64_t(1) << 31);
 }
 
+// half planes for a band above 32 on even inner axes (below, the whole-plane kernels are not bound by the products)
+static bool half_planes(int n1, int n2, int k1, int k2) {
+  return (k1 > 32 || k2 > 32) && k1 <= 64 && k2 <= 64 && k1 % 2 == 0 && k2 % 2 == 0 && n1 % 2 == 0 && n2 % 2 == 0;
+}
+
 static int jb_of(int j) { return j <= 8 ? 8 : j <= 16 ? 16 : j <= 24 ? 24 : 32; }
 
 void plane_expand(const PlaneExpandArgs& a, hipStream_t s) {
@@ -608,6 +803,17 @@ void plane_expand(const PlaneExpandArgs& a, hipStream_t s) {
   const double flops = 2.0 * a.nf * a.n0 * ((double)a.k1 * a.k2 * a.n1 + (double)a.n1 * a.k2 * a.n2);
   dim3 g(B1, a.n0, a.nf);
   const int j1 = a.k1 / 2, jb = jb_of(j1);
+  if (half_planes(a.n1, a.n2, a.k1, a.k2)) {
+    const dim3 gh(ceil_div(a.n1 / 2, 32), a.n0, a.nf);
+    const int waves = std::min(a.k2 <= 48 ? 8 : 4, std::max(4, 2 * ceil_div(a.n2 / 2, 32)));
+    auto half = [&](auto kern) { prof::launch("k_expand", bytes, flops, kern, gh, dim3(64 * waves), 0, s, a); };
+    if (a.k1 <= 48 && a.k2 <= 48) half(k_expand_r2<12, 12>);
+    else if (a.k1 <= 48) half(k_expand_r2<12, 16>);
+    else if (a.k2 <= 48) half(k_expand_r2<16, 12>);
+    else half(k_expand_r2<16, 16>);
+    LDDMM_LAUNCH_CHECK();
+    return;
+  }
   auto go = [&](auto kern) { prof::launch("k_expand", bytes, flops, kern, g, dim3(256), 0, s, a); };
   if (a.k2 <= 32) {
     if (j1 == 16) go(k_expand<16, 1, true>); else if (j1 == 20) go(k_expand<20, 1, true>);
@@ -634,6 +840,17 @@ static void reduce_mode(const PlaneReduceArgs& a, hipStream_t s, double bytes, d
   // Small planes (the 48 x 48 product grid of a 32-wide band: two 64-row tasks for eight waves) take
   // 16-row tasks instead, one per wave: each wave's chain of dependent load groups is then one group
   // long instead of four.
+  if (half_planes(a.n1, a.n2, a.k1, a.k2)) {
+    // two waves (the parities of a1) per x2 tile of the half row and chunk of the half column, up to eight;
+    // chunks of at least 16 rows
+    const int th = ceil_div(a.n2 / 2, 32), h1 = a.n1 / 2;
+    const int parts = std::max(1, std::min(4 / th, h1 / 16));
+    const int waves = std::min(8, 2 * th * parts);
+    prof::launch(nm, bytes, flops, k_reduce_r2<MODE>, g, dim3(64 * waves), waves * 2 * 1024 * 4, s, a,
+                 ceil_div(h1, parts));
+    LDDMM_LAUNCH_CHECK();
+    return;
+  }
   const int t2 = ceil_div(a.n2, 32);
   const bool small = 2 * t2 * ceil_div(a.n1, 64) <= 8 && t2 * ceil_div(a.n1, 16) <= 8;
   if (kt1 == 1 && kt2 == 1 && small)
