@@ -344,7 +344,7 @@ __device__ __forceinline__ int half_slot(int j, int p) { return 4 * (j >> 1) + (
 // B1, B2: k-steps over a parity's K/2 slots.  256^3, 64^3 coefficients, three fields: 112 -> 57 us (201 MB at 3.5
 // TB/s; with the registers of eight waves a workgroup, two waves a SIMD, 72); 160 x 192 x 160, 40 x 48 x 40: 37 -> 22.
 template <int B1, int B2>
-__global__ __launch_bounds__(B2 == 12 ? 512 : 256, B2 == 12 ? 4 : 3) void k_expand_r2(PlaneExpandArgs a) {
+__global__ __launch_bounds__(B2 <= 12 ? 512 : 256, B2 <= 12 ? 4 : 3) void k_expand_r2(PlaneExpandArgs a) {
   __shared__ float red[4 * 1024];
   const int lane = threadIdx.x & 63, i = lane & 31, kh = lane >> 5;
   const int wave = uniform(threadIdx.x >> 6), nw = blockDim.x >> 6;
@@ -627,97 +627,95 @@ __global__ __launch_bounds__(512) void k_prod_plane(ProdPlaneArgs a) {
 }
 
 // ------------------------------------------------------------------ first axis
-// Workgroup (column tile of 32 band columns (a1, a2), row y) with the descriptor row[y] resolved on the
-// host: F of field row.f (if any): r[a0][c] = sum_x0 P0t[x0][a0] part[x0][c] (x0 in chunks of 8 dealt
-// to the 4 waves, summed in LDS in wave order), out = beta out + alpha r + gamma z; then up to two P
-// outputs T[x0'][c] = sum_a0 W0t[a0][x0'] (c1 g1 + c2 g2 + cf fin)[a0][c], fin the field just
-// finished.  Every operand that does not depend on F is requested at the start; absent band sources
-// point at zeros.  As in the other stages, ragged lanes read finite neighbours and are not stored, and
-// rows past the end of an operand read as zeros.
-template <int KT0, int JB, bool EXACT, int CPW>
-__global__ __launch_bounds__(256) void k_axis0(Axis0Kernel a) {
-  __shared__ float red[4 * KT0 * 1024];
-  __shared__ float fin[64 * 32];  // the finished field of this workgroup, [a0][32 columns]
+// Workgroup (column tile of 32 band columns (a1, a2), row y) with the descriptor row[y] resolved on the host: F of
+// field y (y < nin): r[a0][c] = sum_x0 P0t[x0][a0] part[x0][c] (x0 in chunks of 8 dealt to the 8 waves, summed in
+// LDS in wave order), out = beta in + alpha r + gamma z + ysym y; then up to two P outputs
+// T[x0'][c] = sum_a0 W0t[a0][x0'] (c1 g1 + c2 g2 + cf fin)[a0][c], fin the field just finished, a wave per output
+// and tile of 32 rows x0'.  A launch is a few dozen workgroups and waits for memory twice, so what bounds it is
+// latency and the fetch of its code: every operand that does not depend on F is requested at the start, each
+// element of a band array by one thread (the sources of P meet in LDS), loads and stores of a lane share one offset
+// register, and rows past the end of an operand read as zeros.  128^3 with 32^3 coefficients: AX_A us with one
+// field and two outputs, AX_B with four fields.
+template <int KT0, int JB>
+__global__ __launch_bounds__(512) void k_axis0(Axis0Kernel a) {
+  __shared__ float red[8 * KT0 * 1024];
+  __shared__ float src[2][KT0 * 1024];  // the sources of the P outputs, [a0][32 columns]
+  constexpr int CB = 3, M = 2 * KT0;    // chunks of a batch; band elements of a thread
   const int lane = threadIdx.x & 63, i = lane & 31, kh = lane >> 5;
   const int wave = uniform(threadIdx.x >> 6);
-  const int C = a.C, k0 = a.k0, J0 = EXACT ? JB : (k0 + 1) >> 1;
-  const int cb = blockIdx.x * 32;
-  const int c = cb + i;
+  const int C = a.C, k0 = a.k0, c = blockIdx.x * 32 + i;
   const Axis0Kernel::Row& row = a.row[blockIdx.y];
-  const int np = row.np;
-  // P operands that do not depend on F: band-array sources and the first row tile of W0t
-  float gsrc[2][JB], wrow[2][JB];
+  const bool hasF = (int)blockIdx.y < a.nin;
+  const Axis0Kernel::Field& F = a.fld[hasF ? blockIdx.y : 0];
+  const int np = row.np, Q = k0 * C;
+  // this thread's band elements: rows elem(m) + 4 kh of column c
+  const unsigned ve = c < C ? (unsigned)(4 * kh * C + c) * 4u : kOut;
+  auto elem = [&](int m) { return 32 * (m >> 1) + acc_row(wave + 8 * (m & 1), 0); };
+  auto request = [&](float (&x)[M], const float* p) {  // p may be null: zeros
 #pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const Axis0Kernel::Out& o = row.p[u < np ? u : 0];
-    const Rsrc r1 = rsrc(o.g1, (int64_t)k0 * C), r2 = rsrc(o.g2, (int64_t)k0 * C);
-    const Rsrc rw = rsrc(o.w0t, (int64_t)k0 * o.n0t);
-    const int x0 = wave * 32 + i;
+    for (int m = 0; m < M; ++m) x[m] = 0.f;
+    if (p) {
+      const Rsrc r = rsrc(p, Q);
 #pragma unroll
-    for (int j = 0; j < JB; ++j) {
-      const int a0 = kh * J0 + j;
-      const bool ok = u < np && (EXACT || j < J0);
-      gsrc[u][j] = o.c1 * bload_if(r1, (unsigned)(a0 * C + c), ok) + o.c2 * bload_if(r2, (unsigned)(a0 * C + c), ok);
-      wrow[u][j] = bload_if(rw, (unsigned)(a0 * o.n0t + x0), ok);
+      for (int m = 0; m < M; ++m) x[m] = bload_at(r, ve, elem(m) * C);
     }
+  };
+  float g[2][2][M], in[M], z[M], y[M];
+  double sym[M];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) request(g[u][0], row.p[u].g1), request(g[u][1], row.p[u].g2);
+  if (hasF) {
+    request(in, F.beta != 0.f ? F.in : nullptr);  // (an output buffer need not hold finite values before)
+    request(z, F.z);
+    request(y, F.y);
+    if (F.y)
+#pragma unroll
+      for (int m = 0; m < M; ++m) {
+        const int a0 = elem(m) + 4 * kh;
+        sym[m] = F.ysym[a0 < k0 && c < C ? a0 * C + c : 0];
+      }
   }
-  if (row.f >= 0) {
-    const Axis0Kernel::Field& F = a.fld[row.f];
-    const int n0 = a.n0;
-    // epilogue operands of this thread's elements
-    float prev[4 * KT0];
+  // the first task's rows of W0t
+  auto tiles = [&](int u) { return (row.p[u].n0t + 31) >> 5; };
+  const int t0 = tiles(0), ntask = np ? t0 + (np > 1 ? tiles(1) : 0) : 0;
+  float w[JB];
+  auto load_w = [&](int task) {
+    const Axis0Kernel::Out& o = row.p[task >= t0];
+    const Rsrc r = rsrc(o.w0t, (int64_t)k0 * o.n0t);
+    const unsigned v = (unsigned)(kh * o.n0t + (task - (task >= t0 ? t0 : 0)) * 32 + i) * 4u;
 #pragma unroll
-    for (int m = 0; m < 4 * KT0; ++m) {
-      const int e = threadIdx.x + 256 * m;
-      const int l = e & 63, r = (e >> 6) & 15, p = e >> 10;
-      const int a0 = p * 32 + acc_row(r, l), cc = cb + (l & 31);
-      const bool ok = a0 < k0 && cc < C;
-      const unsigned o = ok ? (unsigned)(a0 * C + cc) : 0u;
-      // (in is read only when beta != 0: an output buffer need not hold finite values before)
-      float v = F.beta != 0.f ? F.beta * F.in[o] : 0.f;
-      v += F.gamma * F.z[o];
-      if (F.ysym) v += static_cast<float>(F.ysym[o]) * F.y[o];
-      prev[m] = ok ? v : 0.f;
-    }
-    const Rsrc rpart = rsrc(F.part, (int64_t)n0 * C), rp0 = rsrc(a.p0t, (int64_t)n0 * k0);
+    for (int j = 0; j < JB; ++j) w[j] = bload_at(r, v, 2 * j * o.n0t);
+  };
+  if (wave < ntask) load_w(wave);
+  float fin[M] = {};
+  if (hasF) {
+    const int nch = (a.n0 + 7) >> 3;
+    const Rsrc rpart = rsrc(F.part, (int64_t)a.n0 * C), rp0 = rsrc(a.p0t, (int64_t)a.n0 * k0);
+    const unsigned vp = (unsigned)(4 * kh * C + c) * 4u, va = (unsigned)(4 * kh * k0 + i) * 4u;
     f32x16 acc[KT0];
 #pragma unroll
     for (int p = 0; p < KT0; ++p) zero16(acc[p]);
-    // x0 in chunks of 8 (4 k-steps, lane halves 4 apart) dealt to the waves in turn; with CPW > 0 the
-    // wave's CPW chunks are requested at once (chunks past n0 read zeros)
-    const int nch = (n0 + 7) >> 3;
-    if constexpr (CPW > 0) {
-      float bv[CPW][4], av[CPW][KT0][4];
+    // k-step j of a chunk: rows 8 ch + j + 4 kh; a wave's CB chunks are requested at once
+    for (int ch = wave; ch < nch; ch += 8 * CB) {
+      float bv[CB][4], av[CB][KT0][4];
 #pragma unroll
-      for (int u = 0; u < CPW; ++u)
+      for (int u = 0; u < CB; ++u)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          const int x0 = (wave + 4 * u) * 8 + kh * 4 + j;
-          bv[u][j] = bload(rpart, (unsigned)(x0 * C + c));
+          const int x0 = (ch + 8 * u) * 8 + j;
+          bv[u][j] = bload_at(rpart, x0 + 4 * kh < a.n0 ? vp : kOut, x0 * C);
 #pragma unroll
-          for (int p = 0; p < KT0; ++p) av[u][p][j] = bload(rp0, (unsigned)(x0 * k0 + p * 32 + i));
+          for (int p = 0; p < KT0; ++p) av[u][p][j] = bload_at(rp0, x0 + 4 * kh < a.n0 ? va + 128u * p : kOut, x0 * k0);
         }
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int u = 0; u < CPW; ++u)
+      for (int u = 0; u < CB; ++u)
+        if (ch + 8 * u < nch) {
 #pragma unroll
-        for (int p = 0; p < KT0; ++p)
+          for (int p = 0; p < KT0; ++p)
 #pragma unroll
-          for (int j = 0; j < 4; ++j) acc[p] = mfma(av[u][p][j], bv[u][j], acc[p]);
-    } else {
-      for (int ch = wave; ch < nch; ch += 4) {
-        float bv[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) bv[j] = bload(rpart, (unsigned)((ch * 8 + kh * 4 + j) * C + c));
-#pragma unroll
-        for (int p = 0; p < KT0; ++p) {
-          const int a0 = p * 32 + i;
-          float av[4];
-#pragma unroll
-          for (int j = 0; j < 4; ++j) av[j] = bload(rp0, (unsigned)((ch * 8 + kh * 4 + j) * k0 + a0));
-#pragma unroll
-          for (int j = 0; j < 4; ++j) acc[p] = mfma(av[j], bv[j], acc[p]);
+            for (int j = 0; j < 4; ++j) acc[p] = mfma(av[u][p][j], bv[u][j], acc[p]);
         }
-      }
     }
 #pragma unroll
     for (int p = 0; p < KT0; ++p)
@@ -725,58 +723,48 @@ __global__ __launch_bounds__(256) void k_axis0(Axis0Kernel a) {
       for (int r = 0; r < 16; ++r) red[((wave * KT0 + p) * 16 + r) * 64 + lane] = acc[p][r];
     __syncthreads();
 #pragma unroll
-    for (int m = 0; m < 4 * KT0; ++m) {
-      const int e = threadIdx.x + 256 * m;
-      const int l = e & 63, r = (e >> 6) & 15, p = e >> 10;
-      const float sum = red[e] + red[KT0 * 1024 + e] + red[2 * KT0 * 1024 + e] + red[3 * KT0 * 1024 + e];
-      const int a0 = p * 32 + acc_row(r, l), cc = cb + (l & 31);
-      if (a0 < k0 && cc < C) {
-        const unsigned o = (unsigned)(a0 * C + cc);
-        const float v = F.alpha * sum + prev[m];
-        F.out[o] = v;
-        if (F.out2) F.out2[o] = F.s2 * v;
-        fin[a0 * 32 + (l & 31)] = v;
+    for (int m = 0; m < M; ++m) {
+      const int e = threadIdx.x + 512 * m, a0 = elem(m) + 4 * kh;
+      float sum = red[e];
+#pragma unroll
+      for (int q = 1; q < 8; ++q) sum += red[q * KT0 * 1024 + e];
+      const bool ok = a0 < k0 && c < C;
+      float v = F.beta * in[m] + F.gamma * z[m];
+      if (F.y) v += static_cast<float>(sym[m]) * y[m];
+      v = ok ? F.alpha * sum + v : 0.f;
+      if (ok) {
+        F.out[a0 * C + c] = v;
+        if (F.out2) F.out2[a0 * C + c] = F.s2 * v;
       }
+      fin[m] = v;
     }
-    __syncthreads();
   }
-  // P: row tiles rt = wave, wave + 4, ... (the first one's W0t rows were requested at the start)
+  if (np == 0) return;
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
-    if (u >= np) break;
     const Axis0Kernel::Out& o = row.p[u];
-    const bool useF = row.f >= 0 && o.cf != 0.f;
-    float bv[JB];
 #pragma unroll
-    for (int j = 0; j < JB; ++j) {
-      const int a0 = kh * J0 + j;
-      const bool ok = useF && (EXACT || (j < J0 && a0 < k0));
-      const float fv = fin[ok ? a0 * 32 + i : 0];
-      bv[j] = gsrc[u][j] + (ok ? o.cf * fv : 0.f);
+    for (int m = 0; m < M; ++m) {
+      float v = o.c1 * g[u][0][m] + o.c2 * g[u][1][m];
+      if (o.cf != 0.f) v += o.cf * fin[m];
+      src[u][(elem(m) + 4 * kh) * 32 + i] = v;
     }
-    const Rsrc rw = rsrc(o.w0t, (int64_t)k0 * o.n0t);
-    const int RT = (o.n0t + 31) >> 5;
-    for (int rt = wave; rt < RT; rt += 4) {
-      const int x0 = rt * 32 + i;
-      float av[JB];
-      if (rt == wave) {
+  }
+  __syncthreads();
+  for (int task = wave; task < ntask; task += 8) {
+    if (task != wave) load_w(task);
+    const int u = task >= t0, rt = task - (u ? t0 : 0);
+    const Axis0Kernel::Out& o = row.p[u];
+    f32x16 acc;
+    zero16(acc);
 #pragma unroll
-        for (int j = 0; j < JB; ++j) av[j] = wrow[u][j];
-      } else {
+    for (int j = 0; j < JB; ++j) acc = mfma(w[j], src[u][(2 * j + kh) * 32 + i], acc);
+    const Rsrc rT = rsrc(o.T, (int64_t)o.n0t * C);
 #pragma unroll
-        for (int j = 0; j < JB; ++j) av[j] = bload_if(rw, (unsigned)((kh * J0 + j) * o.n0t + x0), EXACT || j < J0);
-      }
-      f32x16 acc;
-      zero16(acc);
-#pragma unroll
-      for (int j = 0; j < JB; ++j) acc = mfma(av[j], bv[j], acc);
-      if (c < C) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int rr = rt * 32 + acc_row(r, lane);
-          if (rr < o.n0t) o.T[(unsigned)(rr * C + c)] = acc[r];
-        }
-      }
+    for (int r = 0; r < 16; ++r) {
+      const int x0 = rt * 32 + acc_row(r, 0);
+      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, (float)acc[r]), rT,
+                                            (int)(x0 + 4 * kh < o.n0t ? ve : kOut), x0 * C * 4, 0);
     }
   }
 }
@@ -789,9 +777,9 @@ bool planes_ok(const Dims& d) {
          d.k[2] % 2 == 0 && d.P < (int64_t(1) << 31) && (int64_t)d.n[0] * d.k[1] * d.k[2] < (int64_t(1) << 31);
 }
 
-// half planes for a band above 32 on even inner axes (below, the whole-plane kernels are not bound by the products)
-static bool half_planes(int n1, int n2, int k1, int k2) {
-  return (k1 > 32 || k2 > 32) && k1 <= 64 && k2 <= 64 && k1 % 2 == 0 && k2 % 2 == 0 && n1 % 2 == 0 && n2 % 2 == 0;
+// half planes on even inner axes where a band reaches beyond `above`
+static bool half_planes(int n1, int n2, int k1, int k2, int above) {
+  return (k1 > above || k2 > above) && k1 <= 64 && k2 <= 64 && k1 % 2 == 0 && k2 % 2 == 0 && n1 % 2 == 0 && n2 % 2 == 0;
 }
 
 static int jb_of(int j) { return j <= 8 ? 8 : j <= 16 ? 16 : j <= 24 ? 24 : 32; }
@@ -803,11 +791,12 @@ void plane_expand(const PlaneExpandArgs& a, hipStream_t s) {
   const double flops = 2.0 * a.nf * a.n0 * ((double)a.k1 * a.k2 * a.n1 + (double)a.n1 * a.k2 * a.n2);
   dim3 g(B1, a.n0, a.nf);
   const int j1 = a.k1 / 2, jb = jb_of(j1);
-  if (half_planes(a.n1, a.n2, a.k1, a.k2)) {
+  if (half_planes(a.n1, a.n2, a.k1, a.k2, 16)) {
     const dim3 gh(ceil_div(a.n1 / 2, 32), a.n0, a.nf);
     const int waves = std::min(a.k2 <= 48 ? 8 : 4, std::max(4, 2 * ceil_div(a.n2 / 2, 32)));
     auto half = [&](auto kern) { prof::launch("k_expand", bytes, flops, kern, gh, dim3(64 * waves), 0, s, a); };
-    if (a.k1 <= 48 && a.k2 <= 48) half(k_expand_r2<12, 12>);
+    if (a.k1 <= 32 && a.k2 <= 32) half(k_expand_r2<8, 8>);
+    else if (a.k1 <= 48 && a.k2 <= 48) half(k_expand_r2<12, 12>);
     else if (a.k1 <= 48) half(k_expand_r2<12, 16>);
     else if (a.k2 <= 48) half(k_expand_r2<16, 12>);
     else half(k_expand_r2<16, 16>);
@@ -840,7 +829,7 @@ static void reduce_mode(const PlaneReduceArgs& a, hipStream_t s, double bytes, d
   // Small planes (the 48 x 48 product grid of a 32-wide band: two 64-row tasks for eight waves) take
   // 16-row tasks instead, one per wave: each wave's chain of dependent load groups is then one group
   // long instead of four.
-  if (half_planes(a.n1, a.n2, a.k1, a.k2)) {
+  if (half_planes(a.n1, a.n2, a.k1, a.k2, 32)) {  // (a parity of a 32-slot band would fill half a tile)
     // two waves (the parities of a1) per x2 tile of the half row and chunk of the half column, up to eight;
     // chunks of at least 16 rows
     const int th = ceil_div(a.n2 / 2, 32), h1 = a.n1 / 2;
@@ -926,22 +915,20 @@ void plane_prod(const ProdPlaneArgs& a, hipStream_t s) {
 void plane_axis0(const Axis0Args& a, hipStream_t s) {
   if (a.nin > kMaxFields || a.nout > kMaxFields) throw ArgError("plane_axis0: too many fields");
   if (a.k0 > 64) throw ArgError("plane_axis0: band above 64");
-  if (!a.zeros) throw ArgError("plane_axis0: zero source missing");
   // descriptor rows: one per finished field (with the P outputs that read it), then one per P output
   // that reads band arrays only
   Axis0Kernel k{};
-  k.p0t = a.p0t, k.n0 = a.n0, k.k0 = a.k0, k.C = a.C;
+  k.p0t = a.p0t, k.n0 = a.n0, k.k0 = a.k0, k.C = a.C, k.nin = a.nin;
   for (int f = 0; f < a.nin; ++f) {
     Axis0Kernel::Field& F = k.fld[f];
     F.part = a.part[f], F.out = a.out[f], F.in = a.in[f] ? a.in[f] : a.out[f], F.out2 = a.out2[f];
-    F.z = a.z[f] ? a.z[f] : a.zeros;
+    F.z = a.z[f];
     F.y = a.y[f], F.ysym = a.y[f] ? a.ysym[f] : nullptr;
     if (F.y && !F.ysym) throw ArgError("plane_axis0: a symbol-weighted term needs its symbol");
     F.alpha = a.alpha[f], F.beta = a.beta[f], F.gamma = a.z[f] ? a.gamma[f] : 0.f;
     F.s2 = a.s2[f] != 0.f ? a.s2[f] : 1.f;
   }
   int nrow = a.nin;
-  for (int f = 0; f < a.nin; ++f) k.row[f].f = f, k.row[f].np = 0;
   double bytes = 4.0 * a.nin * ((double)a.n0 + a.k0) * a.C, flops = 2.0 * a.nin * a.k0 * a.n0 * (double)a.C;
   for (int g = 0; g < a.nout; ++g) {
     const Axis0Out& o = a.o[g];
@@ -955,43 +942,23 @@ void plane_axis0(const Axis0Args& a, hipStream_t s) {
     } else {
       if (nrow >= Axis0Kernel::kRows) throw ArgError("plane_axis0: too many P outputs");
       r = &k.row[nrow++];
-      r->f = -1, r->np = 0;
     }
     Axis0Kernel::Out& p = r->p[r->np++];
     p.w0t = o.w0t, p.T = o.T, p.n0t = o.n0t;
-    p.g1 = o.g1 ? o.g1 : a.zeros, p.c1 = o.g1 ? o.c1 : 0.f;
-    p.g2 = o.g2 ? o.g2 : a.zeros, p.c2 = o.g2 ? o.c2 : 0.f;
+    p.g1 = o.g1, p.c1 = o.g1 ? o.c1 : 0.f;
+    p.g2 = o.g2, p.c2 = o.g2 ? o.c2 : 0.f;
     p.cf = (o.s1 >= 0 ? o.c1 : 0.f) + (o.s2 >= 0 ? o.c2 : 0.f);
     bytes += 4.0 * (double)o.n0t * a.C;
     flops += 2.0 * o.n0t * a.k0 * (double)a.C;
   }
-  for (int y = 0; y < nrow; ++y)  // rows without outputs read their first slot's pointers: valid ones
-    for (int u = k.row[y].np; u < 2; ++u) {
-      Axis0Kernel::Out& p = k.row[y].p[u];
-      p.w0t = a.p0t, p.T = nullptr, p.n0t = 0, p.g1 = p.g2 = a.zeros, p.c1 = p.c2 = p.cf = 0.f;
-    }
   if (nrow == 0) return;
   dim3 g(ceil_div(a.C, 32), nrow);
-  const int j0 = (a.k0 + 1) / 2, jb = jb_of(j0);
-  const bool ex = a.k0 % 2 == 0;
-  const int cpw = ceil_div(ceil_div(a.n0, 8), 4);  // x0 chunks per wave
   const std::string nm = "k_axis0[" + std::to_string(a.nin) + "F" + std::to_string(a.nout) + "P]";
-  auto go = [&](auto kern) { prof::launch(nm, bytes, flops, kern, g, dim3(256), 0, s, k); };
-  if (ex && j0 == 16 && cpw <= 2) go(k_axis0<1, 16, true, 2>);
-  else if (ex && j0 == 16 && cpw <= 4) go(k_axis0<1, 16, true, 4>);
-  else if (ex && j0 == 16) go(k_axis0<1, 16, true, 0>);
-  else if (ex && j0 == 20 && cpw <= 2) go(k_axis0<2, 20, true, 2>);
-  else if (ex && j0 == 20 && cpw <= 6) go(k_axis0<2, 20, true, 6>);
-  else if (ex && j0 == 20) go(k_axis0<2, 20, true, 0>);
-  else if (ex && j0 == 24 && cpw <= 2) go(k_axis0<2, 24, true, 2>);
-  else if (ex && j0 == 24 && cpw <= 6) go(k_axis0<2, 24, true, 6>);
-  else if (ex && j0 == 24) go(k_axis0<2, 24, true, 0>);
-  else if (ex && j0 == 32) go(k_axis0<2, 32, true, 0>);
-  else if (a.k0 <= 32) {
-    if (jb == 8) go(k_axis0<1, 8, false, 0>); else go(k_axis0<1, 16, false, 0>);
-  } else {
-    if (jb == 24) go(k_axis0<2, 24, false, 0>); else go(k_axis0<2, 32, false, 0>);
-  }
+  auto go = [&](auto kern) { prof::launch(nm, bytes, flops, kern, g, dim3(512), 0, s, k); };
+  if (a.k0 <= 16) go(k_axis0<1, 8>);
+  else if (a.k0 <= 32) go(k_axis0<1, 16>);
+  else if (a.k0 <= 48) go(k_axis0<2, 24>);
+  else go(k_axis0<2, 32>);
   LDDMM_LAUNCH_CHECK();
 }
 

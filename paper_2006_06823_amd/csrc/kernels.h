@@ -131,9 +131,8 @@ struct Axis0Args {
   float alpha[kMaxFields], beta[kMaxFields], gamma[kMaxFields], s2[kMaxFields];
   Axis0Out o[kMaxFields];
   int nin, nout, n0, k0, C;
-  const float* zeros;  // >= k0 C zeros, read in place of absent sources
 };
-// kernel view of Axis0Args: one descriptor row per workgroup row (built by plane_axis0)
+// kernel view of Axis0Args: one descriptor row per workgroup row (built by plane_axis0); rows y < nin finish field y
 struct Axis0Kernel {
   static constexpr int kRows = 2 * kMaxFields;
   struct Field {
@@ -155,11 +154,11 @@ struct Axis0Kernel {
     int n0t;
   };
   struct Row {
-    int f, np;
+    int np;
     Out p[2];
   };
   const float* p0t;
-  int n0, k0, C;
+  int n0, k0, C, nin;
   Field fld[kMaxFields];
   Row row[kRows];
 };

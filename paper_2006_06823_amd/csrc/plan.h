@@ -111,8 +111,6 @@ class Plan {
         Tp_.alloc(2 * kMaxFields * d_.n[0] * C());
         LDDMM_HIP(hipMemset(Tp_.get(), 0, Tp_.size() * sizeof(float)));
         reserve_parts(kMaxFields);
-        zeros_.alloc(std::max<int64_t>(d_.Q, 64 * C()));
-        LDDMM_HIP(hipMemset(zeros_.get(), 0, zeros_.size() * sizeof(float)));
       }
     }
   }
@@ -207,7 +205,6 @@ class Plan {
     for (int f = 0; f < nin; ++f) a.part[f] = part(f0 + f);
     a.p0t = mat(0, kProjT);
     a.n0 = d_.n[0], a.k0 = d_.k[0], a.C = static_cast<int>(C());
-    a.zeros = zeros_.get();
     for (int g = 0; g < kMaxFields; ++g) a.o[g].s1 = a.o[g].s2 = -1;
     return a;
   }
@@ -492,7 +489,7 @@ class Plan {
   const hipStream_t* st_ = nullptr;
   int64_t mat_off_[3][kNumMats] = {};
   DevBuf<T> mats_, t1_, t2_, stk_, blC_;
-  DevBuf<float> pipart_, Tp_, part_, zeros_;
+  DevBuf<float> pipart_, Tp_, part_;
 };
 
 }  // namespace lddmm
