@@ -83,52 +83,49 @@ __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirs
 // lane past n1 or n2 reads finite neighbouring entries and its results are not stored, and rows
 // a2 >= k2 of V meet rows of W2t past its end, which read as zeros (every plane-band entry a tile can
 // reach is written or zero-initialised, so finite).
-template <int JB, int KT2, bool EXACT>
+template <int JB, int KT2>
 __global__ __launch_bounds__(256) void k_expand(PlaneExpandArgs a) {
   __shared__ float red[4 * KT2 * 1024];
-  constexpr int JW = (JB + 3) / 4;  // stage-1 k-steps per wave
+  constexpr int JW = JB / 4;  // stage-1 k-steps per wave
   const int lane = threadIdx.x & 63, i = lane & 31, kh = lane >> 5;
   const int wave = uniform(threadIdx.x >> 6);
-  const int n1 = a.n1, n2 = a.n2, k1 = a.k1, k2 = a.k2, J1 = EXACT ? JB : k1 >> 1;
+  const int n1 = a.n1, n2 = a.n2, k1 = a.k1, k2 = a.k2;
   const int T2 = (n2 + 31) >> 5;
   const int b = blockIdx.x, x0 = blockIdx.y, f = blockIdx.z;
   const Rsrc rT = rsrc(a.T[f] + x0 * (k1 * k2), (int64_t)(a.n0 - x0) * k1 * k2);
   const Rsrc r1 = rsrc(a.w1t[f], (int64_t)k1 * n1);  // [k1][n1]
   const Rsrc r2 = rsrc(a.w2t[f], (int64_t)k2 * n2);  // [k2][n2]
   float* __restrict__ out = a.out + (size_t)(f * a.n0 + x0) * (size_t)(n1 * n2);
-  const int x1 = b * 32 + i;
-  // stage-2 operands of the wave's first x2 tile, requested first
-  float wc[KT2][16];
-#pragma unroll
-  for (int q = 0; q < KT2; ++q)
-#pragma unroll
-    for (int r = 0; r < 16; ++r)
-      wc[q][r] = bload_if(r2, (unsigned)((q * 32 + acc_row(r, lane)) * n2 + wave * 32 + i), wave < T2);
-  // stage 1, this wave's k-steps j = wave JW .. wave JW + JW - 1 (a1 = kh J1 + j)
-  float wb[JW];
+  // stage 1, this wave's k-steps j = wave JW .. wave JW + JW - 1 (a1 = 2 j + kh)
+  const int j0 = 2 * JW * wave;
+  const unsigned vt = (unsigned)(kh * k2 + i) * 4u, vw = (unsigned)(kh * n1 + b * 32 + i) * 4u;
+  float wb[JW], ta[KT2][JW];
 #pragma unroll
   for (int u = 0; u < JW; ++u) {
-    const int j = wave * JW + u;
-    wb[u] = bload_if(r1, (unsigned)((kh * J1 + j) * n1 + x1), (EXACT && JW * 4 == JB) || j < J1);
+    wb[u] = bload_at(r1, vw, (j0 + 2 * u) * n1);
+#pragma unroll
+    for (int q = 0; q < KT2; ++q) ta[q][u] = bload_at(rT, vt, (j0 + 2 * u) * k2 + 32 * q);
   }
+  // stage-2 operands of the wave's first x2 tile
+  float wc[KT2][16];
+  auto load_wc = [&](int t) {
+    const unsigned v = (unsigned)(4 * kh * n2 + t * 32 + i) * 4u;
+#pragma unroll
+    for (int q = 0; q < KT2; ++q)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) wc[q][r] = bload_at(r2, v, (q * 32 + acc_row(r, 0)) * n2);
+  };
+  load_wc(wave);
+  __builtin_amdgcn_sched_barrier(0);
   f32x16 V[KT2];
 #pragma unroll
   for (int q = 0; q < KT2; ++q) {
     zero16(V[q]);
-    const int a2 = q * 32 + i;
-    float ta[JW];
 #pragma unroll
-    for (int u = 0; u < JW; ++u) {
-      const int j = wave * JW + u;
-      ta[u] = bload_if(rT, (unsigned)((kh * J1 + j) * k2 + a2), (EXACT && JW * 4 == JB) || j < J1);
-    }
-#pragma unroll
-    for (int u = 0; u < JW; ++u) V[q] = mfma(ta[u], wb[u], V[q]);
-  }
-#pragma unroll
-  for (int q = 0; q < KT2; ++q)
+    for (int u = 0; u < JW; ++u) V[q] = mfma(ta[q][u], wb[u], V[q]);
 #pragma unroll
     for (int r = 0; r < 16; ++r) red[((wave * KT2 + q) * 16 + r) * 64 + lane] = V[q][r];
+  }
   __syncthreads();
 #pragma unroll
   for (int q = 0; q < KT2; ++q)
@@ -138,29 +135,20 @@ __global__ __launch_bounds__(256) void k_expand(PlaneExpandArgs a) {
       V[q][r] = red[e] + red[KT2 * 1024 + e] + red[2 * KT2 * 1024 + e] + red[3 * KT2 * 1024 + e];
     }
   // stage 2: k-step r of tile q contracts a2 = q 32 + acc_row(r); output rows x1, columns x2
-  const bool fullrows = b * 32 + 32 <= n1;
   for (int t2 = wave; t2 < T2; t2 += 4) {
-    const int x2b = t2 * 32, x2 = x2b + i;
-    if (t2 != wave) {
-#pragma unroll
-      for (int q = 0; q < KT2; ++q)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) wc[q][r] = bload(r2, (unsigned)((q * 32 + acc_row(r, lane)) * n2 + x2));
-    }
+    const int x2 = t2 * 32 + i;
+    if (t2 != wave) load_wc(t2);
     f32x16 acc;
     zero16(acc);
 #pragma unroll
     for (int q = 0; q < KT2; ++q)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc = mfma(V[q][r], wc[q][r], acc);
-    if (fullrows && x2b + 32 <= n2) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) out[(unsigned)((b * 32 + acc_row(r, lane)) * n2 + x2)] = acc[r];
-    } else {
+    if (x2 < n2) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int row = b * 32 + acc_row(r, lane);
-        if (row < n1 && x2 < n2) out[(unsigned)(row * n2 + x2)] = acc[r];
+        if (row < n1) out[(unsigned)(row * n2 + x2)] = acc[r];
       }
     }
   }
@@ -251,12 +239,19 @@ __global__ __launch_bounds__(64 * WAVES) void k_reduce(PlaneReduceArgs a) {
 #pragma unroll
     for (int q = 0; q < KT2; ++q) zero16(R[p][q]);
   const unsigned pbase = (unsigned)(x0 * n1 * n2);
-  constexpr int JA = CH / 2;  // stage-A k-steps of a task
-  constexpr int JC = MODE == kRedPlain ? (JA < 16 ? JA : 16) : 8;
+  typedef RedIn<MODE> In;
+  constexpr int JA = CH / 2;  // stage-A k-steps of a task: rows s CH + 2 j + kh
+  // k-steps of a block: the values of 32 loads, half a task of a plain field (one band tile: its operands at once)
+  constexpr int JC = In::kRaw > 2 ? 4 : In::kRaw > 1 ? 8 : JA < 16 ? JA : 16;
   constexpr int NH = JA / JC > 1 ? 2 : 1;  // accumulators (shorter rounding chains)
+  unsigned va[KT1], vb[KT2];  // this lane's entry of a row (kh) of P1t, of a row (4 kh) of P2t
+#pragma unroll
+  for (int p = 0; p < KT1; ++p) va[p] = p * 32 + i < k1 ? (unsigned)(kh * k1 + p * 32 + i) * 4u : kOut;
+#pragma unroll
+  for (int q = 0; q < KT2; ++q) vb[q] = q * 32 + i < k2 ? (unsigned)(4 * kh * k2 + q * 32 + i) * 4u : kOut;
   for (int task = wave; task < T2 * S1; task += WAVES) {
     const int t = task % T2, s = task / T2;
-    const int x2 = t * 32 + i;
+    const unsigned vx = (unsigned)(kh * n2 + t * 32 + i) * 4u;
     f32x16 W[NH][KT1];
 #pragma unroll
     for (int h = 0; h < NH; ++h)
@@ -264,33 +259,29 @@ __global__ __launch_bounds__(64 * WAVES) void k_reduce(PlaneReduceArgs a) {
       for (int p = 0; p < KT1; ++p) zero16(W[h][p]);
 #pragma unroll
     for (int jc = 0; jc < JA; jc += JC) {
-      float xa[JC];
+      float xa[JC][In::kRaw], pb[KT1][JC];
 #pragma unroll
       for (int j = 0; j < JC; ++j) {
-        const int x1 = s * CH + kh * JA + jc + j;
-        xa[j] = src(f, pbase + (unsigned)(x1 * n2 + x2));
+        const int x1 = s * CH + 2 * (jc + j);
+        src.fetch(f, vx, pbase + (unsigned)(x1 * n2), xa[j]);
+#pragma unroll
+        for (int p = 0; p < KT1; ++p) pb[p][j] = bload_at(rp1, va[p], x1 * k1);
       }
+      if constexpr (KT1 * KT2 * In::kRaw > 1) __builtin_amdgcn_sched_barrier(0);
+      const int h = (jc / JC) % NH;
 #pragma unroll
-      for (int p = 0; p < KT1; ++p) {
-        const int a1 = p * 32 + i;
-        float pb[JC];
+      for (int j = 0; j < JC; ++j) {
+        const float x = In::combine(xa[j]);
 #pragma unroll
-        for (int j = 0; j < JC; ++j) {
-          const int x1 = s * CH + kh * JA + jc + j;
-          pb[j] = bload_if(rp1, (unsigned)(x1 * k1 + a1), a1 < k1);
-        }
-        const int h = (jc / JC) % NH;
-#pragma unroll
-        for (int j = 0; j < JC; ++j) W[h][p] = mfma(xa[j], pb[j], W[h][p]);
+        for (int p = 0; p < KT1; ++p) W[h][p] = mfma(x, pb[p][j], W[h][p]);
       }
     }
     // stage B: k-step r contracts x2 = t 32 + acc_row(r)
 #pragma unroll
     for (int q = 0; q < KT2; ++q) {
-      const int a2 = q * 32 + i;
       float pc[16];
 #pragma unroll
-      for (int r = 0; r < 16; ++r) pc[r] = bload_if(rp2, (unsigned)((t * 32 + acc_row(r, lane)) * k2 + a2), a2 < k2);
+      for (int r = 0; r < 16; ++r) pc[r] = bload_at(rp2, vb[q], (t * 32 + acc_row(r, 0)) * k2);
 #pragma unroll
       for (int p = 0; p < KT1; ++p)
 #pragma unroll
@@ -507,121 +498,93 @@ __global__ __launch_bounds__(512, 4) void k_reduce_r2(PlaneReduceArgs a, int chu
 // and with P2 over its columns; the tiles' partials are summed in LDS in wave order.  The expanded
 // field never goes to memory.  Ragged tiles need no test, as in the separate kernels: grid entries past
 // n1 / n2 are finite and meet rows of P1t / P2t past their ends, which read as zeros.
-template <int MODE, int KT1, int KT2, int JB, bool EXACT>
+template <int MODE>
 __global__ __launch_bounds__(512) void k_prod_plane(ProdPlaneArgs a) {
-  extern __shared__ float red[];  // [ceil(waves / 2)][KT1 KT2][16][64]
+  extern __shared__ float red[];  // [ceil(waves / 2)][16][64]
   constexpr int NE = MODE == kRedV1Products ? 1 : 3;
   const int lane = threadIdx.x & 63, i = lane & 31, kh = lane >> 5;
   const int wave = uniform(threadIdx.x >> 6), nw = blockDim.x >> 6;
-  const int n1 = a.n1, n2 = a.n2, k1 = a.k1, k2 = a.k2, J1 = EXACT ? JB : k1 >> 1;
+  const int n1 = a.n1, n2 = a.n2, k1 = a.k1, k2 = a.k2;
   const int T2 = (n2 + 31) >> 5;
   const int f = blockIdx.x / a.n0, x0 = blockIdx.x - f * a.n0;
   const int s = wave / T2, t = wave - s * T2;
-  const int x1 = s * 32 + i, x2 = t * 32 + i;
-  const unsigned P = (unsigned)a.P, pbase = (unsigned)(x0 * n1 * n2);
+  const unsigned P = (unsigned)a.P;
   const Rsrc r1 = rsrc(a.w1t, (int64_t)k1 * n1), r2 = rsrc(a.w2t, (int64_t)k2 * n2);
   const Rsrc rp1 = rsrc(a.p1t, (int64_t)n1 * k1), rp2 = rsrc(a.p2t, (int64_t)n2 * k2);
   const Rsrc rdiv = rsrc(a.divv, a.P), rG = rsrc(a.G, (int64_t)(MODE == kRedV1Products ? 3 : 9) * a.P);
-  // node offsets of this lane's accumulator rows
-  unsigned pr[16];
-#pragma unroll
-  for (int r = 0; r < 16; ++r) pr[r] = pbase + (unsigned)((s * 32 + acc_row(r, lane)) * n2 + x2);
   // the e components this output reads: V1 e; V3 f < 3 e_f, f >= 3 all three
   const int c0 = (MODE == kRedV3Products && f < 3) ? f : 0;
   const int ne = (MODE == kRedV3Products && f >= 3) ? 3 : 1;
-  // node-field factors of each e component at this lane's nodes (requested before the expansion)
-  float gf[NE][16];
+  // every operand is requested before the first product, in the order of use
+  float ta[NE][16], w1[16], w2[16], gf[NE][16], p1[16], p2[16];
+  const unsigned vt = (unsigned)(kh * k2 + i) * 4u, v1 = (unsigned)(kh * n1 + s * 32 + i) * 4u;
+  const unsigned vg = (unsigned)(4 * kh * n2 + t * 32 + i) * 4u;  // (a row of W2t too)
+  const unsigned vp1 = i < k1 ? (unsigned)(4 * kh * k1 + i) * 4u : kOut, vp2 = i < k2 ? (unsigned)(4 * kh * k2 + i) * 4u : kOut;
 #pragma unroll
-  for (int c = 0; c < NE; ++c)
+  for (int c = 0; c < NE; ++c) {
+    const int cc = c < ne ? c0 + c : c0;
+    const Rsrc rT = rsrc(a.T[cc] + x0 * (k1 * k2), (int64_t)(a.n0 - x0) * k1 * k2);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      unsigned q;
-      if constexpr (MODE == kRedV1Products) q = f == 0 ? kOut : (unsigned)(f - 1) * P + pr[r];
-      else q = f < 3 ? kOut : (unsigned)(3 * c + f - 3) * P + pr[r];
-      gf[c][r] = c < ne ? (q == kOut ? bload(rdiv, pr[r]) : bload(rG, q)) : 0.f;
+    for (int j = 0; j < 16; ++j) ta[c][j] = c < ne ? bload_at(rT, vt, 2 * j * k2) : 0.f;
+    if (c == 0) {
+#pragma unroll
+      for (int j = 0; j < 16; ++j) w1[j] = bload_at(r1, v1, 2 * j * n1);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) w2[r] = bload_at(r2, vg, acc_row(r, 0) * n2);
     }
+    // the node field that multiplies e component c: div v, G_{f-1} (V1) or div v, G_{3 c + f - 3} (V3)
+    const bool dv = MODE == kRedV1Products ? f == 0 : f < 3;
+    const unsigned g = (unsigned)(x0 * n1 * n2) + (dv ? 0u : (unsigned)(MODE == kRedV1Products ? f - 1 : 3 * c + f - 3) * P);
+    const Rsrc rg = dv ? rdiv : rG;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) gf[c][r] = c < ne ? bload_at(rg, vg, g + (unsigned)((s * 32 + acc_row(r, 0)) * n2)) : 0.f;
+  }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) p1[r] = bload_at(rp1, vp1, (s * 32 + acc_row(r, 0)) * k1);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) p2[r] = bload_at(rp2, vp2, (t * 32 + acc_row(r, 0)) * k2);
+  __builtin_amdgcn_sched_barrier(0);
   f32x16 Y;
   zero16(Y);
 #pragma unroll
   for (int c = 0; c < NE; ++c) {
     if (c >= ne) break;
-    const Rsrc rT = rsrc(a.T[c0 + c] + x0 * (k1 * k2), (int64_t)(a.n0 - x0) * k1 * k2);
-    // V[a2][x1] = sum_a1 T[a1][a2] W1t[a1][x1]
-    f32x16 V[KT2];
-#pragma unroll
-    for (int q = 0; q < KT2; ++q) {
-      zero16(V[q]);
-      const int a2 = q * 32 + i;
-#pragma unroll
-      for (int j = 0; j < JB; ++j) {
-        const bool ok = EXACT || j < J1;
-        const float ta = bload_if(rT, (unsigned)((kh * J1 + j) * k2 + a2), ok);
-        const float wb = bload_if(r1, (unsigned)((kh * J1 + j) * n1 + x1), ok);
-        V[q] = mfma(ta, wb, V[q]);
-      }
-    }
-    // D[x1][x2] = sum_a2 V[a2][x1] W2t[a2][x2]
-    f32x16 D;
+    f32x16 V, D;
+    zero16(V);
     zero16(D);
+    // V[a2][x1] = sum_a1 T[a1][a2] W1t[a1][x1], D[x1][x2] = sum_a2 V[a2][x1] W2t[a2][x2]
 #pragma unroll
-    for (int q = 0; q < KT2; ++q)
+    for (int j = 0; j < 16; ++j) V = mfma(ta[c][j], w1[j], V);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) D = mfma(V[q][r], bload(r2, (unsigned)((q * 32 + acc_row(r, lane)) * n2 + x2)), D);
+    for (int r = 0; r < 16; ++r) D = mfma(V[r], w2[r], D);
 #pragma unroll
     for (int r = 0; r < 16; ++r) Y[r] += D[r] * gf[c][r];
   }
-  // W[x2][a1] = sum_x1 Y[x1][x2] P1t[x1][a1] over the tile's rows
-  f32x16 W[KT1];
+  // W[x2][a1] = sum_x1 Y[x1][x2] P1t[x1][a1] over the tile's rows, R[a1][a2] = sum_x2 W[x2][a1] P2t[x2][a2] over
+  // its columns
+  f32x16 W, R;
+  zero16(W);
+  zero16(R);
 #pragma unroll
-  for (int p = 0; p < KT1; ++p) {
-    zero16(W[p]);
-    const int a1 = p * 32 + i;
+  for (int r = 0; r < 16; ++r) W = mfma(Y[r], p1[r], W);
 #pragma unroll
-    for (int r = 0; r < 16; ++r)
-      W[p] = mfma(Y[r], bload_if(rp1, (unsigned)((s * 32 + acc_row(r, lane)) * k1 + a1), a1 < k1), W[p]);
-  }
-  // R[a1][a2] = sum_x2 W[x2][a1] P2t[x2][a2] over the tile's columns
-  f32x16 R[KT1][KT2];
-#pragma unroll
-  for (int q = 0; q < KT2; ++q) {
-    const int a2 = q * 32 + i;
-    float pc[16];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) pc[r] = bload_if(rp2, (unsigned)((t * 32 + acc_row(r, lane)) * k2 + a2), a2 < k2);
-#pragma unroll
-    for (int p = 0; p < KT1; ++p) {
-      zero16(R[p][q]);
-#pragma unroll
-      for (int r = 0; r < 16; ++r) R[p][q] = mfma(W[p][r], pc[r], R[p][q]);
-    }
-  }
+  for (int r = 0; r < 16; ++r) R = mfma(W[r], p2[r], R);
   // partials summed in LDS in a fixed order: waves w < ns store theirs in slot w, then waves w >= ns add
   // theirs to slot w - ns, then the slots are summed in order (ns = ceil(nw / 2) slots of LDS)
-  constexpr int TILES = KT1 * KT2;
   const int ns = (nw + 1) >> 1;
   for (int half = 0; half < 2; ++half) {
-    const bool mine = half == 0 ? wave < ns : wave >= ns;
-    if (mine) {
-      const int slot = half == 0 ? wave : wave - ns;
+    if (half == 0 ? wave < ns : wave >= ns) {
+      float* d = red + (half == 0 ? wave : wave - ns) * 1024 + lane;
 #pragma unroll
-      for (int p = 0; p < KT1; ++p)
-#pragma unroll
-        for (int q = 0; q < KT2; ++q)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            float& d = red[((slot * TILES + p * KT2 + q) * 16 + r) * 64 + lane];
-            d = half == 0 ? R[p][q][r] : d + R[p][q][r];
-          }
+      for (int r = 0; r < 16; ++r) d[r * 64] = half == 0 ? R[r] : d[r * 64] + R[r];
     }
     __syncthreads();
   }
   float* __restrict__ part = a.part + (size_t)blockIdx.x * (k1 * k2);
-  for (int e = threadIdx.x; e < TILES * 16 * 64; e += blockDim.x) {
-    const int l = e & 63, r = (e >> 6) & 15, tile = e >> 10;
-    const int p = tile / KT2, q = tile - p * KT2;
+  for (int e = threadIdx.x; e < 1024; e += blockDim.x) {
+    const int l = e & 63, a1 = acc_row(e >> 6, l), a2 = l & 31;
     float sum = 0.f;
-    for (int w = 0; w < ns; ++w) sum += red[(w * TILES * 16) * 64 + e];
-    const int a1 = p * 32 + acc_row(r, l), a2 = q * 32 + (l & 31);
+    for (int w = 0; w < ns; ++w) sum += red[w * 1024 + e];
     if (a1 < k1 && a2 < k2) part[a1 * k2 + a2] = sum;
   }
 }
@@ -634,8 +597,8 @@ __global__ __launch_bounds__(512) void k_prod_plane(ProdPlaneArgs a) {
 // and tile of 32 rows x0'.  A launch is a few dozen workgroups and waits for memory twice, so what bounds it is
 // latency and the fetch of its code: every operand that does not depend on F is requested at the start, each
 // element of a band array by one thread (the sources of P meet in LDS), loads and stores of a lane share one offset
-// register, and rows past the end of an operand read as zeros.  128^3 with 32^3 coefficients: AX_A us with one
-// field and two outputs, AX_B with four fields.
+// register, and rows past the end of an operand read as zeros.  128^3 with 32^3 coefficients: 7.6 -> 5.2 us
+// with one field, 8.3 -> 5.8 with four (from 14 KB of code at 32-bit offsets per load and four waves).
 template <int KT0, int JB>
 __global__ __launch_bounds__(512) void k_axis0(Axis0Kernel a) {
   __shared__ float red[8 * KT0 * 1024];
@@ -777,12 +740,12 @@ bool planes_ok(const Dims& d) {
          d.k[2] % 2 == 0 && d.P < (int64_t(1) << 31) && (int64_t)d.n[0] * d.k[1] * d.k[2] < (int64_t(1) << 31);
 }
 
-// half planes on even inner axes where a band reaches beyond `above`
+// half planes on even inner axes where a band reaches beyond `above`: the expansion from 18 slots on (128^3, 32^3,
+// two fields 9.8 -> 7.6 us, six 21.8 -> 16.3), the reduction above 32 (its tile's columns are a parity's slots, half
+// of them empty at 32: 6.8 -> 11.1)
 static bool half_planes(int n1, int n2, int k1, int k2, int above) {
   return (k1 > above || k2 > above) && k1 <= 64 && k2 <= 64 && k1 % 2 == 0 && k2 % 2 == 0 && n1 % 2 == 0 && n2 % 2 == 0;
 }
-
-static int jb_of(int j) { return j <= 8 ? 8 : j <= 16 ? 16 : j <= 24 ? 24 : 32; }
 
 void plane_expand(const PlaneExpandArgs& a, hipStream_t s) {
   const int B1 = ceil_div(a.n1, 32);
@@ -790,7 +753,6 @@ void plane_expand(const PlaneExpandArgs& a, hipStream_t s) {
   const double bytes = 4.0 * a.nf * ((double)a.n0 * a.k1 * a.k2 + (double)a.n0 * a.n1 * a.n2);
   const double flops = 2.0 * a.nf * a.n0 * ((double)a.k1 * a.k2 * a.n1 + (double)a.n1 * a.k2 * a.n2);
   dim3 g(B1, a.n0, a.nf);
-  const int j1 = a.k1 / 2, jb = jb_of(j1);
   if (half_planes(a.n1, a.n2, a.k1, a.k2, 16)) {
     const dim3 gh(ceil_div(a.n1 / 2, 32), a.n0, a.nf);
     const int waves = std::min(a.k2 <= 48 ? 8 : 4, std::max(4, 2 * ceil_div(a.n2 / 2, 32)));
@@ -805,15 +767,9 @@ void plane_expand(const PlaneExpandArgs& a, hipStream_t s) {
   }
   auto go = [&](auto kern) { prof::launch("k_expand", bytes, flops, kern, g, dim3(256), 0, s, a); };
   if (a.k2 <= 32) {
-    if (j1 == 16) go(k_expand<16, 1, true>); else if (j1 == 20) go(k_expand<20, 1, true>);
-    else if (j1 == 24) go(k_expand<24, 1, true>); else if (j1 == 32) go(k_expand<32, 1, true>);
-    else if (jb == 8) go(k_expand<8, 1, false>); else if (jb == 16) go(k_expand<16, 1, false>);
-    else if (jb == 24) go(k_expand<24, 1, false>); else go(k_expand<32, 1, false>);
+    if (a.k1 <= 16) go(k_expand<8, 1>); else if (a.k1 <= 32) go(k_expand<16, 1>); else go(k_expand<32, 1>);
   } else {
-    if (j1 == 16) go(k_expand<16, 2, true>); else if (j1 == 20) go(k_expand<20, 2, true>);
-    else if (j1 == 24) go(k_expand<24, 2, true>); else if (j1 == 32) go(k_expand<32, 2, true>);
-    else if (jb == 8) go(k_expand<8, 2, false>); else if (jb == 16) go(k_expand<16, 2, false>);
-    else if (jb == 24) go(k_expand<24, 2, false>); else go(k_expand<32, 2, false>);
+    if (a.k1 <= 16) go(k_expand<8, 2>); else if (a.k1 <= 32) go(k_expand<16, 2>); else go(k_expand<32, 2>);
   }
   LDDMM_LAUNCH_CHECK();
 }
@@ -897,14 +853,10 @@ void plane_prod(const ProdPlaneArgs& a, hipStream_t s) {
   dim3 g(static_cast<unsigned>(nf * a.n0));
   const dim3 b(64 * tiles);
   const size_t lds = prod_plane_lds(tiles, kt1 * kt2);
-  const int j1 = a.k1 / 2;
-  const bool ex = j1 == 16 || j1 == 20 || j1 == 24 || j1 == 32;
-  const int jb = ex ? j1 : jb_of(j1);
   auto go = [&](auto kern) { prof::launch("k_prod_plane", bytes, flops, kern, g, b, lds, s, a); };
   auto pick = [&](auto mode) {
     constexpr int M = decltype(mode)::value;
-    if (ex && jb == 16) go(k_prod_plane<M, 1, 1, 16, true>);
-    else go(k_prod_plane<M, 1, 1, 16, false>);
+    go(k_prod_plane<M>);
   };
   if (a.mode == kRedV1Products) pick(std::integral_constant<int, kRedV1Products>{});
   else if (a.mode == kRedV3Products) pick(std::integral_constant<int, kRedV3Products>{});
