@@ -116,6 +116,18 @@ __global__ __launch_bounds__(256) void k_expand(PlaneExpandArgs a) {
       for (int r = 0; r < 16; ++r) wc[q][r] = bload_at(r2, v, (q * 32 + acc_row(r, 0)) * n2);
   };
   load_wc(wave);
+  if (a.y[f]) {
+    const Rsrc ry = rsrc(a.y[f] + x0 * (k1 * k2), (int64_t)(a.n0 - x0) * k1 * k2);
+    float ty[KT2][JW];
+#pragma unroll
+    for (int q = 0; q < KT2; ++q)
+#pragma unroll
+      for (int u = 0; u < JW; ++u) ty[q][u] = bload_at(ry, vt, (j0 + 2 * u) * k2 + 32 * q);
+#pragma unroll
+    for (int q = 0; q < KT2; ++q)
+#pragma unroll
+      for (int u = 0; u < JW; ++u) ta[q][u] += a.alpha[f] * ty[q][u];
+  }
   __builtin_amdgcn_sched_barrier(0);
   f32x16 V[KT2];
 #pragma unroll
@@ -215,6 +227,17 @@ struct RedIn {
   }
 };
 
+// Finished element e of a plane's band block (field f, plane x0): to the partials, or combined into the output
+__device__ __forceinline__ void reduce_store(const PlaneReduceArgs& a, int f, int x0, int e, float r) {
+  const int n = a.k1 * a.k2;
+  if (a.combine) {  // (at most kMaxFields fields, see plane_reduce; the node sources have more)
+    float* out = a.out[f] + (size_t)x0 * n + e;
+    *out = a.beta[f] == 0.f ? a.alpha[f] * r : a.beta[f] * *out + a.alpha[f] * r;  // beta 0 never reads out
+  } else {
+    a.part[(size_t)(f * a.n0 + x0) * n + e] = r;
+  }
+}
+
 // One workgroup per (field, plane x0); its waves take the tasks (x2 tile t of 32 columns, x1 chunk s of
 // 64 rows) of the plane.  Stage A: W[x2][a1] = sum_x1 in[x1][x2] P1t[x1][a1] over the chunk (the field
 // read along x2; chunks of JC k-steps alternate between two accumulators, shorter rounding chains);
@@ -307,7 +330,6 @@ __global__ __launch_bounds__(64 * WAVES) void k_reduce(PlaneReduceArgs a) {
     }
     __syncthreads();
   }
-  float* __restrict__ part = a.part + (size_t)plane * (k1 * k2);
   for (int e = threadIdx.x; e < TILES * 16 * 64; e += 64 * WAVES) {
     const int l = e & 63, r = (e >> 6) & 15, tile = e >> 10;
     const int p = tile / KT2, q = tile - p * KT2;
@@ -315,7 +337,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_reduce(PlaneReduceArgs a) {
 #pragma unroll
     for (int w = 0; w < NS; ++w) sum += red[(w * TILES * 16) * 64 + e];
     const int a1 = p * 32 + acc_row(r, l), a2 = q * 32 + (l & 31);
-    if (a1 < k1 && a2 < k2) part[a1 * k2 + a2] = sum;
+    if (a1 < k1 && a2 < k2) reduce_store(a, f, x0, a1 * k2 + a2, sum);
   }
 }
 
@@ -362,6 +384,14 @@ __global__ __launch_bounds__(B2 <= 12 ? 512 : 256, B2 <= 12 ? 4 : 3) void k_expa
     for (int j = 0; j < B1; ++j) {
       ta[j] = bload_at(rT, vt, 4 * j * k2);
       wb[j] = bload_at(r1, vw, 4 * j * n1);
+    }
+    if (a.y[f]) {
+      const Rsrc ry = rsrc(a.y[f] + x0 * (k1 * k2), (int64_t)(a.n0 - x0) * k1 * k2);
+      float ty[B1];
+#pragma unroll
+      for (int j = 0; j < B1; ++j) ty[j] = bload_at(ry, vt, 4 * j * k2);
+#pragma unroll
+      for (int j = 0; j < B1; ++j) ta[j] += a.alpha[f] * ty[j];
     }
     load_wc(wave >> 1);
     f32x16 V;
@@ -476,13 +506,12 @@ __global__ __launch_bounds__(512, 4) void k_reduce_r2(PlaneReduceArgs a, int chu
     for (int r = 0; r < 16; ++r) red[((wave * 2 + q) * 16 + r) * 64 + lane] = R[q][r];
   __syncthreads();
   // the sum over the waves of a parity, in order
-  float* __restrict__ part = a.part + (size_t)blockIdx.x * (k1 * k2);
   for (int e = threadIdx.x; e < 4096; e += blockDim.x) {
     const int l = e & 63, r = (e >> 6) & 15, pp = e >> 11;
     float sum = red[e];
     for (int w = 2; w < nw; w += 2) sum += red[(w + pp) * 2048 + (e & 2047)];
     const int s1 = half_slot(acc_row(r, l), pp), s2 = half_slot(l & 31, (e >> 10) & 1);
-    if (s1 < k1 && s2 < k2) part[s1 * k2 + s2] = sum;
+    if (s1 < k1 && s2 < k2) reduce_store(a, f, x0, s1 * k2 + s2, sum);
   }
 }
 
@@ -815,6 +844,7 @@ void plane_reduce(const PlaneReduceArgs& a, hipStream_t s) {
   const double flops = 2.0 * a.nf * a.n0 * ((double)a.n1 * a.n2 * a.k1 + (double)a.k1 * a.n2 * a.k2);
   const double bytes = 4.0 * a.nf * a.n0 * ((double)a.n1 * a.n2 + (double)a.k1 * a.k2);
   if (a.P >= (int64_t(1) << 31)) throw ArgError("plane_reduce: field too large");
+  if (a.combine && a.nf > kMaxFields) throw ArgError("plane_reduce: too many fields to combine");
   switch (a.mode) {
     case kRedPlain: return reduce_mode<kRedPlain>(a, s, bytes, flops);
     case kRedV1Products: return reduce_mode<kRedV1Products>(a, s, bytes, flops);

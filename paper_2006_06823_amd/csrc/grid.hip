@@ -7,7 +7,6 @@
 // [c][n0][n1][n2], n2 contiguous, so neighbouring lanes touch neighbouring nodes.
 #include "kernels.h"
 #include "prof.h"
-#include "stage.h"
 
 #include <type_traits>
 

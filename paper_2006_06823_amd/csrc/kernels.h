@@ -3,6 +3,8 @@
 
 #include "common.h"
 
+#include <vector>
+
 namespace lddmm {
 
 // ---- separable truncated DFT contractions (dft.hip) -------------------------
@@ -12,38 +14,18 @@ void dft_left(const float* in, float* out, const FieldMats<float>& W, int nb, in
               int64_t sIb, int64_t sOb, hipStream_t s);
 void dft_right(const float* in, float* out, const FieldMats<float>& W, int nf, int R, int L, int Mo, hipStream_t s);
 
-// bf16 hi/lo split variants (float in/out, bf16 matrix-core products, float accumulation)
-void dft_left_bf16(const float* in, float* out, const FieldMats<float>& W, int nb, int bpf, int M, int L,
-                   int C, int64_t sIb, int64_t sOb, hipStream_t s);
-void dft_right_bf16(const float* in, float* out, const FieldMats<float>& W, int nf, int R, int L, int Mo,
-                    hipStream_t s);
-
-// fused inner-axis stages (dft_fused.hip), float
-struct IotaABArgs {
-  const float* x[kMaxFields];  // per-field band input [k0][k1][k2]
-  const float* y[kMaxFields];  // optional second input (null: none); slab = x + alpha y
-  float alpha[kMaxFields];
-  const float* w1t[kMaxFields];  // axis-1 matrix transposed, [k1][n1]
-  const float* w2t[kMaxFields];  // axis-2 matrix transposed, [k2][n2]
-  float* out;                   // [nf][k0][n1][n2]
-  int k0, k1, k2, n1, n2;
+// first-axis products with bf16 hi/lo splits (float in/out, bf16 matrix-core products, float accumulation):
+// out[b][m][c] = sum_l W_b[m][l] in[b][l][c], W_b split by split_matrix (hi at w, lo at w + lo)
+struct SplitMats {
+  const unsigned short* w[kMaxFields];
+  int64_t lo;
 };
-struct PiBAArgs {
-  const float* in;  // [nf][k0][n1][n2]
-  const float* p1t;  // axis-1 projection transposed, [n1][k1]
-  const float* p2t;  // axis-2 projection transposed, [n2][k2]
-  float* out[kMaxFields];  // per-field band output [k0][k1][k2]: out = beta out + alpha r
-  float alpha[kMaxFields];
-  float beta[kMaxFields];
-  float* part;  // workspace: [nf][k0][pi_ba_splits(n1)][k1][k2] partial projections
-  int k0, k1, k2, n1, n2;
-};
-bool fused_dft_ok(int n1, int n2, int k1, int k2);
-int pi_ba_splits(int n1);
-void iota_ab(const IotaABArgs& a, int nf, hipStream_t s);
-void pi_ba(const PiBAArgs& a, int nf, hipStream_t s);
+void split_matrix(const float* w, int M, int L, std::vector<unsigned short>& out);
+bool dft_first_bf16_ok(int M, int L, int64_t C);
+void dft_first_bf16(const float* in, float* out, const SplitMats& W, int nb, int M, int L, int C, hipStream_t s);
 
-// the same in double (dft_f64.hip): both inner axes of small planes in one kernel, else one axis each
+// truncated DFT in double (dft_f64.hip): both inner axes of small planes in one kernel (out = iota of x + alpha y;
+// out = beta out + alpha pi), else one axis each
 struct IotaABF64Args {
   const double* x[kMaxFields];
   const double* y[kMaxFields];
@@ -79,6 +61,8 @@ struct PlaneExpandArgs {
   const float* w2t[kMaxFields];  // [k2][n2]
   float* out;                    // [nf][n0][n1][n2]
   int nf, n0, n1, n2, k1, k2;
+  const float* y[kMaxFields];    // optional: T + alpha y is expanded
+  float alpha[kMaxFields];
 };
 // reduction of planes: part[f][x0][a1][a2] = sum_{x1,x2} p1t[x1][a1] v_f(x0, x1, x2) p2t[x2][a2], with the
 // grid value v_f of the mode: a plain field, or a pointwise product of fields of the product grid
@@ -94,6 +78,9 @@ struct PlaneReduceArgs {
   int mode, nf, n0, n1, n2, k1, k2;
   int64_t P;          // grid points per field
   int64_t e_node;     // sources: offset of node n's dv (0: one dv for every node; 3 P: a dv per node)
+  int combine;             // 1: out_f = beta_f out_f + alpha_f r ([n0][k1][k2]) instead of part, nf <= kMaxFields
+  float* out[kMaxFields];
+  float alpha[kMaxFields], beta[kMaxFields];
 };
 // expansion of e~ (T, 1 or 3 components) and reduction of its products with node fields in one pass
 // per plane (product grid): part[f][x0] as PlaneReduceArgs in the modes kRedV1Products / kRedV3Products

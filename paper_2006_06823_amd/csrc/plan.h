@@ -102,9 +102,6 @@ class Plan {
     stk_.alloc(kMaxFields * d_.Q);
     blC_.alloc(kMaxFields * d_.Q);
     if (std::is_same<T, float>::value) {
-      // partial projections of the split fused projection
-      const int64_t slabs = (int64_t)kMaxFields * d_.k[0];
-      pipart_.alloc(slabs * pi_ba_splits(d_.n[1]) * d_.k[1] * d_.k[2]);
       planes_ = !bf16_ && planes_ok(d_) && std::getenv("LDDMM_BL_NO_PLANES") == nullptr;
       prod_fused_ = planes_ && prod_plane_ok(d_) && std::getenv("LDDMM_BL_NO_PROD_FUSE") == nullptr;
       if (planes_) {
@@ -237,8 +234,7 @@ class Plan {
     for (int f = 0; f < nf; ++f) W.w[f] = mat(1, kinds[f][1]);
     left(t1_.get(), dstB, W, nf * k0, k0, n1, k1, n2, (int64_t)k1 * n2, (int64_t)n1 * n2);
     if (!skip0) {
-      for (int f = 0; f < nf; ++f) W.w[f] = mat(0, kinds[f][0]);
-      left(t2_.get(), out, W, nf, 1, n0, k0, n1 * n2, (int64_t)k0 * n1 * n2, d_.P);
+      include_first(t2_.get(), out, nf, kinds);
     } else {
       zero_degenerate_derivatives(out, nf, kinds);
     }
@@ -262,25 +258,23 @@ class Plan {
         }
         return;
       }
-      if (fused_dft_ok(n1, n2, k1, k2)) {
-        IotaABArgs a{};
+      if (fused_inner()) {
+        // the inner axes of the band slabs a0 as planes, then the first axis
+        PlaneExpandArgs a{};
         for (int f = 0; f < nf; ++f) {
-          a.x[f] = xs[f];
+          a.T[f] = xs[f];
           a.y[f] = ys ? ys[f] : nullptr;
           a.alpha[f] = al ? al[f] : 0.f;
           a.w1t[f] = mat(1, kinds[f][1] + kPlainT);
           a.w2t[f] = mat(2, kinds[f][2] + kPlainT);
         }
         a.out = skip0 ? out : t2_.get();
-        a.k0 = k0, a.k1 = k1, a.k2 = k2, a.n1 = n1, a.n2 = n2;
-        iota_ab(a, nf, s());
-        if (!skip0) {
-          FieldMats<T> W{};
-          for (int f = 0; f < nf; ++f) W.w[f] = mat(0, kinds[f][0]);
-          left(t2_.get(), out, W, nf, 1, n0, k0, n1 * n2, (int64_t)k0 * n1 * n2, d_.P);
-        } else {
+        a.nf = nf, a.n0 = k0, a.n1 = n1, a.n2 = n2, a.k1 = k1, a.k2 = k2;
+        plane_expand(a, s());
+        if (!skip0)
+          include_first(t2_.get(), out, nf, kinds);
+        else
           zero_degenerate_derivatives(out, nf, kinds);
-        }
         return;
       }
     } else if (fused_inner()) {
@@ -296,11 +290,7 @@ class Plan {
       a.out = skip0 ? out : t2_.get();
       a.k0 = k0, a.k1 = k1, a.k2 = k2, a.n1 = n1, a.n2 = n2;
       iota_ab_f64(a, nf, s());
-      if (!skip0) {
-        FieldMats<T> W{};
-        for (int f = 0; f < nf; ++f) W.w[f] = mat(0, kinds[f][0]);
-        left(t2_.get(), out, W, nf, 1, n0, k0, n1 * n2, (int64_t)k0 * n1 * n2, d_.P);
-      }
+      if (!skip0) include_first(t2_.get(), out, nf, kinds);
       return;
     }
     // generic path: stack the combinations, then the separable stages
@@ -351,35 +341,26 @@ class Plan {
         }
         return;
       }
-      if (fused_dft_ok(n1, n2, k1, k2)) {
-        const T* srcB = grid;
+      if (fused_inner()) {
+        PlaneReduceArgs r{};
+        r.in = grid;
         if (!(n0 == 1 && k0 == 1)) {
-          FieldMats<T> W{};
-          for (int f = 0; f < nf; ++f) W.w[f] = mat(0, kProj);
-          left(grid, t1_.get(), W, nf, 1, k0, n0, n1 * n2, d_.P, (int64_t)k0 * n1 * n2);
-          srcB = t1_.get();
+          project_first(grid, t1_.get(), nf);
+          r.in = t1_.get();
         }
-        PiBAArgs b{};
-        b.in = srcB;
-        b.p1t = mat(1, kProjT);
-        b.part = pipart_.get();
-        b.p2t = mat(2, kProjT);
-        for (int f = 0; f < nf; ++f) {
-          b.out[f] = dst[f];
-          b.alpha[f] = alpha[f];
-          b.beta[f] = beta[f];
-        }
-        b.k0 = k0, b.k1 = k1, b.k2 = k2, b.n1 = n1, b.n2 = n2;
-        pi_ba(b, nf, s());
+        r.p1t = mat(1, kProjT), r.p2t = mat(2, kProjT);
+        r.combine = 1;
+        for (int f = 0; f < nf; ++f) r.out[f] = dst[f], r.alpha[f] = alpha[f], r.beta[f] = beta[f];
+        r.mode = kRedPlain, r.nf = nf, r.n0 = k0, r.n1 = n1, r.n2 = n2, r.k1 = k1, r.k2 = k2;
+        r.P = (int64_t)k0 * n1 * n2;
+        plane_reduce(r, s());
         return;
       }
     } else if (fused_inner()) {
       PiBAF64Args b{};
       b.in = grid;
       if (!(n0 == 1 && k0 == 1)) {
-        FieldMats<T> W{};
-        for (int f = 0; f < nf; ++f) W.w[f] = mat(0, kProj);
-        left(grid, t1_.get(), W, nf, 1, k0, n0, n1 * n2, d_.P, (int64_t)k0 * n1 * n2);
+        project_first(grid, t1_.get(), nf);
         b.in = t1_.get();
       }
       b.p1t = mat(1, kProjT);
@@ -438,16 +419,52 @@ class Plan {
     }
     mats_.alloc(total);
     LDDMM_HIP(hipMemcpy(mats_.get(), h.data(), total * sizeof(T), hipMemcpyHostToDevice));
+    if constexpr (std::is_same_v<T, float>) {
+      if (!bf16_) return;
+      std::vector<unsigned short> all, one;
+      for (int m : {kPlain, kPref, kDeriv, kProj}) {
+        const int rows = m == kProj ? d_.k[0] : d_.n[0], cols = m == kProj ? d_.n[0] : d_.k[0];
+        split_matrix(h.data() + mat_off_[0][m], rows, cols, one);
+        split_off_[m] = static_cast<int64_t>(all.size());
+        split_lo_[m] = static_cast<int64_t>(one.size() / 2);
+        all.insert(all.end(), one.begin(), one.end());
+      }
+      split_.alloc(static_cast<int64_t>(all.size()));
+      LDDMM_HIP(hipMemcpy(split_.get(), all.data(), all.size() * sizeof(all[0]), hipMemcpyHostToDevice));
+    }
   }
   // axis contraction for the first-axis stages: float or split-bf16 matrix cores
   void left(const T* in, T* out, const FieldMats<T>& W, int nb, int bpf, int M, int L, int C, int64_t sIb,
             int64_t sOb) {
-    if constexpr (std::is_same_v<T, float>) {
-      if (bf16_) return dft_left_bf16(in, out, W, nb, bpf, M, L, C, sIb, sOb, s());
+    if constexpr (std::is_same_v<T, float>)
       dft_left(in, out, W, nb, bpf, M, L, C, sIb, sOb, s());
-    } else {
+    else
       axis_f64(in, out, W, nb, bpf, M, L, C, sIb, sOb, false, s());
+  }
+  // the first axis of nf fields: [k0][n1 n2] -> [n0][n1 n2] with the given kinds, and its projection
+  void include_first(const T* in, T* out, int nf, const int kinds[][3]) {
+    int m[kMaxFields];
+    for (int f = 0; f < nf; ++f) m[f] = kinds[f][0];
+    first(in, out, nf, m, d_.n[0], d_.k[0]);
+  }
+  void project_first(const T* in, T* out, int nf) {
+    int m[kMaxFields];
+    for (int f = 0; f < nf; ++f) m[f] = kProj;
+    first(in, out, nf, m, d_.k[0], d_.n[0]);
+  }
+  void first(const T* in, T* out, int nf, const int* kind, int M, int L) {
+    const int C = d_.n[1] * d_.n[2];
+    if constexpr (std::is_same_v<T, float>) {
+      if (bf16_ && dft_first_bf16_ok(M, L, C)) {
+        SplitMats w{};
+        for (int f = 0; f < nf; ++f) w.w[f] = split_.get() + split_off_[kind[f]];
+        w.lo = split_lo_[kind[0]];  // (the kinds of one direction have one shape)
+        return dft_first_bf16(in, out, w, nf, M, L, C, s());
+      }
     }
+    FieldMats<T> W{};
+    for (int f = 0; f < nf; ++f) W.w[f] = mat(0, kind[f]);
+    left(in, out, W, nf, 1, M, L, C, (int64_t)L * C, (int64_t)M * C);
   }
   void right(const T* in, T* out, const FieldMats<T>& W, int nf, int R, int L, int Mo) {
     if constexpr (std::is_same_v<T, float>)
@@ -458,7 +475,8 @@ class Plan {
   // both inner axes of a transform run in one kernel (or plane by plane)
   bool fused_inner() const {
     if constexpr (std::is_same_v<T, float>)
-      return planes_ || fused_dft_ok(d_.n[1], d_.n[2], d_.k[1], d_.k[2]);
+      return planes_ || (d_.k[1] <= 64 && d_.k[2] <= 64 &&  // (32-bit byte offsets within the stacked slabs)
+                         (int64_t)kMaxFields * d_.k[0] * d_.n[1] * d_.n[2] < (int64_t(1) << 29));
     else
       return fused_f64_ok(d_.n[1], d_.n[2], d_.k[1], d_.k[2]);
   }
@@ -474,8 +492,7 @@ class Plan {
     FieldMats<T> W{};
     const T* srcB = grid;
     if (!(n0 == 1 && k0 == 1)) {
-      for (int f = 0; f < nf; ++f) W.w[f] = mat(0, kProj);
-      left(grid, t1_.get(), W, nf, 1, k0, n0, n1 * n2, d_.P, (int64_t)k0 * n1 * n2);
+      project_first(grid, t1_.get(), nf);
       srcB = t1_.get();
     }
     for (int f = 0; f < nf; ++f) W.w[f] = mat(1, kProj);
@@ -489,7 +506,9 @@ class Plan {
   const hipStream_t* st_ = nullptr;
   int64_t mat_off_[3][kNumMats] = {};
   DevBuf<T> mats_, t1_, t2_, stk_, blC_;
-  DevBuf<float> pipart_, Tp_, part_;
+  DevBuf<float> Tp_, part_;
+  DevBuf<unsigned short> split_;  // hi and lo parts of the first axis' matrices (kind m at split_off_[m])
+  int64_t split_off_[kNumMats] = {}, split_lo_[kNumMats] = {};
 };
 
 }  // namespace lddmm
