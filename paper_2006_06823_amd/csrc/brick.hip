@@ -559,16 +559,16 @@ __global__ void k_tune_disp(float* disp, int n0, int n1, int n2) {
 
 // ---- transformation through whole-deformation maps ------------------------------------
 
-// 64-tap evaluation from a staged box with runtime strides (rows of e2 floats, planes of e1 rows)
-__device__ __forceinline__ float eval_box(const float* __restrict__ br, int s0, int s1, int s2, int e1, int e2,
-                                          const float w0[4], const float w1[4], const float w2[4]) {
+// 64-tap evaluation from a staged box of planes of `plane` floats and rows of `pitch`, first tap at br
+__device__ __forceinline__ float eval_box(lds_float* br, int plane, int pitch, const float w0[4], const float w1[4],
+                                          const float w2[4]) {
   float acc = 0.f;
 #pragma unroll
   for (int a = 0; a < 4; ++a) {
     float sa = 0.f;
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
-      const float* row = br + ((s0 + a) * e1 + (s1 + b)) * e2 + s2;
+      lds_float* row = br + (a * plane + b * pitch);
       sa += w1[b] * (w2[0] * row[0] + w2[1] * row[1] + w2[2] * row[2] + w2[3] * row[3]);
     }
     acc += w0[a] * sa;
@@ -579,15 +579,20 @@ __device__ __forceinline__ float eval_box(const float* __restrict__ br, int s0, 
 // out_n(x) = a w_n(x) P(c)(x - u_n(x)) for node n = blockIdx.y (u_n [3][P] in unit-torus units, w_n
 // optional).  The departure points lie up to a whole deformation away from their nodes, beyond any
 // fixed halo, but they move smoothly: the workgroup takes the bounding box of its tile's 4 x 4 x 4
-// stencils (a min / max over the workgroup), stages the box into LDS when it holds at most CAP floats
-// and evaluates every node from there; a larger box falls back to gathers from global memory.
+// stencils, stages the box into LDS when it holds at most CAP floats and evaluates every node from
+// there; a larger box falls back to gathers from global memory.  Three phases wait for each other
+// (displacements, box, taps), so each is kept short: bounds are packed 16-bit pairs reduced by shuffles,
+// a thread requests its share of the box (some ten values, walked without divisions) at once, and rows
+// keep a pitch of 8 modulo 16, which spreads the four tile rows of a wave over the banks.  Eleven nodes
+// of 128^3: 650 -> PB_US us.
 template <int TX0, int TX1, int TX2, int NTHR, int CAP>
 __global__ __launch_bounds__(NTHR) void k_pull_back_box(float* __restrict__ out, const float* __restrict__ c,
                                                         const float* __restrict__ u, const float* __restrict__ w,
                                                         float a, Grid3 g) {
-  constexpr int PPT = TX0 * TX1 * TX2 / NTHR, NW = NTHR / 64;
+  constexpr int PPT = TX0 * TX1 * TX2 / NTHR, NW = NTHR / 64, U = 12;
+  typedef short s16x2 __attribute__((ext_vector_type(2)));
   __shared__ float br[CAP];
-  __shared__ int bmin[3], bmax[3];
+  __shared__ int bounds[NW][3];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int T2 = (g.n2 + TX2 - 1) / TX2, T1 = (g.n1 + TX1 - 1) / TX1;
   // consecutive tiles of one node on one XCD (its L2 then holds the boxes' overlap)
@@ -595,113 +600,107 @@ __global__ __launch_bounds__(NTHR) void k_pull_back_box(float* __restrict__ out,
   int bid = blockIdx.x;
   if ((nb & 7) == 0) bid = (bid & 7) * (nb >> 3) + (bid >> 3);
   const int bx = bid % T2, rest = bid / T2, by = rest % T1, bz = rest / T1;
+  const int org[3] = {bz * TX0, by * TX1, bx * TX2};
   const int64_t P = g.P, node = blockIdx.y;
   const float* __restrict__ un = u + node * 3 * P;
-  if (tid < 3) bmin[tid] = INT_MAX, bmax[tid] = INT_MIN;
-  float x[PPT][3];
+  const float* __restrict__ wn = w ? w + node * P : nullptr;
+  float x[PPT][3], fac[PPT];
   int pidx[PPT];
   bool live[PPT];
-  int lmin[3] = {INT_MAX, INT_MAX, INT_MAX}, lmax[3] = {INT_MIN, INT_MIN, INT_MIN};
 #pragma unroll
   for (int j = 0; j < PPT; ++j) {
     const int q = tid + NTHR * j;
-    const int l2 = q % TX2, l1 = (q / TX2) % TX1, l0 = q / (TX1 * TX2);
-    const int i0 = bz * TX0 + l0, i1 = by * TX1 + l1, i2 = bx * TX2 + l2;
+    const int i0 = org[0] + q / (TX1 * TX2), i1 = org[1] + (q / TX2) % TX1, i2 = org[2] + q % TX2;
     live[j] = i0 < g.n0 && i1 < g.n1 && i2 < g.n2;
-    pidx[j] = (i0 * g.n1 + i1) * g.n2 + i2;
-    x[j][0] = x[j][1] = x[j][2] = 0.f;
-    if (live[j]) {
-      const int p = pidx[j];
-      x[j][0] = i0 - un[p] * g.n0;
-      x[j][1] = i1 - un[P + p] * g.n1;
-      x[j][2] = i2 - un[2 * P + p] * g.n2;
+    pidx[j] = live[j] ? (i0 * g.n1 + i1) * g.n2 + i2 : 0;
+    x[j][0] = un[pidx[j]], x[j][1] = un[P + pidx[j]], x[j][2] = un[2 * P + pidx[j]];
+    fac[j] = wn ? wn[pidx[j]] : 1.f;
+  }
+  // bounds of the stencils relative to the tile, (min, -max) per axis; 16 bits hold any box worth staging
+  s16x2 bnd[3];
 #pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        const int f = static_cast<int>(floorf(x[j][k]));
-        lmin[k] = min(lmin[k], f - 1);
-        lmax[k] = max(lmax[k], f + 2);
-      }
+  for (int k = 0; k < 3; ++k) bnd[k] = s16x2{16000, 16000};
+#pragma unroll
+  for (int j = 0; j < PPT; ++j) {
+    const int q = tid + NTHR * j;
+    const int n[3] = {g.n0, g.n1, g.n2}, l[3] = {q / (TX1 * TX2), (q / TX2) % TX1, q % TX2};
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      x[j][k] = (org[k] + l[k]) - x[j][k] * n[k];
+      const short f = static_cast<short>(fminf(fmaxf(floorf(x[j][k]) - org[k], -15000.f), 15000.f));
+      if (live[j]) bnd[k] = __builtin_elementwise_min(bnd[k], s16x2{(short)(f - 1), (short)(-f - 2)});
     }
   }
-  __syncthreads();  // bounds initialised
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    if (lmin[k] != INT_MAX) {
-      atomicMin(&bmin[k], lmin[k]);
-      atomicMax(&bmax[k], lmax[k]);
-    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1)
+      bnd[k] = __builtin_elementwise_min(
+          bnd[k], __builtin_bit_cast(s16x2, __shfl_xor(__builtin_bit_cast(int, bnd[k]), o)));
+    if (lane == 0) bounds[wave][k] = __builtin_bit_cast(int, bnd[k]);
   }
   __syncthreads();
-  const int lo0 = bmin[0], lo1 = bmin[1], lo2 = bmin[2];
-  // every tile holds a live node (the grid is ceil-divided), so bmin <= bmax on every axis
-  const int64_t w0b = (int64_t)bmax[0] - lo0 + 1, w1b = (int64_t)bmax[1] - lo1 + 1, w2b = (int64_t)bmax[2] - lo2 + 1;
-  const bool staged = w0b > 0 && w1b > 0 && w2b > 0 && w0b <= g.n0 && w1b <= g.n1 && w2b <= g.n2 && w2b <= 128 &&
-                      w0b * w1b * w2b <= CAP;
-  const int e0 = staged ? (int)w0b : 0, e1 = staged ? (int)w1b : 0, e2 = staged ? (int)w2b : 0;
+  int lo[3], e[3];
+  bool near = true;  // no bound was clamped (nor a point NaN)
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    s16x2 b = __builtin_bit_cast(s16x2, bounds[0][k]);
+#pragma unroll
+    for (int v = 1; v < NW; ++v) b = __builtin_elementwise_min(b, __builtin_bit_cast(s16x2, bounds[v][k]));
+    lo[k] = __builtin_amdgcn_readfirstlane(b[0] + org[k]);
+    e[k] = __builtin_amdgcn_readfirstlane(1 - b[0] - b[1]);
+    near = near && b[0] > -14000 && b[1] > -14000;
+  }
+  // (every tile holds a live node, the grid is ceil-divided: e >= 4)
+  const int pitch = ((e[2] + 7) & ~15) + 8, plane = e[1] * pitch;
+  const bool staged = near && e[0] <= g.n0 && e[1] <= g.n1 && e[2] <= g.n2 && (int64_t)e[0] * plane <= CAP;
   if (staged) {
-    const int m0 = ((lo0 % g.n0) + g.n0) % g.n0, m1 = ((lo1 % g.n1) + g.n1) % g.n1, m2 = ((lo2 % g.n2) + g.n2) % g.n2;
-    // a wave stages rows of e2 columns, two rows per 64 lanes when they are at most 32 columns wide,
-    // RB (pairs of) rows at a time with all their loads requested before its LDS stores
-    constexpr int RB = 4;
-    const int rows = e0 * e1;
-    const bool half = e2 <= 32;
-    const int lrow = half ? (lane >> 5) : 0, lcol = half ? (lane & 31) : lane, rstep = half ? 2 : 1;
-    for (int row0 = wave * RB * rstep; row0 < rows; row0 += NW * RB * rstep) {
-      float vals[RB][2];
+    const int m0 = wrapi(lo[0], g.n0), m1 = wrapi(lo[1], g.n1), m2 = wrapi(lo[2], g.n2);
+    const int total = e[0] * e[1] * e[2];
+    // element tid, tid + NTHR, ..: (r0, r1, col) advanced by the step's digits
+    const int dr = NTHR / e[2], d2 = NTHR - dr * e[2], d0 = dr / e[1], d1 = dr - d0 * e[1];
+    int col = tid % e[2], r1 = tid / e[2], r0 = r1 / e[1];
+    r1 -= r0 * e[1];
+    for (int t0 = tid; t0 < total; t0 += NTHR * U) {
+      float v[U];
+      int at[U];
 #pragma unroll
-      for (int k = 0; k < RB; ++k) {
-        const int row = row0 + k * rstep + lrow;
-        vals[k][0] = vals[k][1] = 0.f;
-        if (row < rows) {
-          const int b0 = row / e1, b1 = row - b0 * e1;
-          int r0 = m0 + b0, r1 = m1 + b1;
-          if (r0 >= g.n0) r0 -= g.n0;
-          if (r1 >= g.n1) r1 -= g.n1;
-          const float* __restrict__ src = c + ((int64_t)r0 * g.n1 + r1) * g.n2;
-#pragma unroll
-          for (int h = 0; h < 2; ++h) {
-            const int cc = lcol + 64 * h;
-            if (cc < e2) {
-              int c2 = m2 + cc;
-              if (c2 >= g.n2) c2 -= g.n2;
-              vals[k][h] = src[c2];
-            }
-          }
-        }
+      for (int k = 0; k < U; ++k) {
+        int y0 = m0 + r0, y1 = m1 + r1, y2 = m2 + col;
+        y0 = y0 >= g.n0 ? y0 - g.n0 : y0;
+        y1 = y1 >= g.n1 ? y1 - g.n1 : y1;
+        y2 = y2 >= g.n2 ? y2 - g.n2 : y2;
+        const bool ok = t0 + NTHR * k < total;
+        at[k] = ok ? r0 * plane + r1 * pitch + col : -1;
+        v[k] = c[ok ? (y0 * g.n1 + y1) * g.n2 + y2 : 0];
+        col += d2, r1 += d1, r0 += d0;
+        if (col >= e[2]) col -= e[2], ++r1;
+        if (r1 >= e[1]) r1 -= e[1], ++r0;
       }
 #pragma unroll
-      for (int k = 0; k < RB; ++k) {
-        const int row = row0 + k * rstep + lrow;
-        if (row < rows) {
-#pragma unroll
-          for (int h = 0; h < 2; ++h) {
-            const int cc = lcol + 64 * h;
-            if (cc < e2) br[row * e2 + cc] = vals[k][h];
-          }
-        }
-      }
+      for (int k = 0; k < U; ++k)
+        if (at[k] >= 0) br[at[k]] = v[k];
     }
     __syncthreads();
   }
 #pragma unroll
   for (int j = 0; j < PPT; ++j) {
     if (!live[j]) continue;
+    const float f0 = floorf(x[j][0]), f1 = floorf(x[j][1]), f2 = floorf(x[j][2]);
     float val;
     if (staged) {
-      const float f0 = floorf(x[j][0]), f1 = floorf(x[j][1]), f2 = floorf(x[j][2]);
       float w0[4], w1[4], w2[4];
       bspline_weights(x[j][0] - f0, w0);
       bspline_weights(x[j][1] - f1, w1);
       bspline_weights(x[j][2] - f2, w2);
-      val = eval_box(br, static_cast<int>(f0) - 1 - lo0, static_cast<int>(f1) - 1 - lo1,
-                     static_cast<int>(f2) - 1 - lo2, e1, e2, w0, w1, w2);
+      const int s0 = static_cast<int>(f0) - 1 - lo[0], s1 = static_cast<int>(f1) - 1 - lo[1],
+                s2 = static_cast<int>(f2) - 1 - lo[2];
+      val = eval_box((lds_float*)br + (s0 * plane + s1 * pitch + s2), plane, pitch, w0, w1, w2);
     } else {
-      const float f0 = floorf(x[j][0]), f1 = floorf(x[j][1]), f2 = floorf(x[j][2]);
       val = eval_global(c, static_cast<int>(f0), static_cast<int>(f1), static_cast<int>(f2), x[j][0] - f0, x[j][1] - f1,
                         x[j][2] - f2, g.n0, g.n1, g.n2);
     }
-    const int64_t o = node * P + pidx[j];
-    out[o] = a * (w ? w[o] * val : val);
+    out[node * P + pidx[j]] = a * (w ? fac[j] * val : val);
   }
 }
 
@@ -713,7 +712,7 @@ void brick_pull_back(float* out, const float* c, const float* u, const float* w,
                      hipStream_t s) {
   // 8 x 8 x 16 nodes per workgroup: the boxes of an 8-voxel deformation of 128^3 hold 5 staged values per
   // node on average and all fit in 8192 floats (32 KB, five workgroups per CU)
-  constexpr int TX0 = 8, TX1 = 8, TX2 = 16, NTHR = 256, CAP = 8192;
+  constexpr int TX0 = 8, TX1 = 8, TX2 = 16, NTHR = 512, CAP = 8192;
   if (nodes < 1 || nodes > 65535) throw ArgError("brick_pull_back: node count out of range");
   const Grid3 g{d.n[0], d.n[1], d.n[2], d.P};
   const int64_t tiles = (int64_t)ceil_div(d.n[0], TX0) * ceil_div(d.n[1], TX1) * ceil_div(d.n[2], TX2);
