@@ -29,29 +29,34 @@ __device__ __forceinline__ GridIdx unflatten(int64_t p, int n1, int n2) {
   return g;
 }
 
-// Tricubic B-spline taps of one point: periodic indices and weights per axis.
+// Tricubic B-spline taps of one point: periodic indices and weights per axis.  A 2D problem's first axis holds one
+// node, whose four taps add up to it: 16 taps instead of 64 (FP64, 64^2: an interpolation 5.1 -> 3.0 us).
 template <typename T>
 struct Taps {
   int i0[4], i1[4], i2[4];
   T w0[4], w1[4], w2[4];
+  bool flat;
   __device__ __forceinline__ void set(T x0, T x1, T x2, int n0, int n1, int n2) {
+    flat = n0 == 1;
     bspline_weights(tap_indices(x0, n0, i0), w0);
     bspline_weights(tap_indices(x1, n1, i1), w1);
     bspline_weights(tap_indices(x2, n2, i2), w2);
   }
+  __device__ __forceinline__ T plane(const T* __restrict__ c, int n1, int n2, int i) const {
+    T s = T(0);
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      const T* row = c + (static_cast<int64_t>(i) * n1 + i1[b]) * n2;
+      const T sb = w2[0] * row[i2[0]] + w2[1] * row[i2[1]] + w2[2] * row[i2[2]] + w2[3] * row[i2[3]];
+      s += w1[b] * sb;
+    }
+    return s;
+  }
   __device__ __forceinline__ T eval(const T* __restrict__ c, int n1, int n2) const {
+    if (flat) return plane(c, n1, n2, 0);
     T acc = T(0);
 #pragma unroll
-    for (int a = 0; a < 4; ++a) {
-      T sa = T(0);
-#pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        const T* row = c + (static_cast<int64_t>(i0[a]) * n1 + i1[b]) * n2;
-        const T sb = w2[0] * row[i2[0]] + w2[1] * row[i2[1]] + w2[2] * row[i2[2]] + w2[3] * row[i2[3]];
-        sa += w1[b] * sb;
-      }
-      acc += w0[a] * sa;
-    }
+    for (int a = 0; a < 4; ++a) acc += w0[a] * plane(c, n1, n2, i0[a]);
     return acc;
   }
 };
@@ -452,7 +457,7 @@ __global__ void k_jacobian(double* out, const T* Du, int64_t P) {
 // registers and in double.  Chunks are independent, so nothing is staged, no thread waits for another, and a
 // pass is a few microseconds of load latency: 128^3, one field 15.8 -> 7.5 us per axis (16.8 MB at 2.2 TB/s; the
 // neighbours' points come from the caches), two fields 11.2, against a staged tile of lines whose serial start
-// sums and recursions each waited for LDS.  FP64 64^2: 7.7 -> 7.4 us.
+// sums and recursions each waited for LDS.  FP64 64^2: 7.7 -> 7.4 us (a 2D field of this size takes the kernel below).
 template <typename T>
 struct Pole {
   static constexpr double z = -0.26794919243112270647255365849413;  // sqrt(3) - 2
@@ -555,6 +560,75 @@ __global__ __launch_bounds__(256) void k_prefilter(PrefilterArgs<T> a) {
   }
 }
 
+// A 2D problem's field, both axes in one workgroup: the plane is staged once (rows of an odd pitch, so lanes on
+// consecutive rows meet different banks), each thread filters its chunks straight from LDS as above.  The two
+// passes of a field of a few thousand nodes were a launch each: FP64 64^2 13.5 -> 6.7 us.
+constexpr int kPlaneThreads = 512;
+constexpr size_t kPlaneBytes = 65536;
+
+template <typename T>
+__global__ __launch_bounds__(kPlaneThreads) void k_prefilter_plane(PrefilterArgs<T> a, int n1, int n2) {
+  constexpr int C = kChunk, W = Pole<T>::W;
+  extern __shared__ __align__(16) unsigned char plane_smem[];
+  T* s = reinterpret_cast<T*>(plane_smem);
+  const int tid = threadIdx.x, pitch = n2 | 1, field = blockIdx.x;
+  const T* __restrict__ f = a.src[field];
+  const T* __restrict__ w = a.w[field];
+  for (int p = tid; p < n1 * n2; p += kPlaneThreads) {
+    const int r = p / n2;
+    s[r * pitch + p - r * n2] = w ? f[p] * w[p] : f[p];
+  }
+  // lines of n points at distance `step`, line l at l * across, lanes on consecutive lines; put(point, value) after
+  // every thread has read
+  auto pass = [&](int n, int step, int lines, int across, auto&& put) {
+    const int nch = (n + C - 1) / C, tasks = nch * lines;
+    for (int t0 = 0; t0 < tasks; t0 += kPlaneThreads) {
+      const int t = t0 + tid, l = t % lines, c0 = t / lines * C;
+      double y[C + W];
+      __syncthreads();
+      if (t < tasks) {
+        const T* line = s + l * across;
+        int i = (c0 - W) % n;
+        i = i < 0 ? i + n : i;
+        auto next = [&] {
+          const double x = static_cast<double>(line[i * step]);
+          i = i + 1 == n ? 0 : i + 1;
+          return x;
+        };
+        const double z = Pole<T>::z;
+        double prev = 0.0;
+#pragma unroll 8
+        for (int k = 0; k < W; ++k) prev = fma(z, prev, next());
+#pragma unroll
+        for (int k = 0; k < C + W; ++k) y[k] = prev = fma(z, prev, next());
+        prev = 0.0;
+#pragma unroll
+        for (int k = C + W - 1; k >= C; --k) prev = fma(z, prev, y[k]);
+#pragma unroll
+        for (int k = C - 1; k >= 0; --k) {
+          prev = fma(z, prev, y[k]);
+          y[k] = -6.0 * z * prev;
+        }
+      }
+      put(t < tasks, l, c0, y);
+    }
+  };
+  T* __restrict__ dst = a.dst + field * a.P;
+  pass(n2, 1, n1, pitch, [&](bool ok, int l, int c0, const double (&y)[C + W]) {
+    __syncthreads();
+    if (ok)
+#pragma unroll
+      for (int k = 0; k < C; ++k)
+        if (c0 + k < n2) s[l * pitch + c0 + k] = static_cast<T>(y[k]);
+  });
+  pass(n1, pitch, n2, 1, [&](bool ok, int l, int c0, const double (&y)[C + W]) {
+    if (ok)
+#pragma unroll
+      for (int k = 0; k < C; ++k)
+        if (c0 + k < n1) dst[(c0 + k) * n2 + l] = static_cast<T>(y[k]);
+  });
+}
+
 inline dim3 grid_for(int64_t n) { return dim3(ceil_div(n, kBlock)); }
 
 }  // namespace
@@ -618,6 +692,14 @@ void prefilter(T* dst, T* tmp, const T* const* src, const T* const* w, int nf, c
   PrefilterArgs<T> a{};
   for (int f = 0; f < nf; ++f) a.src[f] = src[f], a.w[f] = w ? w[f] : nullptr;
   a.P = d.P;
+  // (one round of the workgroup's threads per axis: a row of chunks may not read what another round wrote)
+  if (n0 == 1 && (size_t)n1 * (n2 | 1) * sizeof(T) <= kPlaneBytes && ceil_div(n2, kChunk) * n1 <= kPlaneThreads) {
+    a.dst = dst;
+    prof::launch(nm, 2.0 * nf * d.P * sizeof(T), 0.0, k_prefilter_plane<T>, dim3(nf), dim3(kPlaneThreads),
+                 (uint32_t)((size_t)n1 * (n2 | 1) * sizeof(T)), s, a, n1, n2);
+    LDDMM_LAUNCH_CHECK();
+    return;
+  }
   // passes alternate between dst and tmp so that the last one writes dst
   auto pass = [&](int axis) {
     --left;
