@@ -560,60 +560,75 @@ __global__ __launch_bounds__(256) void k_prefilter(PrefilterArgs<T> a) {
   }
 }
 
-// A 2D problem's field, both axes in one workgroup: the plane is staged once (rows of an odd pitch, so lanes on
-// consecutive rows meet different banks), each thread filters its chunks straight from LDS as above.  The two
-// passes of a field of a few thousand nodes were a launch each: FP64 64^2 13.5 -> 6.7 us.
-constexpr int kPlaneThreads = 512;
-constexpr size_t kPlaneBytes = 65536;
+// Both inner axes of a plane in one workgroup: the plane is staged once (rows of an odd pitch, so lanes on
+// consecutive rows meet different banks), each thread filters one chunk of either axis straight from LDS as above.
+// A 2D field of a few thousand nodes is then one launch instead of two (FP64 64^2: 13.5 -> 6.7 us), a 3D one two
+// instead of three, of 80 KB and a chunk per thread at most (one workgroup a CU; 128^3, two fields: 34 -> 26 us, one no slower).
+constexpr int kPlaneThreads = 1024;
+constexpr int kPlaneBytes = 81920;
 
 template <typename T>
 __global__ __launch_bounds__(kPlaneThreads) void k_prefilter_plane(PrefilterArgs<T> a, int n1, int n2) {
   constexpr int C = kChunk, W = Pole<T>::W;
-  extern __shared__ __align__(16) unsigned char plane_smem[];
-  T* s = reinterpret_cast<T*>(plane_smem);
-  const int tid = threadIdx.x, pitch = n2 | 1, field = blockIdx.x;
-  const T* __restrict__ f = a.src[field];
-  const T* __restrict__ w = a.w[field];
-  for (int p = tid; p < n1 * n2; p += kPlaneThreads) {
-    const int r = p / n2;
-    s[r * pitch + p - r * n2] = w ? f[p] * w[p] : f[p];
-  }
-  // lines of n points at distance `step`, line l at l * across, lanes on consecutive lines; put(point, value) after
-  // every thread has read
-  auto pass = [&](int n, int step, int lines, int across, auto&& put) {
-    const int nch = (n + C - 1) / C, tasks = nch * lines;
-    for (int t0 = 0; t0 < tasks; t0 += kPlaneThreads) {
-      const int t = t0 + tid, l = t % lines, c0 = t / lines * C;
-      double y[C + W];
-      __syncthreads();
-      if (t < tasks) {
-        const T* line = s + l * across;
-        int i = (c0 - W) % n;
-        i = i < 0 ? i + n : i;
-        auto next = [&] {
-          const double x = static_cast<double>(line[i * step]);
-          i = i + 1 == n ? 0 : i + 1;
-          return x;
-        };
-        const double z = Pole<T>::z;
-        double prev = 0.0;
-#pragma unroll 8
-        for (int k = 0; k < W; ++k) prev = fma(z, prev, next());
+  __shared__ T s[kPlaneBytes / sizeof(T)];
+  const int tid = threadIdx.x, pitch = n2 | 1, field = blockIdx.y;
+  const int64_t plane = (int64_t)blockIdx.x * n1 * n2;
+  const T* __restrict__ f = a.src[field] + plane;
+  const T* __restrict__ w = a.w[field] ? a.w[field] + plane : nullptr;
+  {
+    constexpr int U = 8;  // values requested together
+    const int dr = kPlaneThreads / n2, dc = kPlaneThreads - dr * n2;
+    int r = tid / n2, c = tid - r * n2;
+    for (int p0 = tid; p0 < n1 * n2; p0 += kPlaneThreads * U) {
+      T v[U], u[U];
+      int at[U];
 #pragma unroll
-        for (int k = 0; k < C + W; ++k) y[k] = prev = fma(z, prev, next());
-        prev = 0.0;
-#pragma unroll
-        for (int k = C + W - 1; k >= C; --k) prev = fma(z, prev, y[k]);
-#pragma unroll
-        for (int k = C - 1; k >= 0; --k) {
-          prev = fma(z, prev, y[k]);
-          y[k] = -6.0 * z * prev;
-        }
+      for (int k = 0; k < U; ++k) {
+        const int p = p0 + kPlaneThreads * k;
+        at[k] = p < n1 * n2 ? r * pitch + c : -1;
+        v[k] = f[at[k] >= 0 ? p : 0];
+        if (w) u[k] = w[at[k] >= 0 ? p : 0];
+        r += dr, c += dc;
+        if (c >= n2) c -= n2, ++r;
       }
-      put(t < tasks, l, c0, y);
+#pragma unroll
+      for (int k = 0; k < U; ++k)
+        if (at[k] >= 0) s[at[k]] = w ? v[k] * u[k] : v[k];
     }
+  }
+  // lines of n points at distance `step`, line l at l * across, lanes on consecutive lines, a chunk per thread
+  auto pass = [&](int n, int step, int lines, int across, auto&& put) {
+    const int l = tid % lines, c0 = tid / lines * C;
+    const bool mine = c0 < n;
+    double y[C + W];
+    __syncthreads();
+    if (mine) {
+      const T* line = s + l * across;
+      int i = (c0 - W) % n;
+      i = i < 0 ? i + n : i;
+      auto next = [&] {
+        const double x = static_cast<double>(line[i * step]);
+        i = i + 1 == n ? 0 : i + 1;
+        return x;
+      };
+      const double z = Pole<T>::z;
+      double prev = 0.0;
+#pragma unroll 8
+      for (int k = 0; k < W; ++k) prev = fma(z, prev, next());
+#pragma unroll
+      for (int k = 0; k < C + W; ++k) y[k] = prev = fma(z, prev, next());
+      prev = 0.0;
+#pragma unroll
+      for (int k = C + W - 1; k >= C; --k) prev = fma(z, prev, y[k]);
+#pragma unroll
+      for (int k = C - 1; k >= 0; --k) {
+        prev = fma(z, prev, y[k]);
+        y[k] = -6.0 * z * prev;
+      }
+    }
+    put(mine, l, c0, y);
   };
-  T* __restrict__ dst = a.dst + field * a.P;
+  T* __restrict__ dst = a.dst + field * a.P + plane;
   pass(n2, 1, n1, pitch, [&](bool ok, int l, int c0, const double (&y)[C + W]) {
     __syncthreads();
     if (ok)
@@ -692,14 +707,6 @@ void prefilter(T* dst, T* tmp, const T* const* src, const T* const* w, int nf, c
   PrefilterArgs<T> a{};
   for (int f = 0; f < nf; ++f) a.src[f] = src[f], a.w[f] = w ? w[f] : nullptr;
   a.P = d.P;
-  // (one round of the workgroup's threads per axis: a row of chunks may not read what another round wrote)
-  if (n0 == 1 && (size_t)n1 * (n2 | 1) * sizeof(T) <= kPlaneBytes && ceil_div(n2, kChunk) * n1 <= kPlaneThreads) {
-    a.dst = dst;
-    prof::launch(nm, 2.0 * nf * d.P * sizeof(T), 0.0, k_prefilter_plane<T>, dim3(nf), dim3(kPlaneThreads),
-                 (uint32_t)((size_t)n1 * (n2 | 1) * sizeof(T)), s, a, n1, n2);
-    LDDMM_LAUNCH_CHECK();
-    return;
-  }
   // passes alternate between dst and tmp so that the last one writes dst
   auto pass = [&](int axis) {
     --left;
@@ -728,6 +735,17 @@ void prefilter(T* dst, T* tmp, const T* const* src, const T* const* w, int nf, c
       if (a.w[f]) mul<T>(dst + f * d.P, a.src[f], a.w[f], d.P, s);
       else copy_dev<T>(dst + f * d.P, a.src[f], d.P, s);
     }
+  if (n1 > 1 && n2 > 1 && (int64_t)n1 * (n2 | 1) * (int64_t)sizeof(T) <= kPlaneBytes &&
+      (int64_t)ceil_div(n2, kChunk) * n1 <= kPlaneThreads && (int64_t)ceil_div(n1, kChunk) * n2 <= kPlaneThreads) {
+    left = n0 > 1;
+    a.dst = left ? tmp : dst;
+    prof::launch(nm, 2.0 * nf * d.P * sizeof(T), 0.0, k_prefilter_plane<T>, dim3(n0, nf), dim3(kPlaneThreads), 0, s, a, n1,
+                 n2);
+    LDDMM_LAUNCH_CHECK();
+    for (int f = 0; f < nf; ++f) a.src[f] = a.dst + f * d.P, a.w[f] = nullptr;
+    if (n0 > 1) pass(0);
+    return;
+  }
   for (int axis = 2; axis >= 0; --axis)
     if (d.n[axis] > 1) pass(axis);
 }
