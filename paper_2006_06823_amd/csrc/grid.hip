@@ -562,8 +562,8 @@ __global__ __launch_bounds__(256) void k_prefilter(PrefilterArgs<T> a) {
 
 // Both inner axes of a plane in one workgroup: the plane is staged once (rows of an odd pitch, so lanes on
 // consecutive rows meet different banks), each thread filters one chunk of either axis straight from LDS as above.
-// A 2D field of a few thousand nodes is then one launch instead of two (FP64 64^2: 13.5 -> 6.7 us), a 3D one two
-// instead of three, of 80 KB and a chunk per thread at most (one workgroup a CU; 128^3, two fields: 34 -> 26 us, one no slower).
+// A 2D field of a few thousand nodes is then one launch instead of two (FP64 64^2: 13.5 -> 6.4 us), a 3D one two
+// instead of three, of 80 KB and a chunk of 64 lines per wave at most (one workgroup a CU; 128^3, two fields: 34 -> 24 us, one 22 -> 20).
 constexpr int kPlaneThreads = 1024;
 constexpr int kPlaneBytes = 81920;
 
@@ -596,10 +596,12 @@ __global__ __launch_bounds__(kPlaneThreads) void k_prefilter_plane(PrefilterArgs
         if (at[k] >= 0) s[at[k]] = w ? v[k] * u[k] : v[k];
     }
   }
-  // lines of n points at distance `step`, line l at l * across, lanes on consecutive lines, a chunk per thread
+  // lines of n points at distance `step`, line l at l * across: a wave filters one chunk of 64 lines (the wrapped
+  // index is uniform: in vector registers its compare and select cost more than the recursions)
   auto pass = [&](int n, int step, int lines, int across, auto&& put) {
-    const int l = tid % lines, c0 = tid / lines * C;
-    const bool mine = c0 < n;
+    const int groups = (lines + 63) / 64, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l = wave % groups * 64 + (tid & 63), c0 = wave / groups * C;
+    const bool mine = c0 < n && l < lines;
     double y[C + W];
     __syncthreads();
     if (mine) {
@@ -736,7 +738,8 @@ void prefilter(T* dst, T* tmp, const T* const* src, const T* const* w, int nf, c
       else copy_dev<T>(dst + f * d.P, a.src[f], d.P, s);
     }
   if (n1 > 1 && n2 > 1 && (int64_t)n1 * (n2 | 1) * (int64_t)sizeof(T) <= kPlaneBytes &&
-      (int64_t)ceil_div(n2, kChunk) * n1 <= kPlaneThreads && (int64_t)ceil_div(n1, kChunk) * n2 <= kPlaneThreads) {
+      ceil_div(n2, kChunk) * ceil_div(n1, 64) <= kPlaneThreads / 64 &&
+      ceil_div(n1, kChunk) * ceil_div(n2, 64) <= kPlaneThreads / 64) {
     left = n0 > 1;
     a.dst = left ? tmp : dst;
     prof::launch(nm, 2.0 * nf * d.P * sizeof(T), 0.0, k_prefilter_plane<T>, dim3(n0, nf), dim3(kPlaneThreads), 0, s, a, n1,
