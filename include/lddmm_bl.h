@@ -39,7 +39,7 @@
  * buffers are borrowed until the stream has run the call.  The context owns
  * its workspaces (trajectories, departure points, scratch).  Every call runs
  * in order on the stream given at creation and synchronises that stream
- * before it returns, except lddmm_bl_hess_matvec and
+ * before it returns, except lddmm_bl_hess_matvec(_on) and
  * lddmm_bl_project_noalloc, which only enqueue their work: their results are
  * ready, and their buffers free for other use, once the stream has reached
  * them.  No exception or abort crosses the ABI.
@@ -192,6 +192,12 @@ lddmm_bl_status lddmm_bl_adjoint_solve(lddmm_bl_ctx* ctx, void* grad_bl, double*
  * replays a HIP graph captured on the caller's own (dv_bl, hdv_bl) pair (the
  * four most recent pairs are kept). */
 lddmm_bl_status lddmm_bl_hess_matvec(lddmm_bl_ctx* ctx, const void* dv_bl, void* hdv_bl);
+
+/* The same enqueued on `stream` (of the context's device; NULL: the default
+ * stream), for callers whose other work runs there: ordered after that
+ * stream's work and after the context's earlier calls, whose later calls wait
+ * for it. */
+lddmm_bl_status lddmm_bl_hess_matvec_on(lddmm_bl_ctx* ctx, const void* dv_bl, void* hdv_bl, void* stream);
 
 /* Gauss-Newton-Krylov registration (eqs. BLNewton, BLKKT) starting from
  * v_bl_inout (device BL [d][K..]), which receives the result.  PCG uses

@@ -51,9 +51,10 @@ float* scratch_for_current_device() {
 }
 
 template <typename F>
-lddmm_bl_status guarded(lddmm_bl_ctx* ctx, F&& f) {
+lddmm_bl_status guarded(lddmm_bl_ctx* ctx, F&& f, bool join = true) {
   if (!ctx || !ctx->solver) return LDDMM_BL_E_ARG;
   try {
+    if (join) ctx->solver->join();
     return static_cast<lddmm_bl_status>(f());
   } catch (const lddmm::ArgError& e) {
     ctx->err = e.what();
@@ -153,6 +154,18 @@ lddmm_bl_status lddmm_bl_hess_matvec(lddmm_bl_ctx* ctx, const void* dv_bl, void*
     ctx->solver->hess_matvec(dv_bl, hdv_bl);
     return 0;
   });
+}
+
+lddmm_bl_status lddmm_bl_hess_matvec_on(lddmm_bl_ctx* ctx, const void* dv_bl, void* hdv_bl, void* stream) {
+  return guarded(
+      ctx,
+      [&] {
+        if (!dv_bl || !hdv_bl) throw lddmm::ArgError("null vector");
+        if (dv_bl == hdv_bl) throw lddmm::ArgError("dv and hdv may not alias");
+        ctx->solver->hess_matvec_on(dv_bl, hdv_bl, static_cast<hipStream_t>(stream));
+        return 0;
+      },
+      false);
 }
 
 lddmm_bl_status lddmm_bl_gn_solve(lddmm_bl_ctx* ctx, const lddmm_bl_gn_opts* opts, void* v_bl_inout,

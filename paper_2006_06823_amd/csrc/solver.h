@@ -20,6 +20,8 @@ class SolverBase {
   virtual void state_solve(const void* v, void* m1, double* E3) = 0;
   virtual void adjoint_solve(void* grad, double* ginf) = 0;
   virtual void hess_matvec(const void* dv, void* hdv) = 0;
+  virtual void hess_matvec_on(const void* dv, void* hdv, hipStream_t s) = 0;
+  virtual void join() = 0;  // the context's stream waits for a product enqueued on another
   virtual int gn_solve(const lddmm_bl_gn_opts& o, void* v, const void* Z, int r, lddmm_bl_gn_report* rep) = 0;
   virtual void jacobian(double* detmap, double* minmax) = 0;
   virtual void project(const void* grid, void* bl, int ncomp) = 0;

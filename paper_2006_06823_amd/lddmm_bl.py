@@ -35,7 +35,8 @@ STATUS = {
 
 EXPORTS = [
     "lddmm_bl_create", "lddmm_bl_destroy", "lddmm_bl_last_error", "lddmm_bl_set_images",
-    "lddmm_bl_state_solve", "lddmm_bl_adjoint_solve", "lddmm_bl_hess_matvec", "lddmm_bl_gn_solve",
+    "lddmm_bl_state_solve", "lddmm_bl_adjoint_solve", "lddmm_bl_hess_matvec", "lddmm_bl_hess_matvec_on",
+    "lddmm_bl_gn_solve",
     "lddmm_bl_jacobian", "lddmm_bl_project", "lddmm_bl_project_noalloc", "lddmm_bl_include", "lddmm_bl_get_field", "lddmm_bl_dot",
     "lddmm_bl_profile_enable", "lddmm_bl_profile_read", "lddmm_bl_gn_solve_batched",
     "lddmm_bl_tune_candidates", "lddmm_bl_tune_get", "lddmm_bl_tune_set", "lddmm_bl_tune_table",
@@ -103,6 +104,7 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
         "lddmm_bl_state_solve": [vp, vp, vp, dp],
         "lddmm_bl_adjoint_solve": [vp, vp, dp],
         "lddmm_bl_hess_matvec": [vp, vp, vp],
+        "lddmm_bl_hess_matvec_on": [vp, vp, vp, vp],
         "lddmm_bl_gn_solve": [vp, ctypes.POINTER(GNOpts), vp, vp, i32, ctypes.POINTER(GNReport)],
         "lddmm_bl_jacobian": [vp, vp, dp],
         "lddmm_bl_project": [vp, vp, vp, i32],
@@ -330,13 +332,17 @@ class Context:
         return g, ginf.value
 
     def hess_matvec(self, dv: torch.Tensor, out: Optional[torch.Tensor] = None) -> torch.Tensor:
-        """H dv into out, enqueued on the context's stream; the current stream waits for it (no host wait)."""
+        """H dv into out, enqueued on the current stream (no host wait)."""
         self._arg(dv, self._vshape(), "dv")
         out = torch.empty(self._vshape(), dtype=self.dtype, device=self.device) if out is None else \
             self._arg(out, self._vshape(), "out")
-        self._order()
-        self._check(self.lib.lddmm_bl_hess_matvec(self.h, _ptr(dv), _ptr(out)))
-        self._after()
+        cur = torch.cuda.current_stream(self.device)
+        if torch.cuda.is_current_stream_capturing():  # the replay stays on the context's stream
+            self._order()
+            self._check(self.lib.lddmm_bl_hess_matvec(self.h, _ptr(dv), _ptr(out)))
+            self._after()
+        else:
+            self._check(self.lib.lddmm_bl_hess_matvec_on(self.h, _ptr(dv), _ptr(out), ctypes.c_void_p(cur.cuda_stream)))
         return out
 
     def gn_solve(self, v: torch.Tensor, max_gn=10, max_pcg=5, grad_rtol=1e-3, grad_ref_inf=0.0,
