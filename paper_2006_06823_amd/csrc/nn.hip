@@ -475,22 +475,41 @@ __global__ void k_fill(float* p, int64_t n, float v) {
   if (i < n) p[i] = v;
 }
 
-// network input from an image pair: box average of each f0 x f1 x f2 voxel cell, out [2][S^3]
-__global__ void k_pool_pair(const float* __restrict__ I0, const float* __restrict__ I1, int n1, int n2, int f0, int f1,
-                            int f2, int S, float* __restrict__ out) {
+// network input from an image pair: box average of each f0 x f1 x f2 voxel cell, out [2][S^3].  F > 0: cells of F^3,
+// whose loads are then all requested before the first sum (the loops of any other cell wait for a load per row:
+// 128^3 to 64^3 8.5 -> 5.7 us, 16.8 MB)
+template <int F>
+__global__ __launch_bounds__(256) void k_pool_pair(const float* __restrict__ I0, const float* __restrict__ I1, int n1,
+                                                   int n2, int f0, int f1, int f2, int S, float* __restrict__ out) {
   const int64_t S3 = (int64_t)S * S * S;
   const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (e >= 2 * S3) return;
-  const int ch = (int)(e / S3);
-  const int64_t o = e - ch * S3;
-  const int oz = (int)(o / (S * S)), oy = (int)((o / S) % S), ox = (int)(o % S);
-  const float* I = ch == 0 ? I0 : I1;
+  if constexpr (F > 0) f0 = f1 = f2 = F;
+  const int ch = e >= S3;
+  const unsigned o = (unsigned)(e - ch * S3), q = o / (unsigned)S;
+  const int oz = (int)(q / (unsigned)S), oy = (int)(q % (unsigned)S), ox = (int)(o % (unsigned)S);
+  const float* __restrict__ I = ch == 0 ? I0 : I1;
+  auto row = [&](int a, int b) { return I + ((int64_t)(oz * f0 + a) * n1 + (oy * f1 + b)) * n2 + (int64_t)ox * f2; };
   float sum = 0.f;
-  for (int a = 0; a < f0; ++a)
-    for (int b = 0; b < f1; ++b) {
-      const float* row = I + ((int64_t)(oz * f0 + a) * n1 + (oy * f1 + b)) * n2 + (int64_t)ox * f2;
-      for (int c = 0; c < f2; ++c) sum += row[c];
-    }
+  if constexpr (F > 0) {
+    float v[F][F][F];
+#pragma unroll
+    for (int a = 0; a < F; ++a)
+#pragma unroll
+      for (int b = 0; b < F; ++b)
+#pragma unroll
+        for (int c = 0; c < F; ++c) v[a][b][c] = row(a, b)[c];
+#pragma unroll
+    for (int a = 0; a < F; ++a)
+#pragma unroll
+      for (int b = 0; b < F; ++b)
+#pragma unroll
+        for (int c = 0; c < F; ++c) sum += v[a][b][c];
+  } else {
+    for (int a = 0; a < f0; ++a)
+      for (int b = 0; b < f1; ++b)
+        for (int c = 0; c < f2; ++c) sum += row(a, b)[c];
+  }
   out[e] = sum / (float)(f0 * f1 * f2);
 }
 
@@ -750,7 +769,9 @@ void fill(float* p, int64_t n, float v, hipStream_t s) {
 
 void pool_pair(const float* I0, const float* I1, const int n[3], int S, float* out, hipStream_t s) {
   const int64_t tot = 2LL * S * S * S;
-  k_pool_pair<<<ceil_div(tot, 256), 256, 0, s>>>(I0, I1, n[1], n[2], n[0] / S, n[1] / S, n[2] / S, S, out);
+  const int f0 = n[0] / S, f1 = n[1] / S, f2 = n[2] / S;
+  auto* k = f0 == 2 && f1 == 2 && f2 == 2 ? k_pool_pair<2> : f0 == 1 && f1 == 1 && f2 == 1 ? k_pool_pair<1> : k_pool_pair<0>;
+  k<<<ceil_div(tot, 256), 256, 0, s>>>(I0, I1, n[1], n[2], f0, f1, f2, S, out);
   LDDMM_LAUNCH_CHECK();
 }
 
