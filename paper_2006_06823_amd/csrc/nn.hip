@@ -424,14 +424,27 @@ __global__ __launch_bounds__(256) void k_conv_wgrad(WGradArgs a) {
 }
 
 // dw[i] += sum_z part[z][i]
-__global__ __launch_bounds__(256) void k_sum_parts(float* __restrict__ dw, const float* __restrict__ part, int64_t n,
-                                                   int z) {
-  const int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x;
-  if (i >= n) return;
+// (G waves share out the parts of 64 weights: a small layer has many parts and few weights, whose one thread each
+// then read 512 parts in turn, 23.5 -> 4.3 us)
+template <int G>
+__global__ __launch_bounds__(64 * G) void k_sum_parts(float* __restrict__ dw, const float* __restrict__ part, int64_t n,
+                                                      int z) {
+  __shared__ float sums[G][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t i = blockIdx.x * (int64_t)64 + lane;
+  const int per = (z + G - 1) / G, k1 = min(z, (wave + 1) * per);
   float s = 0.f;
+  if (i < n) {
 #pragma unroll 8
-  for (int k = 0; k < z; ++k) s += part[(int64_t)k * n + i];
-  dw[i] += s;
+    for (int k = wave * per; k < k1; ++k) s += part[(int64_t)k * n + i];
+  }
+  sums[wave][lane] = s;
+  __syncthreads();
+  if (wave == 0 && i < n) {
+#pragma unroll
+    for (int g = 1; g < G; ++g) s += sums[g][lane];
+    dw[i] += s;
+  }
 }
 
 // G = dY * act'(Y) as the bf16 operand of both gradients, and the bias gradient db[c] += sum over the
@@ -738,7 +751,8 @@ void conv_backward(const ConvLayer& L, const float* x, const float* y, const flo
     else if (L.stride == 1) launch_wgrad<BoxT, 3, 1>(flops, w, mt, gw, s);
     else launch_wgrad<BoxT, 3, 2>(flops, w, mt, gw, s);
   });
-  k_sum_parts<<<ceil_div(L.nw(), 256), 256, 0, s>>>(L.dw, part, L.nw(), z);
+  if (z >= 128) k_sum_parts<16><<<ceil_div(L.nw(), 64), 1024, 0, s>>>(L.dw, part, L.nw(), z);
+  else k_sum_parts<4><<<ceil_div(L.nw(), 64), 256, 0, s>>>(L.dw, part, L.nw(), z);
   LDDMM_LAUNCH_CHECK();
   if (dx) {
     ConvArgs a{};
