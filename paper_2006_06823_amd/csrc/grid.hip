@@ -8,6 +8,7 @@
 #include "kernels.h"
 #include "prof.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace lddmm {
@@ -563,33 +564,42 @@ __global__ __launch_bounds__(256) void k_prefilter(PrefilterArgs<T> a) {
 // Both inner axes of a plane in one workgroup: the plane is staged once (rows of an odd pitch, so lanes on
 // consecutive rows meet different banks), each thread filters one chunk of either axis straight from LDS as above.
 // A 2D field of a few thousand nodes is then one launch instead of two (FP64 64^2: 13.5 -> 6.4 us), a 3D one two
-// instead of three, of 80 KB and a chunk of 64 lines per wave at most (one workgroup a CU; 128^3, two fields: 34 -> 24 us, one 22 -> 20).
+// instead of three, of 80 KB and a chunk of 64 lines per wave at most (one workgroup a CU; 128^3, two fields: 34 -> 24 us, one 22 -> 17.5).
 constexpr int kPlaneThreads = 1024;
 constexpr int kPlaneBytes = 81920;
 
-template <typename T>
-__global__ __launch_bounds__(kPlaneThreads) void k_prefilter_plane(PrefilterArgs<T> a, int n1, int n2) {
-  constexpr int C = kChunk, W = Pole<T>::W;
-  __shared__ T s[kPlaneBytes / sizeof(T)];
-  const int tid = threadIdx.x, pitch = n2 | 1, field = blockIdx.y;
+// TILE: a workgroup takes 64 columns of a plane (blockIdx.z) with the W columns on either side that their recursions
+// along the rows still feel, so twice the workgroups share 128^2 planes and planes of more columns fit.
+constexpr int kPlaneTile = 64;
+
+template <typename T, bool TILE, int NT, int BYTES>
+__global__ __launch_bounds__(NT) void k_prefilter_plane(PrefilterArgs<T> a, int n1, int n2) {
+  constexpr int C = kChunk, W = Pole<T>::W, OFF = TILE ? W : 0;
+  __shared__ T s[BYTES / sizeof(T)];
+  const int tid = threadIdx.x, field = blockIdx.y;
+  const int x0 = TILE ? blockIdx.z * kPlaneTile : 0, cols = TILE ? min(kPlaneTile, n2 - x0) : n2;
+  const int width = TILE ? kPlaneTile + 2 * W : n2, pitch = width | 1;
   const int64_t plane = (int64_t)blockIdx.x * n1 * n2;
   const T* __restrict__ f = a.src[field] + plane;
   const T* __restrict__ w = a.w[field] ? a.w[field] + plane : nullptr;
   {
     constexpr int U = 8;  // values requested together
-    const int dr = kPlaneThreads / n2, dc = kPlaneThreads - dr * n2;
-    int r = tid / n2, c = tid - r * n2;
-    for (int p0 = tid; p0 < n1 * n2; p0 += kPlaneThreads * U) {
+    const int dr = NT / width, dc = NT - dr * width, total = n1 * width;
+    int r = tid / width, c = tid - r * width;
+    for (int p0 = tid; p0 < total; p0 += NT * U) {
       T v[U], u[U];
       int at[U];
 #pragma unroll
       for (int k = 0; k < U; ++k) {
-        const int p = p0 + kPlaneThreads * k;
-        at[k] = p < n1 * n2 ? r * pitch + c : -1;
-        v[k] = f[at[k] >= 0 ? p : 0];
-        if (w) u[k] = w[at[k] >= 0 ? p : 0];
+        const bool ok = p0 + NT * k < total;
+        int col = c + x0 - OFF;
+        if (TILE) col = col < 0 ? col + n2 : col >= n2 ? col - n2 : col;
+        const int p = ok ? r * n2 + col : 0;
+        at[k] = ok ? r * pitch + c : -1;
+        v[k] = f[p];
+        if (w) u[k] = w[p];
         r += dr, c += dc;
-        if (c >= n2) c -= n2, ++r;
+        if (c >= width) c -= width, ++r;
       }
 #pragma unroll
       for (int k = 0; k < U; ++k)
@@ -598,19 +608,21 @@ __global__ __launch_bounds__(kPlaneThreads) void k_prefilter_plane(PrefilterArgs
   }
   // lines of n points at distance `step`, line l at l * across: a wave filters one chunk of 64 lines (the wrapped
   // index is uniform: in vector registers its compare and select cost more than the recursions)
-  auto pass = [&](int n, int step, int lines, int across, auto&& put) {
+  // (a tile's rows hold their halo and do not wrap)
+  auto pass = [&](int n, bool wrap, const T* base, int step, int lines, int across, auto&& put) {
     const int groups = (lines + 63) / 64, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l = wave % groups * 64 + (tid & 63), c0 = wave / groups * C;
     const bool mine = c0 < n && l < lines;
     double y[C + W];
     __syncthreads();
     if (mine) {
-      const T* line = s + l * across;
-      int i = (c0 - W) % n;
-      i = i < 0 ? i + n : i;
+      const T* line = base + l * across;
+      int i = c0 - W;
+      if (wrap) i %= n, i = i < 0 ? i + n : i;
       auto next = [&] {
         const double x = static_cast<double>(line[i * step]);
-        i = i + 1 == n ? 0 : i + 1;
+        ++i;
+        if (wrap && i == n) i = 0;
         return x;
       };
       const double z = Pole<T>::z;
@@ -631,18 +643,18 @@ __global__ __launch_bounds__(kPlaneThreads) void k_prefilter_plane(PrefilterArgs
     put(mine, l, c0, y);
   };
   T* __restrict__ dst = a.dst + field * a.P + plane;
-  pass(n2, 1, n1, pitch, [&](bool ok, int l, int c0, const double (&y)[C + W]) {
+  pass(cols, !TILE, s + OFF, 1, n1, pitch, [&](bool ok, int l, int c0, const double (&y)[C + W]) {
     __syncthreads();
     if (ok)
 #pragma unroll
       for (int k = 0; k < C; ++k)
-        if (c0 + k < n2) s[l * pitch + c0 + k] = static_cast<T>(y[k]);
+        if (c0 + k < cols) s[l * pitch + OFF + c0 + k] = static_cast<T>(y[k]);
   });
-  pass(n1, pitch, n2, 1, [&](bool ok, int l, int c0, const double (&y)[C + W]) {
+  pass(n1, true, s + OFF, pitch, cols, 1, [&](bool ok, int l, int c0, const double (&y)[C + W]) {
     if (ok)
 #pragma unroll
       for (int k = 0; k < C; ++k)
-        if (c0 + k < n1) dst[(c0 + k) * n2 + l] = static_cast<T>(y[k]);
+        if (c0 + k < n1) dst[(c0 + k) * n2 + x0 + l] = static_cast<T>(y[k]);
   });
 }
 
@@ -737,13 +749,28 @@ void prefilter(T* dst, T* tmp, const T* const* src, const T* const* w, int nf, c
       if (a.w[f]) mul<T>(dst + f * d.P, a.src[f], a.w[f], d.P, s);
       else copy_dev<T>(dst + f * d.P, a.src[f], d.P, s);
     }
-  if (n1 > 1 && n2 > 1 && (int64_t)n1 * (n2 | 1) * (int64_t)sizeof(T) <= kPlaneBytes &&
-      ceil_div(n2, kChunk) * ceil_div(n1, 64) <= kPlaneThreads / 64 &&
-      ceil_div(n1, kChunk) * ceil_div(n2, 64) <= kPlaneThreads / 64) {
+  constexpr int W = Pole<T>::W, kWide = (kPlaneTile + 2 * W) | 1;
+  // LDS and waves of whole planes, or of 64 columns of one: tiles where a plane does not fit, or the planes leave CUs
+  // idle (128^3, one field 12.9 -> 10.5 us; two, whose planes do not, 14.6 against 15.8 in tiles)
+  auto lds_of = [&](bool t) { return (int64_t)n1 * (t ? kWide : n2 | 1) * (int64_t)sizeof(T); };
+  auto waves_of = [&](bool t) {
+    return std::max((t ? kPlaneTile / kChunk : ceil_div(n2, kChunk)) * ceil_div(n1, 64),
+                    ceil_div(n1, kChunk) * (t ? 1 : ceil_div(n2, 64)));
+  };
+  auto fits = [&](bool t) { return lds_of(t) <= kPlaneBytes && waves_of(t) <= kPlaneThreads / 64; };
+  const bool tile = n2 >= kPlaneTile + 2 * W && ((int64_t)n0 * nf < 256 || !fits(false));  // (a halo wraps once)
+  const int64_t lds = lds_of(tile);
+  const int waves = waves_of(tile);
+  if (n1 > 1 && n2 > 1 && fits(tile)) {
     left = n0 > 1;
     a.dst = left ? tmp : dst;
-    prof::launch(nm, 2.0 * nf * d.P * sizeof(T), 0.0, k_prefilter_plane<T>, dim3(n0, nf), dim3(kPlaneThreads), 0, s, a, n1,
-                 n2);
+    auto go = [&](auto* k, int nt) {
+      prof::launch(nm, 2.0 * nf * d.P * sizeof(T), 0.0, k, dim3(n0, nf, tile ? ceil_div(n2, kPlaneTile) : 1), dim3(nt), 0,
+                   s, a, n1, n2);
+    };
+    if (!tile) go(k_prefilter_plane<T, false, 1024, kPlaneBytes>, 1024);
+    else if (waves <= 8 && lds <= 53248) go(k_prefilter_plane<T, true, 512, 53248>, 512);
+    else go(k_prefilter_plane<T, true, 1024, kPlaneBytes>, 1024);
     LDDMM_LAUNCH_CHECK();
     for (int f = 0; f < nf; ++f) a.src[f] = a.dst + f * d.P, a.w[f] = nullptr;
     if (n0 > 1) pass(0);

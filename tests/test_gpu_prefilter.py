@@ -1,5 +1,5 @@
 """The grid prefilter at line lengths around its chunk (16 points), its reach (16 points in FP32, 32 in FP64) and
-its 16-byte rows, in both precisions, and 2D ones that one workgroup holds, or just not.
+its 16-byte rows, in both precisions, and planes that one workgroup holds, whole or in tiles of 64 columns, or just not.
 
 At a zero velocity a step interpolates at the nodes, where the spline of the prefiltered image is the image: the
 final image equals the template.  Tolerance: a pass rounds its output once (unit roundoff u) and has gain at most 3,
@@ -18,7 +18,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("precision,u,tol", [(L.FP32, 2.0 ** -24, 1e-5), (L.FP64, 2.0 ** -53, 1e-10)])
-@pytest.mark.parametrize("N", [(4, 5, 6), (7, 16, 17), (33, 15, 31), (16, 34, 12), (18, 9, 65), (5, 48), (31, 32), (65, 66), (130, 40), (40, 200)])
+@pytest.mark.parametrize("N", [(4, 5, 6), (7, 16, 17), (33, 15, 31), (16, 34, 12), (18, 9, 65), (5, 48), (31, 32), (65, 66), (130, 40), (40, 200),
+                               (5, 20, 97), (4, 150, 130), (4, 33, 161), (129, 100), (20, 192)])
 def test_prefilter_line_lengths(N, precision, u, tol):
     K = (4,) * len(N)
     rng = np.random.default_rng(71)
