@@ -273,12 +273,22 @@ __global__ __launch_bounds__(TL::NTHR, Epi::NF >= 3 ? 2 : 4) void k_brick(Epi ep
         window_weights(d2[n], w2[n]);
       }
     }
+    // where two or more of the wave's four nodes are interpolated apart for some lane, all are: the window would cost
+    // more than it saves
+    bool apart = false;
+    if constexpr (!NODE) {
+      int some = 0;
+#pragma unroll
+      for (int n = 0; n < 4; ++n) some += __builtin_amdgcn_ballot_w64((far >> n) & 1) != 0;
+      apart = some >= 2;
+      if (apart) far = 15;
+    }
     f32x4 acc[NF], node[NF];
 #pragma unroll
     for (int f = 0; f < NF; ++f) acc[f] = node[f] = f32x4{0.f, 0.f, 0.f, 0.f};
     const float* win = br + (l0 * B1 + l1) * LD + l2;
 #pragma unroll 1
-    for (int a = 0; a < 5; ++a) {
+    for (int a = apart ? 5 : 0; a < 5; ++a) {
       f32x4 s[NF], sn[NF];
 #pragma unroll
       for (int f = 0; f < NF; ++f) s[f] = sn[f] = f32x4{0.f, 0.f, 0.f, 0.f};
