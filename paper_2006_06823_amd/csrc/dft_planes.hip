@@ -167,15 +167,16 @@ __global__ __launch_bounds__(256) void k_expand(PlaneExpandArgs a) {
 }
 
 // ------------------------------------------------------------------ reduction
-// Grid value of field f at node offset p (within the field) for the modes: a plain field, or a
-// pointwise product of band-limited fields on the product grid.  Loads past the arrays read 0.
+// Grid value of field f at a node of it for the modes: a plain field, or a pointwise product of band-limited fields
+// on the product grid.  Loads past the arrays read 0.  A plain field is the caller's and may hold infinities or NaN,
+// so the array ends with field f: the next field's values would meet the zeros past P1t's end.
 template <int MODE>
 struct RedIn {
   Rsrc in, e, divv, G;
   unsigned P, en;
-  __device__ __forceinline__ RedIn(const PlaneReduceArgs& a) : P((unsigned)a.P), en((unsigned)a.e_node) {
+  __device__ __forceinline__ RedIn(const PlaneReduceArgs& a, int f) : P((unsigned)a.P), en((unsigned)a.e_node) {
     if constexpr (MODE == kRedPlain) {
-      in = rsrc(a.in, (int64_t)a.nf * a.P);
+      in = rsrc(a.in, (f + 1) * a.P);
     } else {
       const int64_t ne = (MODE == kRedV1Products) ? 1 : (MODE == kRedV1Source || MODE == kRedV3Source) && a.e_node
                          ? (int64_t)(MODE == kRedV1Source ? a.nf : a.nf / 3) * 3 : 3;
@@ -186,13 +187,8 @@ struct RedIn {
       divv = rsrc(a.divv ? a.divv : a.e, a.P);
     }
   }
-  __device__ __forceinline__ float operator()(int f, unsigned p) const {
-    float x[kRaw];
-    fetch(f, p * 4u, 0, x);
-    return combine(x);
-  }
-  // the same in two steps, for the node at byte offset v (per lane) plus u elements (uniform): request its values,
-  // then combine them
+  // in two steps, for the node at byte offset v (per lane) plus u elements (uniform): request its values, then combine
+  // them
   static constexpr int kRaw = MODE == kRedPlain ? 1 : MODE == kRedV1Products ? 2 : MODE == kRedV3Source ? 7 : 6;
   __device__ __forceinline__ void fetch(int f, unsigned v, unsigned u, float (&x)[kRaw]) const {
     if constexpr (MODE == kRedPlain) {
@@ -243,18 +239,17 @@ __device__ __forceinline__ void reduce_store(const PlaneReduceArgs& a, int f, in
 // read along x2; chunks of JC k-steps alternate between two accumulators, shorter rounding chains);
 // stage B: R[a1][a2] += sum_x2 W[x2][a1] P2t[x2][a2], W's registers as the A operand.  Ragged tiles need
 // no test: rows x1 >= n1 meet rows of P1t past its end and columns x2 >= n2 rows of P2t past its end,
-// which read as zeros, against finite grid entries.  The waves' partial R are summed in LDS in wave
-// order (deterministic) and stored.
+// which read as zeros, against finite grid entries (or others of the same field, all of whose coefficients they
+// reach).  The waves' partial R are summed in LDS in wave order (deterministic) and stored.
 template <int MODE, int KT1, int KT2, int WAVES, int CH>
 __global__ __launch_bounds__(64 * WAVES) void k_reduce(PlaneReduceArgs a) {
   extern __shared__ float red[];  // [WAVES / 2][KT1 KT2][16][64]
   const int lane = threadIdx.x & 63, i = lane & 31, kh = lane >> 5;
   const int wave = uniform(threadIdx.x >> 6);
-  const int plane = blockIdx.x;
-  const int f = plane / a.n0, x0 = plane - f * a.n0;
+  const int f = blockIdx.y, x0 = blockIdx.x;
   const int n1 = a.n1, n2 = a.n2, k1 = a.k1, k2 = a.k2;
   const int T2 = (n2 + 31) >> 5, S1 = (n1 + CH - 1) / CH;
-  const RedIn<MODE> src(a);
+  const RedIn<MODE> src(a, f);
   const Rsrc rp1 = rsrc(a.p1t, (int64_t)n1 * k1), rp2 = rsrc(a.p2t, (int64_t)n2 * k2);
   f32x16 R[KT1][KT2];
 #pragma unroll
@@ -446,10 +441,10 @@ __global__ __launch_bounds__(512, 4) void k_reduce_r2(PlaneReduceArgs a, int chu
   constexpr int JC = MODE == kRedPlain ? 8 : In::kRaw == 2 ? 4 : 1;  // k-steps of a block
   const int lane = threadIdx.x & 63, i = lane & 31, kh = lane >> 5;
   const int wave = uniform(threadIdx.x >> 6), nw = blockDim.x >> 6, p = wave & 1;
-  const int f = blockIdx.x / a.n0, x0 = blockIdx.x - f * a.n0;
+  const int f = blockIdx.y, x0 = blockIdx.x;
   const int n1 = a.n1, n2 = a.n2, k1 = a.k1, k2 = a.k2, h1 = n1 >> 1, h2 = n2 >> 1;
   const int T2 = (h2 + 31) >> 5, S1 = (h1 + chunk - 1) / chunk;
-  const In src(a);
+  const In src(a, f);
   const Rsrc rp1 = rsrc(a.p1t, (int64_t)n1 * k1), rp2 = rsrc(a.p2t, (int64_t)n2 * k2);
   const unsigned up = (unsigned)(h1 * n2), plane = (unsigned)(x0 * n1 * n2);
   const float sg = p ? -1.f : 1.f;
@@ -806,7 +801,7 @@ void plane_expand(const PlaneExpandArgs& a, hipStream_t s) {
 template <int MODE>
 static void reduce_mode(const PlaneReduceArgs& a, hipStream_t s, double bytes, double flops) {
   const int kt1 = a.k1 > 32 ? 2 : 1, kt2 = a.k2 > 32 ? 2 : 1;
-  dim3 g(static_cast<unsigned>(a.nf * a.n0));
+  const dim3 g(a.n0, a.nf);
   const char* nm = MODE == kRedPlain ? "k_reduce" : "k_reduce_products";
   // tasks of 64 rows (16-wave workgroups with 32-row tasks measured slower); 8 waves (4 for two band tiles
   // per axis: 8 slowed the product modes of the 40x48x40 band from 29 to 54 us), their partials in half as
