@@ -303,7 +303,9 @@ struct WGradArgs {
   float* part;              // [gridDim.z][Cout][Cin k^3]
   int B, Cin, Cout, Di, Do, pad, nb;
 };
-template <class BoxT, int KS, int S, int MT>
+// RAGGED: some boxes reach past the output.  Their voxels there meet a G of zero, and an input that is not finite is
+// kept from them (64^3 pairs have no such boxes: the test would cost a training step on 16 of them 11 of 1234 us).
+template <class BoxT, int KS, int S, int MT, bool RAGGED>
 __global__ __launch_bounds__(256) void k_conv_wgrad(WGradArgs a) {
   using P = Patch<BoxT, KS, S>;
   constexpr int K3 = KS * KS * KS;
@@ -394,6 +396,8 @@ __global__ __launch_bounds__(256) void k_conv_wgrad(WGradArgs a) {
     __syncthreads();
     if (box + (int)gridDim.z < total) fetch(box + gridDim.z);
     if (mine) {
+      int o0[3];
+      if constexpr (RAGGED) box_origin<BoxT>(box % a.nb, Do, o0);
 #pragma unroll
       for (int q = 0; q < 8; ++q) {  // voxels 16 q + 8 kh + j: eight neighbours of one box row
         const int v = 16 * q + 8 * kh;
@@ -402,6 +406,11 @@ __global__ __launch_bounds__(256) void k_conv_wgrad(WGradArgs a) {
         u16x8 h;
 #pragma unroll
         for (int j = 0; j < 8; ++j) h[j] = xp[j * S];
+        if constexpr (RAGGED) {
+          const int left = o0[0] + lz < Do && o0[1] + ly < Do ? Do - o0[2] - lx : 0;
+#pragma unroll
+          for (int j = 0; j < 8; ++j) h[j] = j < left ? h[j] : (unsigned short)0;
+        }
         const bf16x8 bv = __builtin_bit_cast(bf16x8, h);
 #pragma unroll
         for (int m = 0; m < MT; ++m) {
@@ -655,13 +664,19 @@ void launch_conv(const char* name, double bytes, double flops, ConvArgs a, int B
   LDDMM_LAUNCH_CHECK();
 }
 
-template <class BoxT, int KS, int S>
+template <class BoxT, int KS, int S, bool RAGGED>
 void launch_wgrad(double flops, const WGradArgs& a, int mt, dim3 g, hipStream_t s) {
   const char* name = "k_conv_bwd_weight";
-  if (mt == 1) prof::launch(name, 0.0, flops, k_conv_wgrad<BoxT, KS, S, 1>, g, dim3(256), 0, s, a);
-  else if (mt == 2) prof::launch(name, 0.0, flops, k_conv_wgrad<BoxT, KS, S, 2>, g, dim3(256), 0, s, a);
-  else if constexpr (KS == 3) prof::launch(name, 0.0, flops, k_conv_wgrad<BoxT, KS, S, 4>, g, dim3(256), 0, s, a);
+  auto go = [&](auto* k) { prof::launch(name, 0.0, flops, k, g, dim3(256), 0, s, a); };
+  if (mt == 1) go(k_conv_wgrad<BoxT, KS, S, 1, RAGGED>);
+  else if (mt == 2) go(k_conv_wgrad<BoxT, KS, S, 2, RAGGED>);
+  else if constexpr (KS == 3) go(k_conv_wgrad<BoxT, KS, S, 4, RAGGED>);
   LDDMM_LAUNCH_CHECK();
+}
+template <class BoxT, int KS, int S>
+void launch_wgrad(double flops, const WGradArgs& a, int mt, dim3 g, hipStream_t s) {
+  if (a.Do % BoxT::BX || a.Do % BoxT::BY || a.Do % BoxT::BZ) launch_wgrad<BoxT, KS, S, true>(flops, a, mt, g, s);
+  else launch_wgrad<BoxT, KS, S, false>(flops, a, mt, g, s);
 }
 
 int out_edge(const ConvLayer& L, int Di) { return (Di + 2 * L.pad - L.k) / L.stride + 1; }

@@ -28,3 +28,24 @@ def test_transforms_keep_fields_apart(N, K, precision, bad):
             for o in range(3):
                 if o != f:
                     assert torch.equal(got[o], ref[o]), (call.__name__, f, o)
+
+
+# one level: output edges that leave boxes of voxels partly empty (26, 19, 5), and full ones (32, 16, 8)
+@pytest.mark.parametrize("edge", [26, 19, 5, 32, 16, 8])
+def test_weight_gradient_of_infinite_input(edge):
+    """A voxel in the last corner meets tap 0 of an axis only at an output that does not exist."""
+    net = L.WarmStartNet(channels=(5,), in_size=edge, seed=4)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    x = torch.randn(2, 2, edge, edge, edge, device="cuda", generator=g)
+    dout = torch.randn(2, 3, edge, edge, edge, device="cuda", generator=g)
+    grads = []
+    for value in (0.0, float("inf")):
+        x[1, 1, -1, -1, -1] = value
+        net.forward(x)
+        net.zero_grad()
+        net.backward(dout)
+        grads.append(torch.from_numpy(net.get(1)[:5 * 2 * 27]).reshape(5, 2, 3, 3, 3))
+    met = torch.zeros(2, 3, 3, 3, dtype=torch.bool)
+    met[1, 1:, 1:, 1:] = True
+    assert not torch.isfinite(grads[1][:, met]).all()
+    assert torch.isfinite(grads[1][:, ~met]).all()
