@@ -199,6 +199,10 @@ lddmm_bl_status lddmm_bl_hess_matvec(lddmm_bl_ctx* ctx, const void* dv_bl, void*
  * for it. */
 lddmm_bl_status lddmm_bl_hess_matvec_on(lddmm_bl_ctx* ctx, const void* dv_bl, void* hdv_bl, void* stream);
 
+/* The context's stream waits for the products enqueued on others (no host wait; every later call does this by
+ * itself).  For callers that order work of their own by the context's stream. */
+lddmm_bl_status lddmm_bl_join(lddmm_bl_ctx* ctx);
+
 /* Gauss-Newton-Krylov registration (eqs. BLNewton, BLKKT) starting from
  * v_bl_inout (device BL [d][K..]), which receives the result.  PCG uses
  * L~^{-1}; when precond_Z_or_null is a device array of r BL directions

@@ -168,6 +168,10 @@ lddmm_bl_status lddmm_bl_hess_matvec_on(lddmm_bl_ctx* ctx, const void* dv_bl, vo
       false);
 }
 
+lddmm_bl_status lddmm_bl_join(lddmm_bl_ctx* ctx) {
+  return guarded(ctx, [] { return 0; });
+}
+
 lddmm_bl_status lddmm_bl_gn_solve(lddmm_bl_ctx* ctx, const lddmm_bl_gn_opts* opts, void* v_bl_inout,
                                   const void* precond_Z_or_null, int32_t r, lddmm_bl_gn_report* report) {
   return guarded(ctx, [&] {

@@ -36,7 +36,7 @@ STATUS = {
 EXPORTS = [
     "lddmm_bl_create", "lddmm_bl_destroy", "lddmm_bl_last_error", "lddmm_bl_set_images",
     "lddmm_bl_state_solve", "lddmm_bl_adjoint_solve", "lddmm_bl_hess_matvec", "lddmm_bl_hess_matvec_on",
-    "lddmm_bl_gn_solve",
+    "lddmm_bl_join", "lddmm_bl_gn_solve",
     "lddmm_bl_jacobian", "lddmm_bl_project", "lddmm_bl_project_noalloc", "lddmm_bl_include", "lddmm_bl_get_field", "lddmm_bl_dot",
     "lddmm_bl_profile_enable", "lddmm_bl_profile_read", "lddmm_bl_gn_solve_batched",
     "lddmm_bl_tune_candidates", "lddmm_bl_tune_get", "lddmm_bl_tune_set", "lddmm_bl_tune_table",
@@ -105,6 +105,7 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
         "lddmm_bl_adjoint_solve": [vp, vp, dp],
         "lddmm_bl_hess_matvec": [vp, vp, vp],
         "lddmm_bl_hess_matvec_on": [vp, vp, vp, vp],
+        "lddmm_bl_join": [vp],
         "lddmm_bl_gn_solve": [vp, ctypes.POINTER(GNOpts), vp, vp, i32, ctypes.POINTER(GNReport)],
         "lddmm_bl_jacobian": [vp, vp, dp],
         "lddmm_bl_project": [vp, vp, vp, i32],
@@ -245,16 +246,30 @@ class Context:
         self.dtype = torch.float64 if prob.precision == FP64 else torch.float32
         self.device = torch.device(device) if device is not None else torch.device("cuda", torch.cuda.current_device())
         # a dedicated non-default stream: the library captures its Hessian matvec into a HIP graph on it
-        self.stream = stream if stream is not None else torch.cuda.Stream(device=self.device)
+        self._stream = stream if stream is not None else torch.cuda.Stream(device=self.device)
+        self._handed_out = stream is not None  # the program has the stream
         p = make_params(prob)
         h = ctypes.c_void_p()
         with torch.cuda.device(self.device):
-            st = self.lib.lddmm_bl_create(ctypes.byref(p), ctypes.c_void_p(self.stream.cuda_stream), ctypes.byref(h))
+            st = self.lib.lddmm_bl_create(ctypes.byref(p), ctypes.c_void_p(self._stream.cuda_stream), ctypes.byref(h))
         if st != 0:
             raise LddmmError(st, "lddmm_bl_create: " + self.lib.lddmm_bl_last_error(None).decode())
         self.h = h
 
     # -- helpers -----------------------------------------------------------
+    @property
+    def stream(self):
+        """The stream that the context's calls run on.
+
+        A program that has it may order its own work by it, so from here on Hessian products run on it too, and it
+        waits for the ones that were enqueued on a current stream before.  (A program that never asks for the
+        context's stream cannot tell where they run.)"""
+        if not self._handed_out:
+            self._handed_out = True
+            if self.h:
+                self._check(self.lib.lddmm_bl_join(self.h))
+        return self._stream
+
     def close(self):
         if getattr(self, "h", None):
             self.lib.lddmm_bl_destroy(self.h)
@@ -268,13 +283,13 @@ class Context:
 
     def _order(self):
         """Make the library's stream wait for work queued on the caller's current stream."""
-        _order_after(self.stream, torch.cuda.current_stream(self.device), self.device)
+        _order_after(self._stream, torch.cuda.current_stream(self.device), self.device)
 
     def _after(self):
         """Make the caller's current stream wait for work the library only enqueued (no host wait)."""
         cur = torch.cuda.current_stream(self.device)
-        if cur != self.stream:
-            cur.wait_stream(self.stream)
+        if cur != self._stream:
+            cur.wait_stream(self._stream)
 
     def _check(self, st, allow_warn=False):
         if st < 0 or (st > 0 and not allow_warn):
@@ -332,12 +347,17 @@ class Context:
         return g, ginf.value
 
     def hess_matvec(self, dv: torch.Tensor, out: Optional[torch.Tensor] = None) -> torch.Tensor:
-        """H dv into out, enqueued on the current stream (no host wait)."""
+        """H dv into out, enqueued (no host wait): the current stream has the result when it reaches it, and so has the
+        context's stream in a program that has that stream.
+
+        The product runs on the current stream where that is all the ordering anyone can ask for: with the product on
+        the context's stream the current one waits for it, and a queue that waits slows the dispatch of the product's
+        hundred kernels (128^3 image transport 946 -> 1067 us a call)."""
         self._arg(dv, self._vshape(), "dv")
         out = torch.empty(self._vshape(), dtype=self.dtype, device=self.device) if out is None else \
             self._arg(out, self._vshape(), "out")
         cur = torch.cuda.current_stream(self.device)
-        if torch.cuda.is_current_stream_capturing():  # the replay stays on the context's stream
+        if self._handed_out or torch.cuda.is_current_stream_capturing():
             self._order()
             self._check(self.lib.lddmm_bl_hess_matvec(self.h, _ptr(dv), _ptr(out)))
             self._after()
