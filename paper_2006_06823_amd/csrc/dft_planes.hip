@@ -169,14 +169,14 @@ __global__ __launch_bounds__(256) void k_expand(PlaneExpandArgs a) {
 // ------------------------------------------------------------------ reduction
 // Grid value of field f at a node of it for the modes: a plain field, or a pointwise product of band-limited fields
 // on the product grid.  Loads past the arrays read 0.  A plain field is the caller's and may hold infinities or NaN,
-// so the array ends with field f: the next field's values would meet the zeros past P1t's end.
+// so the array is field f alone: the next field's values would meet the zeros past P1t's end.
 template <int MODE>
 struct RedIn {
   Rsrc in, e, divv, G;
   unsigned P, en;
   __device__ __forceinline__ RedIn(const PlaneReduceArgs& a, int f) : P((unsigned)a.P), en((unsigned)a.e_node) {
     if constexpr (MODE == kRedPlain) {
-      in = rsrc(a.in, (f + 1) * a.P);
+      in = rsrc(a.in + f * a.P, a.P);
     } else {
       const int64_t ne = (MODE == kRedV1Products) ? 1 : (MODE == kRedV1Source || MODE == kRedV3Source) && a.e_node
                          ? (int64_t)(MODE == kRedV1Source ? a.nf : a.nf / 3) * 3 : 3;
@@ -192,7 +192,7 @@ struct RedIn {
   static constexpr int kRaw = MODE == kRedPlain ? 1 : MODE == kRedV1Products ? 2 : MODE == kRedV3Source ? 7 : 6;
   __device__ __forceinline__ void fetch(int f, unsigned v, unsigned u, float (&x)[kRaw]) const {
     if constexpr (MODE == kRedPlain) {
-      x[0] = bload_at(in, v, (unsigned)f * P + u);
+      x[0] = bload_at(in, v, u);
     } else if constexpr (MODE == kRedV1Products) {  // [e div v, e G0, e G1, e G2]
       x[0] = bload_at(e, v, u);
       x[1] = f == 0 ? bload_at(divv, v, u) : bload_at(G, v, (unsigned)(f - 1) * P + u);
@@ -259,7 +259,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_reduce(PlaneReduceArgs a) {
   const unsigned pbase = (unsigned)(x0 * n1 * n2);
   typedef RedIn<MODE> In;
   constexpr int JA = CH / 2;  // stage-A k-steps of a task: rows s CH + 2 j + kh
-  // k-steps of a block: the values of 32 loads, half a task of a plain field (one band tile: its operands at once)
+  // k-steps of a block: the values of 32 loads, half a task of a plain field, requested before the first product
   constexpr int JC = In::kRaw > 2 ? 4 : In::kRaw > 1 ? 8 : JA < 16 ? JA : 16;
   constexpr int NH = JA / JC > 1 ? 2 : 1;  // accumulators (shorter rounding chains)
   unsigned va[KT1], vb[KT2];  // this lane's entry of a row (kh) of P1t, of a row (4 kh) of P2t
@@ -285,7 +285,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_reduce(PlaneReduceArgs a) {
 #pragma unroll
         for (int p = 0; p < KT1; ++p) pb[p][j] = bload_at(rp1, va[p], x1 * k1);
       }
-      if constexpr (KT1 * KT2 * In::kRaw > 1) __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_sched_barrier(0);
       const int h = (jc / JC) % NH;
 #pragma unroll
       for (int j = 0; j < JC; ++j) {
