@@ -203,6 +203,10 @@ lddmm_bl_status lddmm_bl_hess_matvec_on(lddmm_bl_ctx* ctx, const void* dv_bl, vo
  * itself).  For callers that order work of their own by the context's stream. */
 lddmm_bl_status lddmm_bl_join(lddmm_bl_ctx* ctx);
 
+/* 1 if the stream has finished its work, so that nothing needs to wait for it; 0 if it has not, is under capture or
+ * cannot be asked.  Asking disturbs no capture, on this or another thread. */
+int32_t lddmm_bl_stream_idle(void* hip_stream);
+
 /* Gauss-Newton-Krylov registration (eqs. BLNewton, BLKKT) starting from
  * v_bl_inout (device BL [d][K..]), which receives the result.  PCG uses
  * L~^{-1}; when precond_Z_or_null is a device array of r BL directions

@@ -172,6 +172,20 @@ lddmm_bl_status lddmm_bl_join(lddmm_bl_ctx* ctx) {
   return guarded(ctx, [] { return 0; });
 }
 
+int32_t lddmm_bl_stream_idle(void* hip_stream) {
+  // In the default mode a query while any stream of the process is captured fails and ends that capture, as it does
+  // in any mode on a captured stream.
+  auto s = static_cast<hipStream_t>(hip_stream);
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return 0;
+  hipStreamCaptureStatus captured = hipStreamCaptureStatusNone;
+  hipError_t e = hipStreamIsCapturing(s, &captured);
+  const bool idle = e == hipSuccess && captured == hipStreamCaptureStatusNone && (e = hipStreamQuery(s)) == hipSuccess;
+  if (e != hipSuccess) (void)hipGetLastError();  // "not ready" is an answer, not an error of a later call
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  return idle ? 1 : 0;
+}
+
 lddmm_bl_status lddmm_bl_gn_solve(lddmm_bl_ctx* ctx, const lddmm_bl_gn_opts* opts, void* v_bl_inout,
                                   const void* precond_Z_or_null, int32_t r, lddmm_bl_gn_report* report) {
   return guarded(ctx, [&] {

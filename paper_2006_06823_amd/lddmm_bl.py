@@ -36,7 +36,7 @@ STATUS = {
 EXPORTS = [
     "lddmm_bl_create", "lddmm_bl_destroy", "lddmm_bl_last_error", "lddmm_bl_set_images",
     "lddmm_bl_state_solve", "lddmm_bl_adjoint_solve", "lddmm_bl_hess_matvec", "lddmm_bl_hess_matvec_on",
-    "lddmm_bl_join", "lddmm_bl_gn_solve",
+    "lddmm_bl_join", "lddmm_bl_stream_idle", "lddmm_bl_gn_solve",
     "lddmm_bl_jacobian", "lddmm_bl_project", "lddmm_bl_project_noalloc", "lddmm_bl_include", "lddmm_bl_get_field", "lddmm_bl_dot",
     "lddmm_bl_profile_enable", "lddmm_bl_profile_read", "lddmm_bl_gn_solve_batched",
     "lddmm_bl_tune_candidates", "lddmm_bl_tune_get", "lddmm_bl_tune_set", "lddmm_bl_tune_table",
@@ -106,6 +106,7 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
         "lddmm_bl_hess_matvec": [vp, vp, vp],
         "lddmm_bl_hess_matvec_on": [vp, vp, vp, vp],
         "lddmm_bl_join": [vp],
+        "lddmm_bl_stream_idle": [vp],
         "lddmm_bl_gn_solve": [vp, ctypes.POINTER(GNOpts), vp, vp, i32, ctypes.POINTER(GNReport)],
         "lddmm_bl_jacobian": [vp, vp, dp],
         "lddmm_bl_project": [vp, vp, vp, i32],
@@ -221,15 +222,11 @@ def gn_solve_batched(problems, I0s, I1s, vs, max_gn=10, max_pcg=5, grad_rtol=1e-
     return st, [reps[i].as_dict() for i in range(B)]
 
 
-def _order_after(stream, cur, device):
+def _order_after(lib, stream, cur):
     """Make `stream` wait for the work queued on `cur`.  A stream that has finished its work needs no event: asking
-    costs a microsecond, recording an event and waiting for it 19 (of the 44 of a 24^3 transform).  A stream under
-    capture cannot be asked, and only the current device's can be told to be under capture."""
-    if stream == cur:
-        return
-    if device.index == torch.cuda.current_device() and not torch.cuda.is_current_stream_capturing() and cur.query():
-        return
-    stream.wait_stream(cur)
+    costs a microsecond, recording an event and waiting for it 19 (of the 44 of a 24^3 transform)."""
+    if stream != cur and not lib.lddmm_bl_stream_idle(ctypes.c_void_p(cur.cuda_stream)):
+        stream.wait_stream(cur)
 
 
 class Context:
@@ -283,7 +280,7 @@ class Context:
 
     def _order(self):
         """Make the library's stream wait for work queued on the caller's current stream."""
-        _order_after(self._stream, torch.cuda.current_stream(self.device), self.device)
+        _order_after(self.lib, self._stream, torch.cuda.current_stream(self.device))
 
     def _after(self):
         """Make the caller's current stream wait for work the library only enqueued (no host wait)."""
@@ -536,7 +533,7 @@ class WarmStartNet:
             raise LddmmError(st, f"lddmm_nn_{what}: " + self.lib.lddmm_bl_last_error(None).decode())
 
     def _order(self):
-        _order_after(self.stream, torch.cuda.current_stream(self.device), self.device)
+        _order_after(self.lib, self.stream, torch.cuda.current_stream(self.device))
 
     def _dev(self, t, shape, name):
         if not isinstance(t, torch.Tensor) or t.device.type != "cuda" or t.dtype != torch.float32:
