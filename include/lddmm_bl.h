@@ -196,7 +196,9 @@ lddmm_bl_status lddmm_bl_hess_matvec(lddmm_bl_ctx* ctx, const void* dv_bl, void*
 /* The same enqueued on `stream` (of the context's device; NULL: the default
  * stream), for callers whose other work runs there: ordered after that
  * stream's work and after the context's earlier calls, whose later calls wait
- * for it. */
+ * for it (not those under capture: a caller orders replays after products that
+ * were enqueued outside the capture).  Neither that stream nor the context's may
+ * be under capture (E_STATE). */
 lddmm_bl_status lddmm_bl_hess_matvec_on(lddmm_bl_ctx* ctx, const void* dv_bl, void* hdv_bl, void* stream);
 
 /* The context's stream waits for the products enqueued on others (no host wait; every later call does this by

@@ -177,6 +177,8 @@ class Solver final : public SolverBase {
       return hess_matvec(dv, hdv);
     }
     require_state();
+    // (the event would tie what is captured to what is not)
+    if (capturing(s) || capturing(st_)) throw StateError("product on a caller's stream: the streams may not be under capture");
     const T* x = static_cast<const T*>(dv);
     T* y = static_cast<T*>(hdv);
     if (!mv_done_) LDDMM_HIP(hipEventCreateWithFlags(&mv_done_, hipEventDisableTiming));
@@ -199,7 +201,8 @@ class Solver final : public SolverBase {
   // before a call on the context's stream: after the last product enqueued elsewhere
   void join() override {
     st_busy_ = true;  // until the stream is waited for
-    if (!mv_pending_) return;
+    // (what is captured cannot wait for an event from outside: the next call that is not captured does)
+    if (!mv_pending_ || capturing(st_)) return;
     LDDMM_HIP(hipStreamWaitEvent(st_, mv_done_, 0));
     mv_pending_ = false;
   }
@@ -461,6 +464,11 @@ class Solver final : public SolverBase {
   }
 
   // --------------------------------------------------------- small helpers
+  static bool capturing(hipStream_t s) {
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    if (s) LDDMM_HIP(hipStreamIsCapturing(s, &c));
+    return c != hipStreamCaptureStatusNone;
+  }
   void copy(T* dst, const T* src, int64_t n) { copy_dev<T>(dst, src, n, st_); }
   void sync() {
     LDDMM_HIP(hipStreamSynchronize(st_));

@@ -288,6 +288,13 @@ class Context:
         if cur != self._stream:
             cur.wait_stream(self._stream)
 
+    def _capturing(self):
+        """The current stream of the context's device is under capture."""
+        if self.device.index in (None, torch.cuda.current_device()):
+            return torch.cuda.is_current_stream_capturing()
+        with torch.cuda.device(self.device):
+            return torch.cuda.is_current_stream_capturing()
+
     def _check(self, st, allow_warn=False):
         if st < 0 or (st > 0 and not allow_warn):
             raise LddmmError(st, self.lib.lddmm_bl_last_error(self.h).decode())
@@ -354,7 +361,7 @@ class Context:
         out = torch.empty(self._vshape(), dtype=self.dtype, device=self.device) if out is None else \
             self._arg(out, self._vshape(), "out")
         cur = torch.cuda.current_stream(self.device)
-        if self._handed_out or torch.cuda.is_current_stream_capturing():
+        if self._handed_out or self._capturing():
             self._order()
             self._check(self.lib.lddmm_bl_hess_matvec(self.h, _ptr(dv), _ptr(out)))
             self._after()
