@@ -684,7 +684,7 @@ int out_edge(const ConvLayer& L, int Di) { return (Di + 2 * L.pad - L.k) / L.str
 void check_layer(const ConvLayer& L, int Di, int B) {
   if (!((L.k == 3 && (L.stride == 1 || L.stride == 2)) || (L.k == 1 && L.stride == 1)) || L.pad < 0 || L.pad >= L.k)
     throw ArgError("convolution: kernels of 3^3 with stride 1 or 2, or 1^3 with stride 1");
-  if (B < 1 || B > 65535 || Di < 1 || (int64_t)Di * Di * Di >= (int64_t(1) << 31)) throw ArgError("convolution: size");
+  if (B < 1 || Di < 1 || (int64_t)Di * Di * Di >= (int64_t(1) << 31)) throw ArgError("convolution: size");
 }
 
 }  // namespace
