@@ -20,10 +20,15 @@
 // bounds it now is the window's arithmetic after a staging phase that a CU's two workgroups reach together
 // (staging alone 11 us of the pair's 23.5, at 6.2 TB/s).
 //
-// A node displaced by a voxel or more is interpolated apart: from the brick where its stencil lies in it,
-// else by a gather from global memory, with the same products in the same order, so a node's value depends on
-// neither the tile nor its neighbours.  The epilogue combines a node's interpolated values with its other
-// pointwise operands, fusing the SL-RK2 step update of each equation into the same pass.
+// Where one of a wave's nodes is displaced by a voxel or more, the wave sums the 64 taps of each of its nodes
+// instead, from the brick where they lie in it, else from global memory, with the same products in the same
+// order, so a node's value depends on neither the tile nor its neighbours.  Displacements of up to 1.5 voxels at
+// 128^3: one field 26 us, the adjoint pair 40 us, three fields 60 us (the window and then the displaced nodes'
+// taps: 49, 83 and 127 us; all nodes' taps always, in another layout: 34, 66 and 149 us); up to 10 voxels 102,
+// 208 and 291 us (130, 218, 353; 114, 204, 368), bound by the gathers from global memory.
+//
+// The epilogue combines a node's interpolated values with its other pointwise operands, fusing the SL-RK2 step
+// update of each equation into the same pass.
 #include "kernels.h"
 
 #include <climits>
@@ -126,6 +131,18 @@ __device__ __forceinline__ float row4(float a, float b, float c, float d, const 
   return fmaf(w[3], d, fmaf(w[2], c, fmaf(w[1], b, w[0] * a)));
 }
 
+// and of a node's own three
+__device__ __forceinline__ float node3(float a, float b, float c) {
+  return fmaf(1.f / 6.f, c, fmaf(2.f / 3.f, b, (1.f / 6.f) * a));
+}
+
+// p + n as a base that the compiler cannot see through, so that the reads around it take immediate offsets
+__device__ __forceinline__ lds_float* opaque(lds_float* p, int n) {
+  unsigned u = static_cast<unsigned>(reinterpret_cast<uintptr_t>(p + n));
+  asm volatile("" : "+v"(u));
+  return reinterpret_cast<lds_float*>(static_cast<uintptr_t>(u));
+}
+
 // periodic indices of the four taps around the node b
 __device__ __forceinline__ void tap_nodes(int b, int n, int idx[4]) {
   b = wrapi(b, n);
@@ -175,9 +192,9 @@ struct HasNode<E, std::void_t<decltype(E::NODE)>> : std::bool_constant<E::NODE> 
 //   disp(In, k)  displacement of the four departure points along axis k (grid units);
 //   finish(In, v, node, o)  results o[NO] from the interpolated values v[NF] (and the interpolants at the
 //                nodes, node[NF], if NODE).
-template <class Epi, class TL>
-__global__ __launch_bounds__(TL::NTHR, Epi::NF >= 3 ? 2 : 4) void k_brick(Epi epi, const float* __restrict__ coef,
-                                                                          Grid3 g) {
+//   RAW: fields of less than 2^29 nodes, read by 32-bit byte offsets.
+template <class Epi, class TL, bool RAW>
+__global__ __launch_bounds__(TL::NTHR, 4) void k_brick(Epi epi, const float* __restrict__ coef, Grid3 g) {
   constexpr int TX0 = TL::TX0, TX1 = TL::TX1, TX2 = TL::TX2, NTHR = TL::NTHR, QPT = TL::QPT;
   constexpr int B0 = TL::B0, B1 = TL::B1, LD = TL::LD, QB = TL::QB, NQ = TL::NQ, VOL = TL::VOL;
   constexpr int NF = Epi::NF, NE = (NQ + NTHR - 1) / NTHR, Q2 = TX2 / 4;
@@ -200,7 +217,6 @@ __global__ __launch_bounds__(TL::NTHR, Epi::NF >= 3 ? 2 : 4) void k_brick(Epi ep
   coef += comp * P;
   // staging: every load of the thread is requested before its first LDS store
   f32x4 v[NF][NE];
-  const bool rawbuf = P < (int64_t(1) << 29);  // 32-bit byte offsets within a field
   Rsrc rs[NF];
 #pragma unroll
   for (int f = 0; f < NF; ++f) rs[f] = rsrc(coef + f * Epi::FS * P, P);
@@ -211,7 +227,7 @@ __global__ __launch_bounds__(TL::NTHR, Epi::NF >= 3 ? 2 : 4) void k_brick(Epi ep
       const int row = e / QB, q = e - row * QB, b0 = row / B1, b1 = row - b0 * B1;
       const int r0 = wrap_near(t0 - HALO + b0, g.n0), r1 = wrap_near(t1 - HALO + b1, g.n1);
       const int c = wrap_near(t2 - 4 + 4 * q, g.n2);
-      if (rawbuf) {
+      if constexpr (RAW) {
         const unsigned off = ((unsigned)(r0 * g.n1 + r1) * (unsigned)g.n2 + (unsigned)c) * 4u;
 #pragma unroll
         for (int f = 0; f < NF; ++f) v[f][k] = bload4(rs[f], off);
@@ -258,37 +274,175 @@ __global__ __launch_bounds__(TL::NTHR, Epi::NF >= 3 ? 2 : 4) void k_brick(Epi ep
     }
   }
   __syncthreads();
+  // The 64 taps of the tile's node (k0, k1, k2) displaced by (e0, e1, e2), from the brick if they lie in it, else from
+  // global memory.  Where every lane's do, 4 x 4 taps of a field at a time, the next requested before the present are
+  // summed; where some do not, a plane of taps at a time, whose sums all lanes share.
+  auto taps = [&](int k0, int k1, int k2, float e0, float e1, float e2, float (&val)[NF]) {
+    const float f0 = floorf(e0), f1 = floorf(e1), f2 = floorf(e2);
+    float x0, x1, x2, u0[4], u1[4], u2[4];
+    {
+#pragma clang fp contract(off)  // not fused with the products that formed e, as in the window
+      x0 = e0 - f0, x1 = e1 - f1, x2 = e2 - f2;
+    }
+    brick_weights(x0, u0);
+    brick_weights(x1, u1);
+    brick_weights(x2, u2);
+    // (displacements beyond every grid are as good as none: the index is periodic)
+    auto whole = [](float f) { return static_cast<int>(fabsf(f) < 1e9f ? f : 0.f); };
+    const int d0 = whole(f0), d1 = whole(f1), d2 = whole(f2);
+    // first tap in the brick
+    const int s0 = k0 + HALO - 1 + d0, s1 = k1 + HALO - 1 + d1, s2 = k2 + HALO - 1 + d2;
+    const bool inb = ((unsigned)s0 <= B0 - 4) & ((unsigned)s1 <= B1 - 4) & ((unsigned)s2 <= LD - 4);
+    lds_float* p = (lds_float*)br + (inb ? (s0 * B1 + s1) * LD + s2 : 0);
+#pragma unroll
+    for (int f = 0; f < NF; ++f) val[f] = 0.f;
+    auto read = [&](lds_float* r, float (&v)[4][4]) {
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) v[b][c] = r[b * LD + c];
+    };
+    auto sum = [&](const float (&v)[4][4]) {
+      float sa = 0.f;
+#pragma unroll
+      for (int b = 0; b < 4; ++b) sa = fmaf(u1[b], row4(v[b][0], v[b][1], v[b][2], v[b][3], u2), sa);
+      return sa;
+    };
+    if (__builtin_amdgcn_ballot_w64(!inb) == 0) {
+      float d[2][4][4];
+      read(opaque(p, 0), d[0]);
+#pragma unroll
+      for (int i = 0; i < 4 * NF; ++i) {
+        if (i + 1 < 4 * NF) read(opaque(p, (i + 1) % NF * VOL + (i + 1) / NF * B1 * LD), d[(i + 1) & 1]);
+        __builtin_amdgcn_sched_barrier(0);
+        val[i % NF] = fmaf(u0[i / NF], sum(d[i & 1]), val[i % NF]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      return;
+    }
+    constexpr int FB = NF < 3 ? NF : 1;  // fields requested together, as the registers of four waves allow
+    constexpr unsigned unit = RAW ? 4u : 1u;
+    unsigned row[4] = {}, col[4] = {}, pl = 0;  // offsets of rows, columns and the plane
+    int i0 = 0;
+    if (!inb) {
+      int i1[4], i2[4];
+      i0 = wrapi(t0 + k0 + d0 % g.n0 - 1, g.n0);
+      tap_nodes(t1 + k1 + d1 % g.n1, g.n1, i1);
+      tap_nodes(t2 + k2 + d2 % g.n2, g.n2, i2);
+      pl = (unsigned)i0 * (unsigned)plane * unit;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) row[c] = (unsigned)i1[c] * (unsigned)g.n2 * unit, col[c] = (unsigned)i2[c] * unit;
+    }
+#pragma unroll 1
+    for (int a = 0; a < 4; ++a) {
+#pragma unroll
+      for (int f0 = 0; f0 < NF; f0 += FB) {
+        float v[FB][4][4];
+#pragma unroll
+        for (int f = 0; f < FB; ++f) read(p + (f0 + f) * VOL, v[f]);
+        if (!inb) {
+#pragma unroll
+          for (int c = 0; c < 4; ++c) asm volatile("" : "+v"(col[c]));  // (their 16 sums with the rows are not kept)
+#pragma unroll
+          for (int f = 0; f < FB; ++f)
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+#pragma unroll
+              for (int c = 0; c < 4; ++c)
+                if constexpr (RAW) v[f][b][c] = bload(rs[f0 + f], pl + row[b] + col[c]);
+                else v[f][b][c] = coef[(f0 + f) * Epi::FS * P + (pl + row[b] + col[c])];
+        }
+#pragma unroll
+        for (int f = 0; f < FB; ++f) val[f0 + f] = fmaf(u0[0], sum(v[f]), val[f0 + f]);
+      }
+      u0[0] = u0[1], u0[1] = u0[2], u0[2] = u0[3];
+      if (inb) p += B1 * LD;
+      pl += (unsigned)plane * unit;
+      if (++i0 == g.n0) i0 = 0, pl = 0;
+    }
+  };
 #pragma unroll
   for (int j = 0; j < QPT; ++j) {
     const int q = tid + NTHR * j, l2 = (q % Q2) * 4, l1 = (q / Q2) % TX1, l0 = q / (Q2 * TX1);
+    bool far = false;  // a node displaced by a voxel or more
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const f32x4 d = epi.disp(in[j], k);
+#pragma unroll
+      for (int n = 0; n < 4; ++n) far |= !(fabsf(d[n]) < 1.f);
+    }
+    if (__builtin_amdgcn_ballot_w64(far) != 0) {
+      // All taps (the window and the displaced nodes' taps after it take longer, see above), 64 neighbours of the
+      // wave's 256 nodes at a time, a node a lane from its operands to its results: a tap of all lanes then lies in two
+      // rows' lines and in as many banks as lanes (of the lanes' own quads, in eight rows' and a quarter of the banks).
+      // The next nodes' operands are requested before the present taps.
+      const int q0 = q - (tid & 63);
+      auto place = [&](int n, int (&m)[3]) {
+        const int e = 4 * q0 + 64 * n + (tid & 63);
+        m[0] = e / (TX1 * TX2), m[1] = e / TX2 % TX1, m[2] = e % TX2;
+        const int i1 = t1 + m[1], i2 = t2 + m[2];
+        return t0 + m[0] < g.n0 && i1 < g.n1 && i2 < g.n2
+                   ? ((unsigned)(m[0] * g.n1 + i1) * (unsigned)g.n2 + (unsigned)i2) * 4u : kOut;
+      };
+      typename Epi::In now, next;
+      int m[3];
+      unsigned at = place(0, m);
+      auto fetch = [&](typename Epi::In& x, unsigned o) {
+        epi.load(x, [&](const float* p) { return f32x4{bload(rsrc(p + base, left), o), 0.f, 0.f, 0.f}; });
+      };
+      fetch(now, at);
+#pragma unroll 1
+      for (int n = 0; n < 4; ++n) {
+        int mn[3];
+        const unsigned an = place(n + 1, mn);
+        if (n < 3) fetch(next, an);
+        float val[NF];
+        taps(m[0], m[1], m[2], epi.disp(now, 0).x, epi.disp(now, 1).x, epi.disp(now, 2).x, val);
+        f32x4 v[NF], nv[NF], o[Epi::NO];
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+          v[f] = f32x4{val[f], 0.f, 0.f, 0.f}, nv[f] = f32x4{0.f, 0.f, 0.f, 0.f};
+          if constexpr (NODE) {
+            lds_float* p = (lds_float*)br + f * VOL + ((m[0] + HALO) * B1 + m[1] + HALO) * LD + m[2] + HALO;
+#pragma unroll
+            for (int a = -1; a < 2; ++a) {
+              float sn = 0.f;
+#pragma unroll
+              for (int b = -1; b < 2; ++b) {
+                lds_float* r = p + (a * B1 + b) * LD;
+                sn = fmaf(b == 0 ? 2.f / 3.f : 1.f / 6.f, node3(r[-1], r[0], r[1]), sn);
+              }
+              nv[f].x = fmaf(a == 0 ? 2.f / 3.f : 1.f / 6.f, sn, nv[f].x);
+            }
+          }
+        }
+        epi.finish(now, v, nv, o);
+#pragma unroll
+        for (int k = 0; k < Epi::NO; ++k)
+          __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, (float)o[k].x),
+                                                rsrc(epi.out + (comp + k) * P + base, left), (int)at, 0, 0);
+        now = next, at = an;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) m[k] = mn[k];
+      }
+      continue;
+    }
     float w0[4][5], w1[4][5], w2[4][5];
-    unsigned far = 0;  // nodes displaced by a voxel or more
     {
       const f32x4 d0 = epi.disp(in[j], 0), d1 = epi.disp(in[j], 1), d2 = epi.disp(in[j], 2);
 #pragma unroll
       for (int n = 0; n < 4; ++n) {
-        if (!(fabsf(d0[n]) < 1.f && fabsf(d1[n]) < 1.f && fabsf(d2[n]) < 1.f)) far |= 1u << n;
         window_weights(d0[n], w0[n]);
         window_weights(d1[n], w1[n]);
         window_weights(d2[n], w2[n]);
       }
-    }
-    // where two or more of the wave's four nodes are interpolated apart for some lane, all are: the window would cost
-    // more than it saves
-    bool apart = false;
-    if constexpr (!NODE) {
-      int some = 0;
-#pragma unroll
-      for (int n = 0; n < 4; ++n) some += __builtin_amdgcn_ballot_w64((far >> n) & 1) != 0;
-      apart = some >= 2;
-      if (apart) far = 15;
     }
     f32x4 acc[NF], node[NF];
 #pragma unroll
     for (int f = 0; f < NF; ++f) acc[f] = node[f] = f32x4{0.f, 0.f, 0.f, 0.f};
     const float* win = br + (l0 * B1 + l1) * LD + l2;
 #pragma unroll 1
-    for (int a = apart ? 5 : 0; a < 5; ++a) {
+    for (int a = 0; a < 5; ++a) {
       f32x4 s[NF], sn[NF];
 #pragma unroll
       for (int f = 0; f < NF; ++f) s[f] = sn[f] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -308,12 +462,15 @@ __global__ __launch_bounds__(TL::NTHR, Epi::NF >= 3 ? 2 : 4) void k_brick(Epi ep
             for (int n = 0; n < 4; ++n) t[n] = fmaf(w2[n][c], r[n + c], t[n]);
 #pragma unroll
           for (int n = 0; n < 4; ++n) s[f][n] = fmaf(w1[n][b], t[n], s[f][n]);
+          // (three fields' rows are not all requested at once: 184 registers in the tiles of few threads)
+          if constexpr (NF >= 3 && !NODE)
+            if (f == NF - 1 && b % 2) __builtin_amdgcn_sched_barrier(0);
           if constexpr (NODE) {  // taps (1/6, 2/3, 1/6) around the node
             if (b >= 1 && b <= 3) {
               const float wb = b == 2 ? 2.f / 3.f : 1.f / 6.f;
 #pragma unroll
               for (int n = 0; n < 4; ++n)
-                sn[f][n] = fmaf(wb, fmaf(1.f / 6.f, r[n + 3], fmaf(2.f / 3.f, r[n + 2], (1.f / 6.f) * r[n + 1])), sn[f][n]);
+                sn[f][n] = fmaf(wb, node3(r[n + 1], r[n + 2], r[n + 3]), sn[f][n]);
             }
           }
         }
@@ -331,51 +488,6 @@ __global__ __launch_bounds__(TL::NTHR, Epi::NF >= 3 ? 2 : 4) void k_brick(Epi ep
       }
     }
     if (off[j] == kOut) continue;
-    if (far) {
-      const f32x4 d0 = epi.disp(in[j], 0), d1 = epi.disp(in[j], 1), d2 = epi.disp(in[j], 2);
-#pragma unroll 1
-      for (int n = 0; n < 4; ++n) {
-        if (!((far >> n) & 1)) continue;
-        auto pick = [&](const f32x4& d) { return n == 0 ? d.x : n == 1 ? d.y : n == 2 ? d.z : d.w; };
-        const float e0 = pick(d0), e1 = pick(d1), e2 = pick(d2);
-        const float f0 = floorf(e0), f1 = floorf(e1), f2 = floorf(e2);
-        // first tap in the brick
-        const int s0 = l0 + HALO - 1 + static_cast<int>(f0), s1 = l1 + HALO - 1 + static_cast<int>(f1),
-                  s2 = l2 + n + HALO - 1 + static_cast<int>(f2);
-        const bool inb = fabsf(e0) < 64.f && fabsf(e1) < 64.f && fabsf(e2) < 64.f && s0 >= 0 && s0 + 3 < B0 &&
-                         s1 >= 0 && s1 + 3 < B1 && s2 >= 0 && s2 + 3 < LD;
-        float u0[4], u1[4], u2[4];
-        brick_weights(e0 - f0, u0);
-        brick_weights(e1 - f1, u1);
-        brick_weights(e2 - f2, u2);
-#pragma unroll 1
-        for (int f = 0; f < NF; ++f) {
-          float val = 0.f;
-          if (inb) {
-            lds_float* p = (lds_float*)br + f * VOL + (s0 * B1 + s1) * LD + s2;
-#pragma unroll
-            for (int a = 0; a < 4; ++a) {
-              float sa = 0.f;
-#pragma unroll
-              for (int b = 0; b < 4; ++b) {
-                lds_float* r = p + (a * B1 + b) * LD;
-                sa = fmaf(u1[b], row4(r[0], r[1], r[2], r[3], u2), sa);
-              }
-              val = fmaf(u0[a], sa, val);
-            }
-          } else {
-            // (displacements beyond every grid are as good as none: the index is periodic)
-            auto node = [](int i, float fl, int n) { return i + static_cast<int>(fabsf(fl) < 1e9f ? fl : 0.f) % n; };
-            val = eval_global(coef + f * Epi::FS * P, node(t0 + l0, f0, g.n0), node(t1 + l1, f1, g.n1),
-                              node(t2 + l2 + n, f2, g.n2), e0 - f0, e1 - f1, e2 - f2, g.n0, g.n1, g.n2);
-          }
-#pragma unroll
-          for (int m = 0; m < 4; ++m)
-#pragma unroll
-            for (int h = 0; h < NF; ++h) acc[h][m] = (m == n && h == f) ? val : acc[h][m];
-        }
-      }
-    }
     f32x4 o[Epi::NO];
     epi.finish(in[j], acc, node, o);
     const int last = g.n2 - (t2 + l2);  // nodes left in the row
@@ -509,11 +621,11 @@ struct EpiCharacteristics : Shape<3> {
   }
 };
 
-template <class Epi, class TL>
+template <class Epi, class TL, bool RAW = true>
 void launch_tile(const std::string& name, double bytes, const Epi& epi, const float* coef, const Grid3& g,
                  hipStream_t s) {
   dim3 grid(ceil_div(g.n2, TL::TX2) * Epi::NC, ceil_div(g.n1, TL::TX1), ceil_div(g.n0, TL::TX0));
-  prof::launch(name, bytes, 0.0, k_brick<Epi, TL>, grid, dim3(TL::NTHR), 0, s, epi, coef, g);
+  prof::launch(name, bytes, 0.0, k_brick<Epi, TL, RAW>, grid, dim3(TL::NTHR), 0, s, epi, coef, g);
 }
 
 std::string shape_key(const Dims& d) {
@@ -524,6 +636,11 @@ template <class Epi>
 void launch(const std::string& name, double bytes, const Epi& epi, const float* coef, const Dims& d,
             hipStream_t s, int tile = -1) {
   const Grid3 g{d.n[0], d.n[1], d.n[2], d.P};
+  if (d.P >= (int64_t(1) << 29)) {
+    launch_tile<Epi, TileA, false>(name, bytes, epi, coef, g, s);
+    LDDMM_LAUNCH_CHECK();
+    return;
+  }
   if (tile < 0) tile = std::max(0, tune::get(shape_key(d) + ":gs" + std::to_string(Epi::NF), 0));
   switch (tile) {
     case 1:
