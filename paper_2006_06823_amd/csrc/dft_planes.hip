@@ -28,7 +28,6 @@
 
 #include <algorithm>
 #include <string>
-#include <vector>
 
 namespace lddmm {
 
@@ -48,25 +47,16 @@ __device__ __forceinline__ void zero16(f32x16& a) {
   for (int r = 0; r < 16; ++r) a[r] = 0.f;
 }
 
-constexpr int kMaxKh = 32;  // k-steps of a contraction over a band axis (K <= 64)
-
-// Raw buffer loads: one 32-bit offset register per load (the compiler batches them instead of waiting
-// on each 64-bit address), and the hardware range check returns 0 for an offset at or past the end of
-// the buffer, so a tile that runs past the last row of an array reads zeros.  kOut is such an offset.
+// Raw buffer loads: a byte offset per lane (a register that loads at uniform distances share) and an element offset
+// uniform across the wave.  The hardware's range check covers the sum of the two and returns 0 at or past the end of
+// the buffer, so a tile that runs past the last row of an array reads zeros, as it does with a lane offset of kOut.
+// (The tests' short and odd axes give wrong sums where a row past the end reads anything else.)
 typedef __amdgpu_buffer_rsrc_t Rsrc;
 constexpr unsigned kOut = 0xFFFFFFF0u;
 __device__ __forceinline__ Rsrc rsrc(const float* p, int64_t n) {
   const int64_t bytes = n * 4 < 0x7FFFFFF0 ? n * 4 : 0x7FFFFFF0;
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), (short)0, (int)bytes, 0x00020000);
 }
-__device__ __forceinline__ float bload(Rsrc r, unsigned idx) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)(idx * 4u), 0, 0));
-}
-__device__ __forceinline__ float bload_if(Rsrc r, unsigned idx, bool ok) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)(ok ? idx * 4u : kOut), 0, 0));
-}
-
-// byte offset in a register, element offset uniform: loads at uniform distances share the register
 __device__ __forceinline__ float bload_at(Rsrc r, unsigned voff, unsigned uidx) {
   return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)voff, (int)(uidx * 4u), 0));
 }
@@ -850,23 +840,19 @@ void plane_reduce(const PlaneReduceArgs& a, hipStream_t s) {
   }
 }
 
-// one wave per 32 x 32 tile of a plane (at most 8), their partials in ceil(tiles / 2) slots of at
-// most 64 KB of LDS together.  The fused pass is chosen for inner bands of at most 32 (one band tile
-// per axis): with two, every workgroup's repeated expansions (each output field's workgroup expands
-// the e components it reads) cost more than the separate kernels save (160x192x160 / 40x48x40
-// deformation state: 46 us per fused launch against 30 us for the separate reduction).
-static size_t prod_plane_lds(int tiles, int kt) { return (size_t)((tiles + 1) / 2) * kt * 4096; }
-bool prod_plane_ok(const Dims& d) {
-  const int tiles = ceil_div(d.n[1], 32) * ceil_div(d.n[2], 32);
-  const int kt = (d.k[1] > 32 ? 2 : 1) * (d.k[2] > 32 ? 2 : 1);
-  return planes_ok(d) && tiles <= 8 && kt == 1 && prod_plane_lds(tiles, kt) <= 64 * 1024;
+// one wave per 32 x 32 tile of a plane (at most 8), their partials in ceil(tiles / 2) slots of 4 KB of
+// LDS.  The fused pass is chosen for inner bands of at most 32 (one band tile per axis): with two,
+// every workgroup's repeated expansions (each output field's workgroup expands the e components it
+// reads) cost more than the separate kernels save (160x192x160 / 40x48x40 deformation state: 46 us
+// per fused launch against 30 us for the separate reduction).
+static bool prod_plane_fits(int n1, int n2, int k1, int k2) {
+  return ceil_div(n1, 32) * ceil_div(n2, 32) <= 8 && k1 <= 32 && k2 <= 32;
 }
+bool prod_plane_ok(const Dims& d) { return planes_ok(d) && prod_plane_fits(d.n[1], d.n[2], d.k[1], d.k[2]); }
 
 void plane_prod(const ProdPlaneArgs& a, hipStream_t s) {
+  if (!prod_plane_fits(a.n1, a.n2, a.k1, a.k2)) throw ArgError("plane_prod: plane or band too large");
   const int tiles = ceil_div(a.n1, 32) * ceil_div(a.n2, 32);
-  const int kt1 = a.k1 > 32 ? 2 : 1, kt2 = a.k2 > 32 ? 2 : 1;
-  if (tiles > 8 || kt1 * kt2 != 1 || prod_plane_lds(tiles, 1) > 64 * 1024)
-    throw ArgError("plane_prod: plane or band too large");
   if (a.P >= (int64_t(1) << 31)) throw ArgError("plane_prod: field too large");
   const int nf = a.mode == kRedV1Products ? 4 : 6;
   const int ne = a.mode == kRedV1Products ? 1 : 3;
@@ -877,14 +863,10 @@ void plane_prod(const ProdPlaneArgs& a, hipStream_t s) {
                         (double)a.k1 * a.n2 * a.k2);
   dim3 g(static_cast<unsigned>(nf * a.n0));
   const dim3 b(64 * tiles);
-  const size_t lds = prod_plane_lds(tiles, kt1 * kt2);
+  const size_t lds = (size_t)((tiles + 1) / 2) * 4096;
   auto go = [&](auto kern) { prof::launch("k_prod_plane", bytes, flops, kern, g, b, lds, s, a); };
-  auto pick = [&](auto mode) {
-    constexpr int M = decltype(mode)::value;
-    go(k_prod_plane<M>);
-  };
-  if (a.mode == kRedV1Products) pick(std::integral_constant<int, kRedV1Products>{});
-  else if (a.mode == kRedV3Products) pick(std::integral_constant<int, kRedV3Products>{});
+  if (a.mode == kRedV1Products) go(k_prod_plane<kRedV1Products>);
+  else if (a.mode == kRedV3Products) go(k_prod_plane<kRedV3Products>);
   else throw ArgError("plane_prod: unknown mode");
   LDDMM_LAUNCH_CHECK();
 }
