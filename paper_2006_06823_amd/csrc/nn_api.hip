@@ -151,6 +151,7 @@ class Net {
   }
 
   void forward(const float* in, int B, float* out) {
+    out_ = nullptr;  // no pass to go back through until this one is done
     ensure(B);
     pack_weights(layers_.data(), packed_at_.data(), (int)layers_.size(), false, st_);
     const float* x = in;
@@ -394,6 +395,7 @@ lddmm_bl_status nn_guard(lddmm_nn_ctx* c, F&& f) {
     lddmm::set_global_error(e.what());
     return LDDMM_BL_E_STATE;
   } catch (const std::bad_alloc&) {
+    (void)hipGetLastError();  // (the next launch's check would find it)
     lddmm::set_global_error("device allocation failed");
     return LDDMM_BL_E_OOM;
   } catch (const std::exception& e) {
